@@ -743,33 +743,26 @@ int check_err(Group* g) {
     return SIPF_OK;
 }
 
-// 2-D: natural (kx, ky) half spectrum H x (H/2+1) <-> the device layout
+// 2-D: natural (kx, ky) half spectrum H x (H/2+1) -> the device layout
 // (H/2+1) x H, ky-major with kx in the FFT storage order
-void permute_spectrum2(const void* src, void* dst, int H, size_t tsize, bool to_perm) {
+void permute_spectrum2(const void* src, void* dst, int H, size_t tsize) {
     const int HH = H / 2 + 1;
     const size_t e = 2 * tsize;
     for (int kx = 0; kx < H; ++kx) {
         const int p = fft_perm(H, kx);
-        for (int ky = 0; ky < HH; ++ky) {
-            const size_t nat = (size_t)kx * HH + ky;
-            const size_t per = (size_t)ky * H + p;
-            if (to_perm) std::memcpy((char*)dst + per * e, (const char*)src + nat * e, e);
-            else std::memcpy((char*)dst + nat * e, (const char*)src + per * e, e);
-        }
+        for (int ky = 0; ky < HH; ++ky)
+            std::memcpy((char*)dst + ((size_t)ky * H + p) * e, (const char*)src + ((size_t)kx * HH + ky) * e, e);
     }
 }
 
-// natural <-> permuted (kx, ky) layout of a half spectrum (host arrays of 2*T per entry)
-void permute_spectrum(const void* src, void* dst, int H, size_t tsize, bool to_perm) {
+// natural -> permuted (kx, ky) layout of a half spectrum (host arrays of 2*T per entry)
+void permute_spectrum(const void* src, void* dst, int H, size_t tsize) {
     const int HH = H / 2 + 1;
     const size_t e = 2 * tsize;
     for (int kx = 0; kx < H; ++kx)
-        for (int ky = 0; ky < H; ++ky) {
-            const size_t nat = ((size_t)kx * H + ky) * HH;
-            const size_t per = ((size_t)fft_perm(H, kx) * H + fft_perm(H, ky)) * HH;
-            if (to_perm) std::memcpy((char*)dst + per * e, (const char*)src + nat * e, HH * e);
-            else std::memcpy((char*)dst + nat * e, (const char*)src + per * e, HH * e);
-        }
+        for (int ky = 0; ky < H; ++ky)
+            std::memcpy((char*)dst + ((size_t)fft_perm(H, kx) * H + fft_perm(H, ky)) * HH * e,
+                        (const char*)src + ((size_t)kx * H + ky) * HH * e, HH * e);
 }
 
 // Set up the group's instances (parameters already in g->in): tuning, H
@@ -952,8 +945,8 @@ template <typename T> int init_fields(Group* g, int i, const void* alpha0, int a
     else std::memcpy(nat.data(), alpha0, nat.size() * sizeof(T));
     for (T v : nat)
         if (!std::isfinite((double)v)) return fail(SIPF_ENUMERIC, "non-finite alpha0");
-    if (I.dim == 2) permute_spectrum2(nat.data(), per.data(), H, sizeof(T), true);
-    else permute_spectrum(nat.data(), per.data(), H, sizeof(T), true);
+    if (I.dim == 2) permute_spectrum2(nat.data(), per.data(), H, sizeof(T));
+    else permute_spectrum(nat.data(), per.data(), H, sizeof(T));
     HIPCHK(hipMemcpyAsync(I.alpha, per.data(), per.size() * sizeof(T), hipMemcpyHostToDevice, g->stream));
     HIPCHK(field_x<T>(g, H, fdesc_dev<T>(g, g->fslot[i]), 1, XP_GRAD));
     HIPCHK(field_inv<T>(g, H, fdesc_dev<T>(g, g->fslot[i]), 1, I.dim));
@@ -1053,14 +1046,15 @@ template <typename T> int get_field_typed(Group* g, int i, int which, void* out,
     const Inst& I = g->in[i];
     if (g->method == SIPF_METHOD_DIRECT) {
         if (which != SIPF_FIELD_ALPHA) return fail(SIPF_EINVAL, "a direct SIPF context has no grids");
+        // the kz = 0 .. H/2 part of every row of the full spectrum, packed in the partial-sum
+        // scratch (every step writes it before reading it)
         const int H = I.H, HH = H / 2 + 1;
-        std::vector<T> full(2 * (size_t)H * H * H), half(2 * (size_t)H * H * HH);
-        HIPCHK(hipMemcpyAsync(full.data(), I.alpha, full.size() * sizeof(T), hipMemcpyDeviceToHost, g->stream));
+        const size_t V = 2 * sizeof(T);
+        HIPCHK(hipMemcpy2DAsync(I.part, HH * V, I.alpha, H * V, HH * V, (size_t)H * H, hipMemcpyDeviceToDevice,
+                                g->stream));
+        HIPCHK(hipMemcpyAsync(out, I.part, HH * V * H * H, on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost,
+                              g->stream));
         HIPCHK(hipStreamSynchronize(g->stream));
-        for (size_t r = 0; r < (size_t)H * H; ++r)
-            std::memcpy(half.data() + 2 * r * HH, full.data() + 2 * r * H, 2 * HH * sizeof(T));
-        if (on_device) HIPCHK(hipMemcpy(out, half.data(), half.size() * sizeof(T), hipMemcpyHostToDevice));
-        else std::memcpy(out, half.data(), half.size() * sizeof(T));
         return check_err(g);
     }
     const int H = I.H;
@@ -1077,13 +1071,13 @@ template <typename T> int get_field_typed(Group* g, int i, int which, void* out,
     } else if (which == SIPF_FIELD_GRAD) {
         HIPCHK(hipMemcpyAsync(out, I.G, I.dim * ng * sizeof(T), kind, g->stream));
     } else if (which == SIPF_FIELD_ALPHA) {
-        std::vector<T> per(2 * nspec), nat(2 * nspec);
-        HIPCHK(hipMemcpyAsync(per.data(), I.alpha, per.size() * sizeof(T), hipMemcpyDeviceToHost, g->stream));
-        HIPCHK(hipStreamSynchronize(g->stream));
-        if (I.dim == 2) permute_spectrum2(per.data(), nat.data(), H, sizeof(T), false);
-        else permute_spectrum(per.data(), nat.data(), H, sizeof(T), false);
-        if (on_device) HIPCHK(hipMemcpy(out, nat.data(), nat.size() * sizeof(T), hipMemcpyHostToDevice));
-        else std::memcpy(out, nat.data(), nat.size() * sizeof(T));
+        // natural order on the device: straight into out, or by way of B1 (overwritten by the
+        // next step's first field pass before it is read) to the host or to a device address
+        // that is not aligned for whole complex values
+        const bool straight = on_device && (uintptr_t)out % sizeof(cplx_t<T>) == 0;
+        cplx_t<T>* nat = straight ? (cplx_t<T>*)out : (cplx_t<T>*)I.B1;
+        HIPCHK(launch_natural<T>(I.dim, H, (const cplx_t<T>*)I.alpha, nat, g->stream));
+        if (!straight) HIPCHK(hipMemcpyAsync(out, nat, 2 * nspec * sizeof(T), kind, g->stream));
     } else {
         return fail(SIPF_EINVAL, "unknown field");
     }

@@ -45,6 +45,69 @@ int fft_perm(int N, int k) {
     return (k % N1) * N2 + k / N1;
 }
 
+// ---------------------------------------------------------------------------
+// Storage order -> natural order of a half spectrum (the ABI's layout), on the
+// device.  Both kernels are copies bound by memory: 3-D rows along kz move
+// whole (one thread per value, writes coalesced), the 2-D spectrum is
+// transposed through LDS.  Against a read-back, a permutation on the host and
+// a copy to the device again, reading alpha takes 34.4 -> 0.09 ms at H = 256,
+// 1.4 -> 0.05 ms at H = 128 and 14 -> 0.05 ms at H = 2048 in 2-D.
+// ---------------------------------------------------------------------------
+struct PermMap {
+    int pm, pt, n1, n2;  // length pm pt: pt blocks of pm, each in two-stage order pm = n1 n2
+    __device__ __forceinline__ int pos(int k) const {
+        const int r = k / pt;
+        return (k % pt) * pm + (r % n1) * n2 + r / n1;
+    }
+    __device__ __forceinline__ int freq(int p) const {
+        const int r = p % pm;
+        return p / pm + pt * (r / n2 + n1 * (r % n2));
+    }
+};
+
+template <typename V>
+__global__ __launch_bounds__(256) void k_natural3(const V* __restrict__ per, V* __restrict__ nat, int H, PermMap m) {
+    const int HH = H / 2 + 1;
+    const int n = H * H * HH;
+    const int e = (int)(blockIdx.x * 256 + threadIdx.x);
+    if (e >= n) return;
+    const int row = e / HH, kz = e - row * HH;
+    const int kx = row / H, ky = row - kx * H;
+    nat[e] = per[(m.pos(kx) * H + m.pos(ky)) * HH + kz];
+}
+
+constexpr int NT2 = 32;  // tile of the 2-D transposition
+template <typename V>
+__global__ __launch_bounds__(256) void k_natural2(const V* __restrict__ per, V* __restrict__ nat, int H, PermMap m) {
+    __shared__ V t[NT2][NT2 + 1];
+    const int HH = H / 2 + 1;
+    const int p0 = blockIdx.x * NT2, k0 = blockIdx.y * NT2;  // storage position of kx; ky
+    const int c = threadIdx.x % NT2, r0 = threadIdx.x / NT2;
+    for (int r = r0; r < NT2; r += 256 / NT2)
+        if (k0 + r < HH && p0 + c < H) t[r][c] = per[(size_t)(k0 + r) * H + p0 + c];
+    __syncthreads();
+    for (int r = r0; r < NT2; r += 256 / NT2)
+        if (p0 + r < H && k0 + c < HH) nat[(size_t)m.freq(p0 + r) * HH + k0 + c] = t[c][r];
+}
+
+template <typename T>
+hipError_t launch_natural(int dim, int H, const cplx_t<T>* per, cplx_t<T>* nat, hipStream_t s) {
+    PermMap m;
+    m.pm = H > 256 ? H / 16 : H;
+    m.pt = H > 256 ? 16 : 1;
+    m.n2 = fft_perm(m.pm, 1);
+    m.n1 = m.pm / m.n2;
+    const int HH = H / 2 + 1;
+    if (dim == 2)
+        hipLaunchKernelGGL((k_natural2<cplx_t<T>>), dim3((H + NT2 - 1) / NT2, (HH + NT2 - 1) / NT2), dim3(256), 0, s,
+                           per, nat, H, m);
+    else
+        hipLaunchKernelGGL((k_natural3<cplx_t<T>>), dim3((H * H * HH + 255) / 256), dim3(256), 0, s, per, nat, H, m);
+    return hipGetLastError();
+}
+template hipError_t launch_natural<float>(int, int, const cplx_t<float>*, cplx_t<float>*, hipStream_t);
+template hipError_t launch_natural<double>(int, int, const cplx_t<double>*, cplx_t<double>*, hipStream_t);
+
 // 3-D grids: powers of two 8 .. 256 and the mixed-radix sizes 12, 22, 46, 90;
 // FP64 up to 64 (the plane passes' LDS)
 bool fft_size_supported(int H, bool fp64) {

@@ -170,6 +170,9 @@ template <typename T> hipError_t launch_inv_rows2(int H, const FieldDesc<T>* fd,
 bool fft2d_size_supported(int H);
 // digit permutation of the LDS FFT of length N: storage position of frequency k
 int fft_perm(int N, int k);
+// half spectrum in the FFT's storage order -> natural order (3-D or 2-D), out of place
+template <typename T>
+hipError_t launch_natural(int dim, int H, const cplx_t<T>* per, cplx_t<T>* nat, hipStream_t s);
 
 // --- particle pass (particles.hip) -------------------------------------------
 // nitems: the item list's header, [0] the count the sort writes and [1] the
