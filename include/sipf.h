@@ -348,7 +348,9 @@ int sipf_profile_read(sipf_ctx* ctx, double* ms, int64_t* launches);
 int sipf_save(sipf_ctx* ctx, const char* path);
 int sipf_load(const char* path, void* hip_stream, sipf_ctx** out);
 
-/* Release all device memory of the context (NULL is a no-op). */
+/* Release the context and its device memory (NULL is a no-op).  Up to 1 GiB per
+ * device of the memory of destroyed contexts and batches is kept for the next
+ * ones (sipf_release_cached_memory returns it). */
 int sipf_destroy(sipf_ctx* ctx);
 
 /* Message of the last failure on this thread ("" if none). */
@@ -426,7 +428,8 @@ int sipf_dbg_deposit(const sipf_params* prm, int64_t count, const void* X, void*
                      void* hip_stream);
 
 /* Return to the device the work buffers that sipf_adjoint keeps between
- * calls (on every device).  Call with no adjoint running. */
+ * calls and the memory kept from destroyed contexts and batches (on every
+ * device).  Call with no adjoint running. */
 int sipf_release_cached_memory(void);
 
 /*

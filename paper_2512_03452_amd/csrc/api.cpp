@@ -234,7 +234,9 @@ struct Group {
     WorkItem* items = nullptr;  // concatenated work items of the particle pass
     int* nitems = nullptr;  // [0] item count, [1] ticket counter of the persistent passes (zero between launches)
     int items_cap = 0;
-    std::vector<void*> allocs;
+    void* arena = nullptr;  // the block that holds the group's buffers (Arena)
+    size_t arena_bytes = 0;
+    std::vector<void*> allocs;  // buffers made later (diagnostics)
     void* diag = nullptr;  // diagnostics scratch, allocated on first use
     // captured graphs of run segments, by (buffer set, steps since the last
     // sort, segment length, whether the tile counts of a due sort are ready):
@@ -263,6 +265,79 @@ struct sipf_batch : Group {};
 
 namespace {
 
+// Device blocks kept for later use instead of freed: hipMalloc and hipFree
+// cost tens of microseconds to milliseconds each, and hipFree waits for the
+// device.  A block goes to any later request on the same device that it fits
+// (best fit, at most twice the request).  Its last use has ended when it is
+// put back (the owner waits for its stream), so the next owner may use it on
+// any stream.  sipf_release_cached_memory returns the blocks.
+struct BufCache {
+    struct Blk {
+        int dev;
+        size_t n;
+        void* p;
+    };
+    explicit BufCache(size_t most) : limit(most) {}
+    const size_t limit;  // bytes kept per device at most
+    std::mutex mu;
+    std::vector<Blk> free_blocks;
+    // *got: the size of the block, to be handed back with it
+    hipError_t get(size_t n, void** out, size_t* got) {
+        int dev = 0;
+        hipError_t e = hipGetDevice(&dev);
+        if (e != hipSuccess) return e;
+        {
+            std::lock_guard<std::mutex> lock(mu);
+            int best = -1;
+            for (int i = 0; i < (int)free_blocks.size(); ++i) {
+                const Blk& b = free_blocks[i];
+                if (b.dev == dev && b.n >= n && b.n <= 2 * n && (best < 0 || b.n < free_blocks[best].n)) best = i;
+            }
+            if (best >= 0) {
+                *out = free_blocks[best].p;
+                *got = free_blocks[best].n;
+                free_blocks.erase(free_blocks.begin() + best);
+                return hipSuccess;
+            }
+        }
+        *got = n;
+        return hipMalloc(out, n);
+    }
+    void put(void* p, size_t n) {
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess) {
+            (void)hipGetLastError();
+            (void)hipFree(p);
+            return;
+        }
+        {
+            std::lock_guard<std::mutex> lock(mu);
+            size_t held = 0;
+            for (const Blk& b : free_blocks) held += b.dev == dev ? b.n : 0;
+            if (held + n <= limit) {
+                free_blocks.push_back({dev, n, p});
+                return;
+            }
+        }
+        (void)hipFree(p);
+    }
+    void release() {
+        std::lock_guard<std::mutex> lock(mu);
+        for (const Blk& b : free_blocks) {
+            int cur = 0;
+            if (hipGetDevice(&cur) == hipSuccess && cur != b.dev) (void)hipSetDevice(b.dev);
+            (void)hipFree(b.p);
+            if (cur != b.dev) (void)hipSetDevice(cur);
+        }
+        free_blocks.clear();
+    }
+};
+// The adjoint's work buffers (about 2 GB of tape, segment and noise buffers in
+// an FP64 adjoint of 2e6 particles), and the blocks of destroyed contexts and
+// batches, of which at most 1 GiB per device stays.
+BufCache g_buf_cache(SIZE_MAX);
+BufCache g_group_cache(size_t(1) << 30);
+
 int dalloc(Group* g, void** p, size_t bytes) {
     *p = nullptr;
     if (bytes == 0) bytes = 16;
@@ -275,6 +350,47 @@ int dalloc(Group* g, void** p, size_t bytes) {
     g->allocs.push_back(*p);
     return SIPF_OK;
 }
+
+// The device memory of a group: every buffer is a part of one block, so that
+// creating and destroying a group costs one allocation however many instances
+// it has (a 64-instance batch held 860 buffers: 11 ms to create and 85 ms to
+// destroy, now 1.3 and 0.5 ms).  want() names a buffer, commit() allocates the
+// block and sets the pointers.
+struct Arena {
+    struct Part {
+        void** p;
+        size_t off;
+    };
+    std::vector<Part> parts;
+    size_t size = 0;
+    template <typename Q> void want(Q** p, size_t bytes) {
+        *p = nullptr;
+        // large buffers start on a 2 MiB page, as allocations of their own do (packed at
+        // 256 bytes, the particle pass at H = 256 took 747 instead of 620 us)
+        const size_t to = bytes >= (size_t(4) << 20) ? size_t(2) << 20 : 256;
+        size = (size + to - 1) / to * to;
+        parts.push_back({(void**)p, size});
+        size += bytes;
+    }
+    int commit(Group* g) {
+        const size_t n = (size + 65535) / 65536 * 65536;
+        hipError_t e = g_group_cache.get(n, &g->arena, &g->arena_bytes);
+        if (e != hipSuccess) {
+            // give the kept blocks back and try once more
+            (void)hipGetLastError();
+            g_group_cache.release();
+            g_buf_cache.release();
+            e = g_group_cache.get(n, &g->arena, &g->arena_bytes);
+        }
+        if (e != hipSuccess) {
+            g->arena = nullptr;
+            (void)hipGetLastError();
+            return fail(SIPF_ENOMEM, std::string("hipMalloc failed: ") + hipGetErrorString(e));
+        }
+        for (const Part& q : parts) *q.p = (char*)g->arena + q.off;
+        return SIPF_OK;
+    }
+};
 
 // The parameter-derived fields of a particle descriptor (buffers left null).
 template <typename T> PartDesc<T> pdesc_params(const sipf_params& p, int64_t P, int H, int dim, int tile) {
@@ -337,20 +453,6 @@ template <typename T> FieldDesc<T> make_fdesc(const Group* g, int i) {
     const double h0 = filter_h0(&p);
     f.filt = p.H0 < 0 ? (T)0 : (T)(2.0 * M_PI * M_PI / (h0 * h0));
     return f;
-}
-
-template <typename T> int upload_descs(Group* g) {
-    const int n = (int)g->in.size();
-    std::vector<PartDesc<T>> pd(2 * n);
-    std::vector<FieldDesc<T>> fd(n);
-    for (int i = 0; i < n; ++i) {
-        pd[i] = make_pdesc<T>(g, i, 0);
-        pd[n + i] = make_pdesc<T>(g, i, 1);
-        fd[g->fslot[i]] = make_fdesc<T>(g, i);
-    }
-    HIPCHK(hipMemcpy(g->pdesc, pd.data(), pd.size() * sizeof(PartDesc<T>), hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(g->fdesc, fd.data(), fd.size() * sizeof(FieldDesc<T>), hipMemcpyHostToDevice));
-    return SIPF_OK;
 }
 
 template <typename T> const PartDesc<T>* pdesc_dev(const Group* g, int set) {
@@ -774,18 +876,20 @@ template <typename T> int alloc_direct(Group* g) {
     const size_t V = 2 * sizeof(T);
     I.nslices = dir_slices(I.H, I.P);
     I.mslices = dir_mode_slices(I.H, I.P);
-    if ((rc = dalloc(g, &I.xs[0], I.P * sizeof(T)))) return rc;
-    if ((rc = dalloc(g, &I.ys[0], I.P * sizeof(T)))) return rc;
-    if ((rc = dalloc(g, &I.zs[0], I.P * sizeof(T)))) return rc;
-    if ((rc = dalloc(g, (void**)&I.ids[0], I.P * sizeof(uint32_t)))) return rc;
-    if ((rc = dalloc(g, &I.alpha, H3 * V))) return rc;
-    if ((rc = dalloc(g, &I.gc, 3 * H3 * V))) return rc;
-    if ((rc = dalloc(g, &I.part, (size_t)I.nslices * H3 * V))) return rc;
-    if ((rc = dalloc(g, &I.gpart, (size_t)I.mslices * 3 * I.P * sizeof(T)))) return rc;
-    if ((rc = dalloc(g, (void**)&g->steps, sizeof(uint32_t)))) return rc;
-    if ((rc = dalloc(g, (void**)&g->errs, sizeof(int)))) return rc;
-    HIPCHK(hipMemset(g->steps, 0, sizeof(uint32_t)));
-    HIPCHK(hipMemset(g->errs, 0, sizeof(int)));
+    Arena ar;
+    ar.want(&g->steps, sizeof(uint32_t));
+    ar.want(&g->errs, sizeof(int));
+    const size_t zeros = ar.size;
+    ar.want(&I.xs[0], I.P * sizeof(T));
+    ar.want(&I.ys[0], I.P * sizeof(T));
+    ar.want(&I.zs[0], I.P * sizeof(T));
+    ar.want(&I.ids[0], I.P * sizeof(uint32_t));
+    ar.want(&I.alpha, H3 * V);
+    ar.want(&I.gc, 3 * H3 * V);
+    ar.want(&I.part, (size_t)I.nslices * H3 * V);
+    ar.want(&I.gpart, (size_t)I.mslices * 3 * I.P * sizeof(T));
+    if ((rc = ar.commit(g))) return rc;
+    HIPCHK(hipMemsetAsync(g->arena, 0, zeros, g->stream));
     g->classes.push_back(HClass{I.H, 0, 1});
     g->fslot.assign(1, 0);
     return SIPF_OK;
@@ -817,62 +921,72 @@ template <typename T> int alloc_group(Group* g) {
     int64_t cap = 0;
     const int sc = sort_chunk();
     for (int i = 0; i < n; ++i) {
-        Inst& I = g->in[i];
-        const int64_t P = I.P;
-        const int d = I.dim;
-        const size_t ng = grid_size(I.H, d);
-        const size_t nspec = spec_size(I.H, d);
-        for (int s = 0; s < 2; ++s) {
-            if ((rc = dalloc(g, &I.xs[s], P * sizeof(T)))) return rc;
-            if ((rc = dalloc(g, &I.ys[s], P * sizeof(T)))) return rc;
-            if (d == 3 && (rc = dalloc(g, &I.zs[s], P * sizeof(T)))) return rc;
-            if ((rc = dalloc(g, (void**)&I.ids[s], P * sizeof(uint32_t)))) return rc;
-        }
-        if ((rc = dalloc(g, &I.phi, ng * sizeof(T)))) return rc;
-        if ((rc = dalloc(g, &I.B1, nspec * 2 * sizeof(T)))) return rc;
-        if ((rc = dalloc(g, &I.alpha, nspec * 2 * sizeof(T)))) return rc;
-        if ((rc = dalloc(g, &I.gspec, d * nspec * 2 * sizeof(T)))) return rc;
-        if ((rc = dalloc(g, &I.G, d * ng * sizeof(T)))) return rc;
-        for (int64_t b = 0; b < P; b += sc) chunks.push_back(SortChunk{b, i, 0});
+        const Inst& I = g->in[i];
+        for (int64_t b = 0; b < I.P; b += sc) chunks.push_back(SortChunk{b, i, 0});
         const int nt = (I.H + I.tile - 1) / I.tile;  // tiles per axis, the last may be partial
         seg_off[i] = (int)cap;
         const int64_t ch = std::min(g->chunk, g->adj_chunk);  // the smaller item size gives more items
-        cap += (P + ch - 1) / ch + (d == 2 ? (int64_t)nt * nt : (int64_t)nt * nt * nt);
+        cap += (I.P + ch - 1) / ch + (I.dim == 2 ? (int64_t)nt * nt : (int64_t)nt * nt * nt);
     }
     if (cap >= (int64_t(1) << 31) || chunks.size() >= (size_t(1) << 31))
         return fail(SIPF_EINVAL, "too many particles in one group");
     g->items_cap = (int)cap;
     g->nchunks = (int)chunks.size();
-    if ((rc = dalloc(g, (void**)&g->counts, (size_t)n * mk * sizeof(uint32_t)))) return rc;
-    if ((rc = dalloc(g, (void**)&g->cursor, (size_t)n * mk * sizeof(uint32_t)))) return rc;
-    if ((rc = dalloc(g, (void**)&g->steps, n * sizeof(uint32_t)))) return rc;
-    if ((rc = dalloc(g, (void**)&g->errs, n * sizeof(int)))) return rc;
-    if ((rc = dalloc(g, &g->pdesc, 2 * n * sizeof(PartDesc<T>)))) return rc;
-    if ((rc = dalloc(g, &g->fdesc, n * sizeof(FieldDesc<T>)))) return rc;
-    if ((rc = dalloc(g, (void**)&g->chunks, chunks.size() * sizeof(SortChunk)))) return rc;
-    if ((rc = dalloc(g, (void**)&g->seg, cap * sizeof(WorkItem)))) return rc;
-    if ((rc = dalloc(g, (void**)&g->seg_off, n * sizeof(int)))) return rc;
-    if ((rc = dalloc(g, (void**)&g->seg_n, n * sizeof(int)))) return rc;
-    if ((rc = dalloc(g, (void**)&g->items, cap * sizeof(WorkItem)))) return rc;
-    if ((rc = dalloc(g, (void**)&g->nitems, 16))) return rc;
-    HIPCHK(hipMemcpy(g->chunks, chunks.data(), chunks.size() * sizeof(SortChunk), hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(g->seg_off, seg_off.data(), n * sizeof(int), hipMemcpyHostToDevice));
-    HIPCHK(hipMemset(g->nitems, 0, 16));
-    HIPCHK(hipMemset(g->counts, 0, (size_t)n * mk * sizeof(uint32_t)));
-    HIPCHK(hipMemset(g->steps, 0, n * sizeof(uint32_t)));
-    HIPCHK(hipMemset(g->errs, 0, n * sizeof(int)));
-    if (g->positivity) {
-        if ((rc = dalloc(g, (void**)&g->pos_count, n * sizeof(int)))) return rc;
-        for (Inst& I : g->in) {
-            if ((rc = dalloc(g, (void**)&I.pos_sw, I.P * sizeof(uint32_t)))) return rc;
-            if ((rc = dalloc(g, (void**)&I.pos_flag, 3 * grid_size(I.H, I.dim)))) return rc;  // flags, 2 scratch
-            HIPCHK(hipMemset(I.pos_sw, 0, I.P * sizeof(uint32_t)));
+    // first the tables and counters, which one copy fills
+    Arena ar;
+    ar.want(&g->steps, n * sizeof(uint32_t));
+    ar.want(&g->errs, n * sizeof(int));
+    ar.want(&g->nitems, 16);
+    ar.want(&g->counts, (size_t)n * mk * sizeof(uint32_t));
+    ar.want(&g->pdesc, 2 * n * sizeof(PartDesc<T>));
+    ar.want(&g->fdesc, n * sizeof(FieldDesc<T>));
+    ar.want(&g->seg_off, n * sizeof(int));
+    ar.want(&g->chunks, chunks.size() * sizeof(SortChunk));
+    const size_t table_bytes = ar.size;
+    ar.want(&g->cursor, (size_t)n * mk * sizeof(uint32_t));
+    ar.want(&g->seg, cap * sizeof(WorkItem));
+    ar.want(&g->seg_n, n * sizeof(int));
+    ar.want(&g->items, cap * sizeof(WorkItem));
+    for (Inst& I : g->in) {
+        const int64_t P = I.P;
+        const size_t ng = grid_size(I.H, I.dim), nspec = spec_size(I.H, I.dim);
+        for (int s = 0; s < 2; ++s) {
+            ar.want(&I.xs[s], P * sizeof(T));
+            ar.want(&I.ys[s], P * sizeof(T));
+            if (I.dim == 3) ar.want(&I.zs[s], P * sizeof(T));
+            ar.want(&I.ids[s], P * sizeof(uint32_t));
+        }
+        ar.want(&I.phi, ng * sizeof(T));
+        ar.want(&I.B1, nspec * 2 * sizeof(T));
+        ar.want(&I.alpha, nspec * 2 * sizeof(T));
+        ar.want(&I.gspec, I.dim * nspec * 2 * sizeof(T));
+        ar.want(&I.G, I.dim * ng * sizeof(T));
+        if (g->positivity) {
+            ar.want(&I.pos_sw, P * sizeof(uint32_t));
+            ar.want(&I.pos_flag, 3 * ng);  // flags, 2 scratch
         }
     }
+    if (g->positivity) ar.want(&g->pos_count, n * sizeof(int));
+    if ((rc = ar.commit(g))) return rc;
+    // the tables: zero counters, descriptors, segment offsets, sort chunks
+    std::vector<char> table(table_bytes, 0);
+    auto host = [&](const void* dev) { return table.data() + ((const char*)dev - (const char*)g->arena); };
+    PartDesc<T>* pd = (PartDesc<T>*)host(g->pdesc);
+    FieldDesc<T>* fd = (FieldDesc<T>*)host(g->fdesc);
+    for (int i = 0; i < n; ++i) {
+        pd[i] = make_pdesc<T>(g, i, 0);
+        pd[n + i] = make_pdesc<T>(g, i, 1);
+        fd[g->fslot[i]] = make_fdesc<T>(g, i);
+    }
+    std::memcpy(host(g->seg_off), seg_off.data(), n * sizeof(int));
+    std::memcpy(host(g->chunks), chunks.data(), chunks.size() * sizeof(SortChunk));
+    HIPCHK(hipMemcpy(g->arena, table.data(), table_bytes, hipMemcpyHostToDevice));
+    if (g->positivity)
+        for (const Inst& I : g->in) HIPCHK(hipMemsetAsync(I.pos_sw, 0, I.P * sizeof(uint32_t), g->stream));
     g->pgrid = std::max(1, std::min(g->items_cap, g->dim == 2 ? particle_resident_blocks2<T>(g->scheme, g->win_bytes)
                                                                 : particle_resident_blocks<T>(g->scheme, g->win_bytes,
                                                                                               g->sorted)));
-    return upload_descs<T>(g);
+    return SIPF_OK;
 }
 
 // Positions of instance i (AoS, host or device) -> SoA set 0, wrapped, ids 0..P-1.
@@ -977,6 +1091,15 @@ void free_group(Group* g) {
     g->gcache.clear();
     if (g->cap) (void)hipStreamDestroy(g->cap);
     for (void* p : g->allocs) (void)hipFree(p);
+    if (g->arena) {
+        // nothing of the group is pending when its block goes back
+        if (hipStreamSynchronize(g->stream) != hipSuccess) {
+            (void)hipGetLastError();
+            (void)hipDeviceSynchronize();
+        }
+        g_group_cache.put(g->arena, g->arena_bytes);
+        g->arena = nullptr;
+    }
 }
 
 // Shared set-up of contexts and batches: validation, host checks, tuning.
@@ -1232,63 +1355,7 @@ int destroy_any(Group* g) {
 // pathwise adjoint of a single-instance context
 // ---------------------------------------------------------------------------
 
-// Device buffer freed when it goes out of scope (adjoint temporaries).
-// Device work buffers of the adjoint are kept for later calls instead of
-// freed: an FP64 adjoint of 2e6 particles holds about 2 GB of tape, segment
-// and noise buffers, and hipMalloc + hipFree of those cost milliseconds per
-// call (hipFree also waits for the device).  Cached blocks are reused by any
-// later adjoint on the same device whose request fits (best fit, at most
-// twice the request) and returned by sipf_release_cached_memory.
-struct BufCache {
-    struct Blk {
-        int dev;
-        size_t n;
-        void* p;
-    };
-    std::mutex mu;
-    std::vector<Blk> free_blocks;
-    hipError_t get(size_t n, void** out) {
-        int dev = 0;
-        hipError_t e = hipGetDevice(&dev);
-        if (e != hipSuccess) return e;
-        {
-            std::lock_guard<std::mutex> lock(mu);
-            int best = -1;
-            for (int i = 0; i < (int)free_blocks.size(); ++i) {
-                const Blk& b = free_blocks[i];
-                if (b.dev == dev && b.n >= n && b.n <= 2 * n && (best < 0 || b.n < free_blocks[best].n)) best = i;
-            }
-            if (best >= 0) {
-                *out = free_blocks[best].p;
-                free_blocks.erase(free_blocks.begin() + best);
-                return hipSuccess;
-            }
-        }
-        return hipMalloc(out, n);
-    }
-    void put(void* p, size_t n) {
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess) {
-            (void)hipGetLastError();
-            (void)hipFree(p);
-            return;
-        }
-        std::lock_guard<std::mutex> lock(mu);
-        free_blocks.push_back({dev, n, p});
-    }
-    void release() {
-        std::lock_guard<std::mutex> lock(mu);
-        for (const Blk& b : free_blocks) {
-            int cur = 0;
-            if (hipGetDevice(&cur) == hipSuccess && cur != b.dev) (void)hipSetDevice(b.dev);
-            (void)hipFree(b.p);
-            if (cur != b.dev) (void)hipSetDevice(cur);
-        }
-        free_blocks.clear();
-    }
-};
-BufCache g_buf_cache;
-
+// Device buffer that goes back to the cache when it goes out of scope (adjoint temporaries).
 struct DevBuf {
     void* p = nullptr;
     size_t n = 0;
@@ -1297,7 +1364,7 @@ struct DevBuf {
     }
     hipError_t alloc(size_t bytes) {
         n = bytes ? bytes : 16;
-        return g_buf_cache.get(n, &p);
+        return g_buf_cache.get(n, &p, &n);
     }
 };
 
@@ -2105,6 +2172,7 @@ int sipf_dbg_cells(const sipf_params* prm, int64_t count, const void* X, int32_t
 
 int sipf_release_cached_memory(void) {
     g_buf_cache.release();
+    g_group_cache.release();
     return SIPF_OK;
 }
 
