@@ -39,29 +39,15 @@ constexpr int SORT_CHUNK = SORT_THREADS * SORT_PER_THREAD;
 constexpr int MAX_KEYS = 4096;     // (H / tile)^3 <= 16^3, (H / tile)^2 <= 64^2
 constexpr int MIN_WINDOW_ITEM = 64;  // smaller items deposit and gather straight from global memory
 
-// Push phase: re-read each particle (1) or keep the item's particles in
-// registers from the load phase (0); unroll factor of the push loop.
-#ifndef SIPF_RELOAD
-#define SIPF_RELOAD 1
-#endif
-#ifndef SIPF_PUSH_UNROLL
-#define SIPF_PUSH_UNROLL 8
-#endif
-// Minimum waves per SIMD the register allocation of the two-phase passes
-// (FP64 steps, and the deposit-only and push-only passes of both precisions)
-// must leave room for; 0 leaves it to the compiler.  A budget of six waves
-// spilled 50-105 VGPRs in FP64: on the adjoint workload (P = 2e6, H = 64, 100
-// steps) the compiler's choice took the FP64 forward from 27.1 to 22.8 ms and
-// forward + adjoint from 87.5 to 73.5 ms (a budget of four: 24.8 and 76.2 ms);
-// FP32 forward + adjoint 36.9 -> 36.5 ms.
+// Waves per SIMD the registers of the two-phase FP64 step and of the
+// deposit-only and push-only passes of both precisions leave room for: four,
+// i.e. two workgroups per CU.  An FP64 split step takes 161 registers if left
+// alone (one workgroup per CU), 128 with 10 spilled here: mixed workload in
+// FP64, P = 5e5, H = 64, 79.5 -> 71.8 us per step.
 #ifndef SIPF_PART_WAVES
-#define SIPF_PART_WAVES 0
+#define SIPF_PART_WAVES 4
 #endif
-#if SIPF_PART_WAVES > 0
 #define SIPF_PART_ATTR __attribute__((amdgpu_waves_per_eu(SIPF_PART_WAVES)))
-#else
-#define SIPF_PART_ATTR
-#endif
 
 int particle_threads() { return PT; }
 int particle_chunk() { return CH; }
@@ -287,13 +273,6 @@ __device__ __forceinline__ void deposit_one(Sink& sink, T x, T y, T z, T hl, con
     }
 }
 
-template <typename T> struct LdsSink {
-    typename Fixed<T>::I* win;
-    T scale;  // 2^S
-    __device__ __forceinline__ void operator()(int idx, T F) const {
-        atomicAdd(reinterpret_cast<typename Fixed<T>::U*>(win + idx), (typename Fixed<T>::U)Fixed<T>::quant(F * scale));
-    }
-};
 template <typename T> struct GlobalSink {
     T* phi;
     T m;
@@ -338,7 +317,8 @@ template <typename T> struct Win;
 #define SIPF_WIN_G 15
 #endif
 template <> struct Win<float> { static constexpr int D = SIPF_WIN_D, G = SIPF_WIN_G; };
-template <> struct Win<double> { static constexpr int D = 15, G = 11; };
+// FP64: two workgroups per CU by registers, so 55 KB of window costs nothing
+template <> struct Win<double> { static constexpr int D = 19, G = 13; };
 // a window plane must fit one workgroup (plane_map)
 static_assert(Win<float>::D * Win<float>::D <= PT && Win<double>::D * Win<double>::D <= PT, "window plane");
 static_assert(Win<float>::G * Win<float>::G <= PT && Win<double>::G * Win<double>::G <= PT, "window plane");
@@ -373,7 +353,7 @@ int particle_window_bytes(bool fp64) {
 
 // Thread -> (i0, j, k) for walking a window of ey x ez columns along i with
 // stride nrep = PT / (ey ez) (ey ez <= PT); threads beyond nrep ey ez get
-// i0 = INT_MAX and do nothing.
+// an i0 past any window and do nothing.
 __device__ __forceinline__ void plane_map(int ey, int ez, int& i0, int& j, int& k, int& nrep) {
     const int pl = ey * ez;
     nrep = PT / pl;
@@ -385,25 +365,27 @@ __device__ __forceinline__ void plane_map(int ey, int ez, int& i0, int& j, int& 
         divmod_small(t, pl, 1.0f / (float)pl, i0, r);
         divmod_small(r, ez, 1.0f / (float)ez, j, k);
     } else {
-        i0 = INT_MAX;
+        i0 = 1 << 20;
     }
 }
 
 // Deposit of one particle into a fixed-stride fixed-point window whose node
-// (i, j, k) is at (i D + j) D + k, origin (ox, oy, oz).  The scale 2^S is
-// folded into the x factors (every Gamma_4 weight has exactly one).
+// (i, j, k) is at (i D + j) D + k and whose first cell (one node in from the
+// edge) is (cx, cy, cz); false, depositing nothing, when the particle's cell is
+// not one of the window's (nx, ny, nz).  The scale 2^S is folded into the x
+// factors (every Gamma_4 weight has exactly one).
 template <typename T, bool P2>
-__device__ __forceinline__ void deposit_fast(typename Fixed<T>::I* win, T x, T y, T z, T hl, const Wrap<P2>& wr, int ox,
-                                             int oy, int oz, T scale) {
+__device__ __forceinline__ bool deposit_fast(typename Fixed<T>::I* win, T x, T y, T z, T hl, const Wrap<P2>& wr, int cx,
+                                             int cy, int cz, int nx, int ny, int nz, T scale) {
     constexpr int D = Win<T>::D;
     using U = typename Fixed<T>::U;
     const T sx = x * hl, sy = y * hl, sz = z * hl;
     const T fx = floor(sx), fy = floor(sy), fz = floor(sz);
-    const int gx = (int)fx, gy = (int)fy, gz = (int)fz;
+    const int ix = wr((int)fx - cx), iy = wr((int)fy - cy), iz = wr((int)fz - cz);
+    if (ix >= nx || iy >= ny || iz >= nz) return false;
     const Axis4<T> ax = axis4(sx - fx), ay = axis4(sy - fy), az = axis4(sz - fz);
     const T S = (T)1 + (ax.w0 * ax.w1 + ay.w0 * ay.w1 + az.w0 * az.w1) * (T)0.5;
-    const int base = (wr(gx - 1 - ox) * D + wr(gy - 1 - oy)) * D + wr(gz - 1 - oz);
-    U* w = reinterpret_cast<U*>(win) + base;
+    U* w = reinterpret_cast<U*>(win) + mad24(mad24(ix, D, iy), D, iz);
     const T X[4] = {ax.wm * scale, ax.w0 * scale, ax.w1 * scale, ax.wp * scale};
     const T Y[4] = {ay.wm, ay.w0, ay.w1, ay.wp};
     const T Z[4] = {az.wm, az.w0, az.w1, az.wp};
@@ -436,18 +418,30 @@ __device__ __forceinline__ void deposit_fast(typename Fixed<T>::I* win, T x, T y
             SIPF_ADD(i, j, 3, Z[3], xy);
         }
 #undef SIPF_ADD
+    return true;
+}
+
+// Window cells along one axis: n cells from relative cell o for an item whose
+// cells span [lo, hi] (mean: about `mean`), wanted with m cells of margin on
+// both sides, on a grid of H cells with at most `most` cells in the window.
+// Cells that find no room are the item's outermost ones.
+__device__ __forceinline__ void window_axis(int lo, int hi, int m, int mean, int most, int H, int& o, int& n) {
+    const int nb = hi - lo + 1;
+    n = min(min(nb + 2 * m, most), H);
+    o = lo - (n - nb) / 2;  // spare cells on both sides
+    if (nb > n) o = max(lo, min(hi - n + 1, mean - n / 2));
 }
 
 // Trilinear gather from a fixed-stride window (node (i, j, k) at (i G + j) G + k,
-// three planes of G^3); false if the cell is not covered by the loaded part
-// (ex, ey, ez) of the window.
+// three planes of G^3) whose first cell is (cx, cy, cz); false if the cell is
+// not one of the window's (nx, ny, nz).
 template <typename T, bool P2>
 __device__ __forceinline__ bool gather_fast(const T* Gw, int gx, int gy, int gz, T lx, T ly, T lz, const Wrap<P2>& wr,
-                                            int ox, int oy, int oz, int ex, int ey, int ez, T& vx, T& vy, T& vz) {
+                                            int cx, int cy, int cz, int nx, int ny, int nz, T& vx, T& vy, T& vz) {
     constexpr int G = Win<T>::G;
     constexpr int G3 = G * G * G;
-    const int ix = wr(gx - ox), iy = wr(gy - oy), iz = wr(gz - oz);
-    if (ix > ex - 2 || iy > ey - 2 || iz > ez - 2) return false;
+    const int ix = wr(gx - cx), iy = wr(gy - cy), iz = wr(gz - cz);
+    if (ix >= nx || iy >= ny || iz >= nz) return false;
     const T* p = Gw + mad24(mad24(ix, G, iy), G, iz);
     const T wx[2] = {(T)1 - lx, lx}, wy[2] = {(T)1 - ly, ly}, wz[2] = {(T)1 - lz, lz};
     T ax = 0, ay = 0, az = 0;
@@ -471,219 +465,225 @@ __device__ __forceinline__ bool gather_fast(const T* Gw, int gx, int gy, int gz,
     return true;
 }
 
-// One work item: particles [beg, beg + cnt) of one instance, held in registers.
+// Gradient window rows held in registers between the loads and the LDS
+// writes: each thread owns one (j, k) column of the window (plane_map) and
+// every nrep-th node of it along i.
+template <typename T> struct GradRows {
+    static constexpr int G = Win<T>::G;
+    // nrep is smallest, PT / G^2, for the full window
+    static constexpr int R = (G + PT / (G * G) - 1) / (PT / (G * G));
+    T v[3 * R];
+    template <bool P2>
+    __device__ __forceinline__ void load(const T* Gr, int H, const Wrap<P2>& wr, int ox, int oy, int oz, int ex, int ey,
+                                         int ez) {
+        int i0, wj, wk, nrep;
+        plane_map(ey, ez, i0, wj, wk, nrep);
+        const int H3 = H * H * H;
+        const int nyz = wr(oy + wj) * H + wr(oz + wk);
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            const int i = i0 + q * nrep;
+            if (i < ex) {
+                const int node = wr(ox + i) * H * H + nyz;
+                v[3 * q] = gp(Gr)[node];
+                v[3 * q + 1] = gp(Gr)[H3 + node];
+                v[3 * q + 2] = gp(Gr)[2 * H3 + node];
+            }
+        }
+    }
+    __device__ __forceinline__ void store(T* Gw, int ex, int ey, int ez) const {
+        constexpr int G3 = G * G * G;
+        int i0, wj, wk, nrep;
+        plane_map(ey, ez, i0, wj, wk, nrep);
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            const int i = i0 + q * nrep;
+            if (i < ex) {
+                const int o = (i * G + wj) * G + wk;
+                Gw[o] = v[3 * q];
+                Gw[G3 + o] = v[3 * q + 1];
+                Gw[2 * G3 + o] = v[3 * q + 2];
+            }
+        }
+    }
+};
+
+// One work item: particles [beg, beg + cnt) of one instance.
+//
+// The windows follow the bounding box of the item's cells.  A box wider than
+// a window (tiles of the window's size, a period's drift, a stray particle)
+// keeps the window on the cells around the item's mean, and the particles
+// outside it use the grids in HBM one by one: a few strays cost a few atomics
+// instead of sending the whole item there (one FP64 item of 3072 particles in
+// ten had a stray; a deposit of 2e6 blob particles that had drifted since
+// their sort took 950 us, now 76).  Items of a few particles skip the
+// windows.
+//
+// What bounds it: the LDS atomics and vector work of many items per workgroup
+// at large P, one item's chain of memory and LDS round trips at small P.
+// Hence: one barrier for the box; the gradient rows are loaded while the
+// deposit window is flushed; the next item's ticket is drawn before the
+// deposit, which waits for no memory; and the cold paths stand once in the
+// code, in loops that are not unrolled (eight unrolled pushes with three
+// gathers each made 100 KB of code, more than the instruction cache; now 26 KB,
+// at the same time per particle).  Before and after, us per launch: H = 256,
+// P = 1e6 617 -> 177; torus P = 1e7, H = 128 190 -> 187 (with tile counts 243
+// -> 213); FP64 blob P = 2e6, H = 64 166 -> 101 (324 -> 131), its push-only
+// pass 117 -> 83; mixed P = 1e6, H = 64, the whole step, 58.5 -> 54.9.
 template <typename T, bool DEP, bool PUSH, int SCHEME, bool P2>
-__device__ __forceinline__ void item_pass(const PartDesc<T>& a, int64_t beg, int cnt, unsigned char* lds,
-                                          int win_bytes, int* sh, const TileCount& tc) {
+__device__ __forceinline__ void item_pass(const PartDesc<T>& a, int64_t beg, int cnt, unsigned char* lds, int4* sh,
+                                          const TileCount& tc, const Ticket& ticket) {
     using I = typename Fixed<T>::I;
+    constexpr int D = Win<T>::D, G = Win<T>::G;
     const int tid = threadIdx.x;
     const int H = a.H, Hh = H / 2;
     const Wrap<P2> wr{H, H - 1};
     const T hl = a.hl;
-    T px[PPT], py[PPT], pz[PPT];
-#if !SIPF_RELOAD
-    uint32_t pid[PPT];
-#endif
     // uniform per-item bases and 32-bit offsets; lanes past the end load the
     // item's last particle (cnt >= 1), so all loads issue without branches
     const T* ix = a.x + beg;
     const T* iy = a.y + beg;
     const T* iz = a.z + beg;
     const uint32_t* iid = a.id + beg;
+    const T x0 = gp(ix)[0], y0 = gp(iy)[0], z0 = gp(iz)[0];
+    T px[PPT], py[PPT], pz[PPT];
 #pragma unroll
     for (int k = 0; k < PPT; ++k) {
-        const int j = tid + k * PT;
-        const uint32_t jj = (uint32_t)(j < cnt ? j : cnt - 1);
-        px[k] = gp(ix)[jj];
-        py[k] = gp(iy)[jj];
-        pz[k] = gp(iz)[jj];
-#if !SIPF_RELOAD
-        if (PUSH) pid[k] = gp(iid)[jj];
-#endif
+        if (k * PT < cnt) {
+            const uint32_t jj = (uint32_t)min(tid + k * PT, cnt - 1);
+            px[k] = gp(ix)[jj];
+            py[k] = gp(iy)[jj];
+            pz[k] = gp(iz)[jj];
+        }
     }
-    if (tc.counts != nullptr) {
-        tc_reference(tc, a, px[0], py[0], pz[0]);
-        __syncthreads();
+    tc_reference(tc, a, x0, y0, z0);
+    // bounding box of the item's cells, relative to the first particle's cell
+    const int rx = __builtin_amdgcn_readfirstlane(wr(ifloor(x0 * hl)));
+    const int ry = __builtin_amdgcn_readfirstlane(wr(ifloor(y0 * hl)));
+    const int rz = __builtin_amdgcn_readfirstlane(wr(ifloor(z0 * hl)));
+    auto rel = [&](T p, int r) { return wr(wr(ifloor(p * hl)) - r + Hh) - Hh; };
+    int bx = 0, by = 0, bz = 0;  // the first particle's cell is in the box
+#pragma unroll
+    for (int k = 0; k < PPT; ++k) {
+        if (k * PT < cnt) {
+            bx = pk_min(bx, pk_bounds(rel(px[k], rx)));
+            by = pk_min(by, pk_bounds(rel(py[k], ry)));
+            bz = pk_min(bz, pk_bounds(rel(pz[k], rz)));
+        }
     }
+    block_bounds3<PT / 64>(bx, by, bz, sh);
     const bool windows = cnt >= MIN_WINDOW_ITEM;
-    int rx = 0, ry = 0, rz = 0;
-    if (windows) {
-        // bounding box of the item's cells, relative to the first particle's cell
-        if (tid < 3) sh[tid] = INT_MAX;
-        else if (tid < 6) sh[tid] = INT_MIN;
-        __syncthreads();
-        rx = wr(ifloor(gp(a.x)[beg] * hl));
-        ry = wr(ifloor(gp(a.y)[beg] * hl));
-        rz = wr(ifloor(gp(a.z)[beg] * hl));
-        int mnx = INT_MAX, mny = INT_MAX, mnz = INT_MAX, mxx = INT_MIN, mxy = INT_MIN, mxz = INT_MIN;
+    // the item's mean cell, where its box outgrows a window
+    int mx = 0, my = 0, mz = 0;
+    constexpr int LEAST = D - 3 < G - 1 ? D - 3 : G - 1;
+    if (windows && max(max(pk_hi(bx) - pk_lo(bx), pk_hi(by) - pk_lo(by)), pk_hi(bz) - pk_lo(bz)) >= LEAST) {
+        int sx = 0, sy = 0, sz = 0;
 #pragma unroll
         for (int k = 0; k < PPT; ++k) {
-            if (tid + k * PT < cnt) {
-                const int cx = wr(wr(ifloor(px[k] * hl)) - rx + Hh) - Hh;
-                const int cy = wr(wr(ifloor(py[k] * hl)) - ry + Hh) - Hh;
-                const int cz = wr(wr(ifloor(pz[k] * hl)) - rz + Hh) - Hh;
-                mnx = min(mnx, cx); mxx = max(mxx, cx);
-                mny = min(mny, cy); mxy = max(mxy, cy);
-                mnz = min(mnz, cz); mxz = max(mxz, cz);
+            if (k * PT < cnt && tid + k * PT < cnt) {
+                sx += rel(px[k], rx);
+                sy += rel(py[k], ry);
+                sz += rel(pz[k], rz);
             }
         }
-        mnx = wave_min(mnx); mny = wave_min(mny); mnz = wave_min(mnz);
-        mxx = wave_max(mxx); mxy = wave_max(mxy); mxz = wave_max(mxz);
-        if ((tid & 63) == 0) {
-            atomicMin(&sh[0], mnx); atomicMin(&sh[1], mny); atomicMin(&sh[2], mnz);
-            atomicMax(&sh[3], mxx); atomicMax(&sh[4], mxy); atomicMax(&sh[5], mxz);
-        }
+        int* sum = reinterpret_cast<int*>(sh + PT / 64);
+        if (tid < 3) sum[tid] = 0;
         __syncthreads();
+        atomicAdd(sum, sx);
+        atomicAdd(sum + 1, sy);
+        atomicAdd(sum + 2, sz);
+        __syncthreads();
+        mx = sum[0] / cnt;
+        my = sum[1] / cnt;
+        mz = sum[2] / cnt;
     }
 
-    if (DEP && windows && H > Win<T>::D && sh[3] - sh[0] + 4 <= Win<T>::D && sh[4] - sh[1] + 4 <= Win<T>::D &&
-        sh[5] - sh[2] + 4 <= Win<T>::D) {
-        // fast path: fixed-stride window, nodes -1..+2 around the box
-        constexpr int D = Win<T>::D;
+    // gradient window: the box, the W^- margin and the trilinear reach
+    int gcx = 0, gcy = 0, gcz = 0, gnx = 0, gny = 0, gnz = 0;  // first cell, cells
+    if (PUSH && windows) {
+        window_axis(pk_lo(bx), pk_hi(bx), a.gmargin, mx, G - 1, H, gcx, gnx);
+        window_axis(pk_lo(by), pk_hi(by), a.gmargin, my, G - 1, H, gcy, gny);
+        window_axis(pk_lo(bz), pk_hi(bz), a.gmargin, mz, G - 1, H, gcz, gnz);
+        gcx = wr(gcx + rx + H);
+        gcy = wr(gcy + ry + H);
+        gcz = wr(gcz + rz + H);
+    }
+    GradRows<T> rows;
+
+    if (DEP) {
         I* win = reinterpret_cast<I*>(lds);
-        const int ox = wr(rx + sh[0] - 1), oy = wr(ry + sh[1] - 1), oz = wr(rz + sh[2] - 1);
-        const int ex = sh[3] - sh[0] + 4, ey = sh[4] - sh[1] + 4, ez = sh[5] - sh[2] + 4;
-        // each thread owns one (j, k) column of the window and walks i
-        int i0, wj, wk, nrep;
-        plane_map(ey, ez, i0, wj, wk, nrep);
-        for (int i = i0; i < ex; i += nrep) win[(i * D + wj) * D + wk] = 0;
-        const int need = (11 * cnt + 7) / 8;
-        const int S = min(Magic<T>::MAXS, Fixed<T>::BITS - (32 - __clz(need)));
-        const T scale = (T)ldexp(1.0, S);
+        int cx = 0, cy = 0, cz = 0, nx = 0, ny = 0, nz = 0;  // first cell, cells
+        T scale = (T)1, back = a.wmass;
+        if (windows) {
+            window_axis(pk_lo(bx), pk_hi(bx), 0, mx, D - 3, H, cx, nx);
+            window_axis(pk_lo(by), pk_hi(by), 0, my, D - 3, H, cy, ny);
+            window_axis(pk_lo(bz), pk_hi(bz), 0, mz, D - 3, H, cz, nz);
+            cx = wr(cx + rx + H);
+            cy = wr(cy + ry + H);
+            cz = wr(cz + rz + H);
+            // nodes -1..+2 around the window's cells
+            int i0, wj, wk, nrep;
+            plane_map(ny + 3, nz + 3, i0, wj, wk, nrep);
+            for (int i = i0; i < nx + 3; i += nrep) win[(i * D + wj) * D + wk] = 0;
+            const int need = (11 * cnt + 7) / 8;
+            const int S = min(Magic<T>::MAXS, Fixed<T>::BITS - (32 - __clz(need)));
+            scale = (T)ldexp(1.0, S);
+            back = a.wmass * (T)ldexp(1.0, -S);
+        }
         __syncthreads();
+        ticket.draw();
+        bool out = !windows;  // some particle of the thread is outside the window
+        if (windows) {
 #pragma unroll
-        for (int k = 0; k < PPT; ++k)
-            if (tid + k * PT < cnt) deposit_fast<T>(win, px[k], py[k], pz[k], hl, wr, ox, oy, oz, scale);
-        __syncthreads();
-        const T back = a.wmass * (T)ldexp(1.0, -S);
-        {
-            const int nyz = wr(oy + wj) * H + wr(oz + wk);
-            for (int i = i0; i < ex; i += nrep) {
+            for (int k = 0; k < PPT; ++k)
+                if (k * PT < cnt && tid + k * PT < cnt)
+                    out |= !deposit_fast<T>(win, px[k], py[k], pz[k], hl, wr, cx, cy, cz, nx, ny, nz, scale);
+        }
+        if (__any(out)) {
+            GlobalSink<T> sink{a.phi, a.wmass};
+#pragma unroll 1
+            for (int j = tid; j < cnt; j += PT) {
+                const T x = gp(ix)[j], y = gp(iy)[j], z = gp(iz)[j];
+                if (wr(ifloor(x * hl) - cx) >= nx || wr(ifloor(y * hl) - cy) >= ny || wr(ifloor(z * hl) - cz) >= nz)
+                    deposit_one(sink, x, y, z, hl, wr, 0, 0, 0, H, H);
+            }
+        }
+        if (PUSH && windows) rows.load(a.G, H, wr, gcx, gcy, gcz, gnx + 1, gny + 1, gnz + 1);
+        if (windows) {
+            __syncthreads();
+            int i0, wj, wk, nrep;
+            plane_map(ny + 3, nz + 3, i0, wj, wk, nrep);
+            const int ox = cx - 1;
+            const int nyz = wr(cy + wj - 1) * H + wr(cz + wk - 1);
+            for (int i = i0; i < nx + 3; i += nrep) {
                 const I v = win[(i * D + wj) * D + wk];
                 if (v != 0) gatomic_add(a.phi + wr(ox + i) * H * H + nyz, (T)v * back);
             }
+            if (PUSH) __syncthreads();  // the window memory is reused below
         }
-        __syncthreads();  // the window memory is reused below
-    } else if (DEP) {
-        int ox = 0, oy = 0, oz = 0, Wx = H, Wy = H, Wz = H;
-        bool use_win = false;
-        if (windows) {
-            // nodes -1..+2 around every cell of the box
-            axis_window(rx, sh[0] - 1, sh[3] + 2, wr, ox, Wx);
-            axis_window(ry, sh[1] - 1, sh[4] + 2, wr, oy, Wy);
-            axis_window(rz, sh[2] - 1, sh[5] + 2, wr, oz, Wz);
-            use_win = (int64_t)Wx * Wy * Wz * (int64_t)sizeof(I) <= win_bytes;
-        }
-        if (use_win) {
-            I* win = reinterpret_cast<I*>(lds);
-            const int nw = Wx * Wy * Wz;
-            for (int e = tid; e < nw; e += PT) win[e] = 0;
-            // 2^S with S = BITS - bitlength(ceil(11 cnt / 8)): |sum of F| <= 1.375 cnt per node
-            const int need = (11 * cnt + 7) / 8;
-            const int S = Fixed<T>::BITS - (32 - __clz(need));
-            const T scale = (T)ldexp(1.0, S);
-            __syncthreads();
-            LdsSink<T> sink{win, scale};
-#pragma unroll
-            for (int k = 0; k < PPT; ++k)
-                if (tid + k * PT < cnt) deposit_one(sink, px[k], py[k], pz[k], hl, wr, ox, oy, oz, Wy, Wz);
-            __syncthreads();
-            const T back = a.wmass * (T)ldexp(1.0, -S);
-            const int WyWz = Wy * Wz;
-            for (int e = tid; e < nw; e += PT) {
-                const I v = win[e];
-                if (v != 0) {
-                    const int ex = e / WyWz, r = e - ex * WyWz;
-                    const int ey = r / Wz, ez = r - ey * Wz;
-                    const size_t node = ((size_t)wr(ox + ex) * H + wr(oy + ey)) * H + wr(oz + ez);
-                    gatomic_add(a.phi + node, (T)v * back);
-                }
-            }
-            __syncthreads();  // the window memory is reused below
-        } else {
-            GlobalSink<T> sink{a.phi, a.wmass};
-#pragma unroll
-            for (int k = 0; k < PPT; ++k)
-                if (tid + k * PT < cnt) deposit_one(sink, px[k], py[k], pz[k], hl, wr, 0, 0, 0, H, H);
-        }
+    } else if (windows) {
+        rows.load(a.G, H, wr, gcx, gcy, gcz, gnx + 1, gny + 1, gnz + 1);
     }
+    if (!DEP) ticket.draw();
 
     if (PUSH) {
-        // gradient window: cells of the box (+ margin for the W^- displacement) and +1 for the trilinear reach
-        int ox = 0, oy = 0, oz = 0, Wx = H, Wy = H, Wz = H;
-        bool use_win = false, fast = false;
-        const T* Gl = reinterpret_cast<const T*>(lds);
-        size_t n3 = 0;
-        if (windows && H > Win<T>::G) {
-            constexpr int G = Win<T>::G;
-            constexpr int G3 = G * G * G;
-            for (int m = a.gmargin; m >= 0 && !fast; --m)
-                fast = sh[3] - sh[0] + 2 + 2 * m <= G && sh[4] - sh[1] + 2 + 2 * m <= G &&
-                       sh[5] - sh[2] + 2 + 2 * m <= G;
-            if (fast) {
-                int m = a.gmargin;
-                while (sh[3] - sh[0] + 2 + 2 * m > G || sh[4] - sh[1] + 2 + 2 * m > G || sh[5] - sh[2] + 2 + 2 * m > G) --m;
-                ox = wr(rx + sh[0] - m);
-                oy = wr(ry + sh[1] - m);
-                oz = wr(rz + sh[2] - m);
-                Wx = sh[3] - sh[0] + 2 + 2 * m;
-                Wy = sh[4] - sh[1] + 2 + 2 * m;
-                Wz = sh[5] - sh[2] + 2 + 2 * m;
-                T* Gw = reinterpret_cast<T*>(lds);
-                const int H3 = H * H * H;
-                int i0, wj, wk, nrep;
-                plane_map(Wy, Wz, i0, wj, wk, nrep);
-                const int nyz = wr(oy + wj) * H + wr(oz + wk);
-                for (int i = i0; i < Wx; i += nrep) {
-                    const int node = wr(ox + i) * H * H + nyz;
-                    const int o = (i * G + wj) * G + wk;
-                    Gw[o] = gp(a.G)[node];
-                    Gw[G3 + o] = gp(a.G)[H3 + node];
-                    Gw[2 * G3 + o] = gp(a.G)[2 * H3 + node];
-                }
-                __syncthreads();
-            }
-        }
-        if (windows && !fast) {
-            for (int m = a.gmargin; m >= 0 && !use_win; --m) {
-                axis_window(rx, sh[0] - m, sh[3] + 1 + m, wr, ox, Wx);
-                axis_window(ry, sh[1] - m, sh[4] + 1 + m, wr, oy, Wy);
-                axis_window(rz, sh[2] - m, sh[5] + 1 + m, wr, oz, Wz);
-                use_win = 3 * (int64_t)Wx * Wy * Wz * (int64_t)sizeof(T) <= win_bytes;
-            }
-            if (use_win) {
-                T* Gw = reinterpret_cast<T*>(lds);
-                const int nw = Wx * Wy * Wz;
-                n3 = (size_t)nw;
-                const size_t H3 = (size_t)H * H * H;
-                const int WyWz = Wy * Wz;
-                for (int e = tid; e < nw; e += PT) {
-                    const int ex = e / WyWz, r = e - ex * WyWz;
-                    const int ey = r / Wz, ez = r - ey * Wz;
-                    const size_t node = ((size_t)wr(ox + ex) * H + wr(oy + ey)) * H + wr(oz + ez);
-                    Gw[e] = gp(a.G)[node];
-                    Gw[nw + e] = gp(a.G)[H3 + node];
-                    Gw[2 * nw + e] = gp(a.G)[2 * H3 + node];
-                }
-                __syncthreads();
-            }
+        T* Gw = reinterpret_cast<T*>(lds);
+        if (windows) {
+            rows.store(Gw, gnx + 1, gny + 1, gnz + 1);
+            __syncthreads();
         }
         const uint32_t n = *a.step + 1u;
         const size_t H3 = (size_t)H * H * H;
-#pragma unroll SIPF_PUSH_UNROLL
+#pragma unroll 1
         for (int k = 0; k < PPT; ++k) {
+            if (k * PT >= cnt) break;
             const int j = tid + k * PT;
             const bool valid = j < cnt;
             T nx = (T)0, ny = (T)0, nz = (T)0;
             if (valid) {
-#if SIPF_RELOAD
             // re-read from L2 rather than holding eight particles in registers
             const T x = gp(ix)[j], y = gp(iy)[j], z = gp(iz)[j];
             const uint32_t idk = gp(iid)[j];
-#else
-            const T x = px[k], y = py[k], z = pz[k];
-            const uint32_t idk = pid[k];
-#endif
             T yx, yy, yz, w0, w1, w2;
             T zn[6];
             if (SCHEME == SIPF_STRANG) {
@@ -706,22 +706,13 @@ __device__ __forceinline__ void item_pass(const PartDesc<T>& a, int64_t beg, int
             const T sx = yx * hl, sy = yy * hl, sz = yz * hl;
             const T fx = floor(sx), fy = floor(sy), fz = floor(sz);
             const int gx = (int)fx, gy = (int)fy, gz = (int)fz;
-            int ix[2] = {wr(gx - ox), wr(gx + 1 - ox)};
-            int iy[2] = {wr(gy - oy), wr(gy + 1 - oy)};
-            int iz[2] = {wr(gz - oz), wr(gz + 1 - oz)};
             T vx, vy, vz;
-            const bool inside = !fast && use_win && (Wx == H || ix[0] <= Wx - 2) && (Wy == H || iy[0] <= Wy - 2) &&
-                                (Wz == H || iz[0] <= Wz - 2);
-            if (fast && gather_fast<T>(Gl, gx, gy, gz, sx - fx, sy - fy, sz - fz, wr, ox, oy, oz, Wx, Wy, Wz, vx, vy,
-                                       vz)) {
-                // gathered from the fixed-stride window
-            } else if (inside) {
-                trilinear3<T>(Gl, n3, Wy, Wz, ix, iy, iz, sx - fx, sy - fy, sz - fz, vx, vy, vz);
-            } else {
-                ix[0] = wr(gx); ix[1] = wr(gx + 1);
-                iy[0] = wr(gy); iy[1] = wr(gy + 1);
-                iz[0] = wr(gz); iz[1] = wr(gz + 1);
-                trilinear3<T>(gp(a.G), H3, H, H, ix, iy, iz, sx - fx, sy - fy, sz - fz, vx, vy, vz);
+            if (!gather_fast<T>(Gw, gx, gy, gz, sx - fx, sy - fy, sz - fz, wr, gcx, gcy, gcz, gnx, gny, gnz, vx, vy,
+                                vz)) {
+                const int jx[2] = {wr(gx), wr(gx + 1)};
+                const int jy[2] = {wr(gy), wr(gy + 1)};
+                const int jz[2] = {wr(gz), wr(gz + 1)};
+                trilinear3<T>(gp(a.G), H3, H, H, jx, jy, jz, sx - fx, sy - fy, sz - fz, vx, vy, vz);
             }
             nx = wrap_box(yx + a.chitau * vx + a.s * w0, a.L, a.halfL, a.invL);
             ny = wrap_box(yy + a.chitau * vy + a.s * w1, a.L, a.halfL, a.invL);
@@ -890,7 +881,7 @@ __device__ __forceinline__ bool sorted_candidate(const PartDesc<float>& a, const
 // does not fit the windows.
 template <int SCHEME, bool P2>
 __device__ __forceinline__ bool item_sorted(const PartDesc<float>& a, int64_t beg, int cnt, unsigned char* lds,
-                                            int* sh, const TileCount& tc) {
+                                            int* sh, const TileCount& tc, const Ticket& ticket) {
     float px[PPT], py[PPT], pz[PPT];
     uint32_t pid[PPT];
     load_cols(a, beg, cnt, px, py, pz, pid);
@@ -954,7 +945,7 @@ __device__ __forceinline__ bool item_sorted(const PartDesc<float>& a, int64_t be
         for (int w = tid; w < nwords; w += PT) cw[w] = 0u;
     }
     // gradient window: the box, the W^- margin m and the trilinear reach
-    const int gox = wr(rx + bx0 - m), goy = wr(ry + by0 - m), goz = wr(rz + bz0 - m);
+    const int gox = wr(rx + bx0 - m), goy = wr(ry + by0 - m), goz = wr(rz + bz0 - m);  // first cell and node
     const int gWx = nbx + 1 + 2 * m, gWy = nby + 1 + 2 * m, gWz = nbz + 1 + 2 * m;
     {
         const int H3 = H * H * H;
@@ -975,6 +966,7 @@ __device__ __forceinline__ bool item_sorted(const PartDesc<float>& a, int64_t be
     const uint32_t step_n = *a.step + 1u;
     const size_t H3 = (size_t)H * H * H;
     __syncthreads();
+    ticket.draw();
 
     float acc[32];
     int run = -1;  // window base node of the run in acc
@@ -1021,8 +1013,8 @@ __device__ __forceinline__ bool item_sorted(const PartDesc<float>& a, int64_t be
         const float fx = floorf(sx), fy = floorf(sy), fz = floorf(sz);
         const int gx = (int)fx, gy = (int)fy, gz = (int)fz;
         float vx, vy, vz;
-        if (!gather_fast<float>(Gw, gx, gy, gz, sx - fx, sy - fy, sz - fz, wr, gox, goy, goz, gWx, gWy, gWz, vx,
-                                vy, vz)) {
+        if (!gather_fast<float>(Gw, gx, gy, gz, sx - fx, sy - fy, sz - fz, wr, gox, goy, goz, gWx - 1, gWy - 1,
+                                gWz - 1, vx, vy, vz)) {
             const int jx[2] = {wr(gx), wr(gx + 1)};
             const int jy[2] = {wr(gy), wr(gy + 1)};
             const int jz[2] = {wr(gz), wr(gz + 1)};
@@ -1123,20 +1115,21 @@ __device__ __forceinline__ bool item_sorted(const PartDesc<float>& a, int64_t be
 template <typename T, bool DEP, bool PUSH, int SCHEME, bool P2, bool SORTED, bool COUNT>
 __device__ __forceinline__ void particles_body(const PartDesc<T>* __restrict__ pds,
                                                const WorkItem* __restrict__ items, int* hdr, int win_bytes,
-                                               unsigned char* smem_raw, int* sh, int* slot_p, uint32_t* kcounts,
+                                               unsigned char* smem_raw, int4* sh, int* slot_p, uint32_t* kcounts,
                                                uint32_t* tslot, int* tref) {
     const int n = hdr[0];
     if (!COUNT) kcounts = nullptr;
     if (kcounts != nullptr)
         for (int i = threadIdx.x; i < TC_SLOTS; i += PT)
             ((LDS_AS uint32_t*)tslot)[i] = 0u;  // first read after the item's barriers
-    for (int it = blockIdx.x; it < n; it = next_item(hdr, n, slot_p)) {
+    const Ticket ticket{hdr, n, slot_p};
+    for (int it = blockIdx.x; it < n; it = ticket.next()) {
         const WorkItem w = items[it];
         const PartDesc<T>& a = pds[w.inst];
         const TileCount tc{kcounts != nullptr ? kcounts + (size_t)w.inst * MAX_KEYS : nullptr, tslot, tref};
         bool done = false;
-        if constexpr (SORTED) done = sorted_candidate(a, w, win_bytes) && item_sorted<SCHEME, P2>(a, w.beg, w.cnt, smem_raw, sh, tc);
-        if (!done) item_pass<T, DEP, PUSH, SCHEME, P2>(a, w.beg, w.cnt, smem_raw, win_bytes, sh, tc);
+        if constexpr (SORTED) done = sorted_candidate(a, w, win_bytes) && item_sorted<SCHEME, P2>(a, w.beg, w.cnt, smem_raw, reinterpret_cast<int*>(sh), tc, ticket);
+        if (!done) item_pass<T, DEP, PUSH, SCHEME, P2>(a, w.beg, w.cnt, smem_raw, sh, tc, ticket);
         tc_flush(tc, a);
     }
 }
@@ -1148,7 +1141,7 @@ __global__ __launch_bounds__(PT) SIPF_PART_ATTR void k_particles(const PartDesc<
                                                   const WorkItem* __restrict__ items, int* hdr, int win_bytes,
                                                   uint32_t* kcounts) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    __shared__ int sh[8];
+    __shared__ int4 sh[PT / 64 + 1];
     __shared__ int slot;
     __shared__ uint32_t tslot[TC_SLOTS];
     __shared__ int tref[3];
@@ -1167,7 +1160,7 @@ __global__ __launch_bounds__(PT) __attribute__((amdgpu_waves_per_eu(SIPF_TWO_WAV
     const PartDesc<float>* __restrict__ pds, const WorkItem* __restrict__ items, int* hdr, int win_bytes,
     uint32_t* kcounts) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    __shared__ int sh[8];
+    __shared__ int4 sh[PT / 64 + 1];
     __shared__ int slot;
     __shared__ uint32_t tslot[TC_SLOTS];
     __shared__ int tref[3];
@@ -1186,7 +1179,7 @@ __global__ __launch_bounds__(PT) __attribute__((amdgpu_waves_per_eu(SIPF_FUSED_W
     const PartDesc<T>* __restrict__ pds, const WorkItem* __restrict__ items, int* hdr, int win_bytes,
     uint32_t* kcounts) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    __shared__ int sh[12];
+    __shared__ int4 sh[PT / 64 + 1];
     __shared__ int slot;
     __shared__ uint32_t tslot[TC_SLOTS];
     __shared__ int tref[3];

@@ -96,6 +96,46 @@ __device__ __forceinline__ int wave_max(int v) {
     return v;
 }
 
+// Bounds of up to three small signed values over a workgroup of NW waves, in
+// one barrier.  Each value c travels as the 16-bit pair (c, -c), whose
+// pairwise minimum gives the lower bound and minus the upper one, through the
+// lanes of a wave by DPP moves (a lane-shuffle reduction of six separate
+// values goes through LDS 36 times); one 16-byte LDS word per wave then
+// combines the waves.  sh: NW int4, read until the caller's next barrier.
+typedef short short2v __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ int pk_bounds(int c) { return (c & 0xFFFF) | (int)((unsigned)(-c) << 16); }
+__device__ __forceinline__ int pk_min(int a, int b) {
+    return __builtin_bit_cast(int, __builtin_elementwise_min(__builtin_bit_cast(short2v, a), __builtin_bit_cast(short2v, b)));
+}
+__device__ __forceinline__ int pk_lo(int v) { return (int)(short)(v & 0xFFFF); }
+__device__ __forceinline__ int pk_hi(int v) { return -(v >> 16); }
+// lane 63 receives the minimum over the wave
+__device__ __forceinline__ int wave_pk_min(int v) {
+    v = pk_min(v, __builtin_amdgcn_update_dpp(v, v, 0x111, 0xf, 0xf, false));  // row_shr 1, 2, 4, 8
+    v = pk_min(v, __builtin_amdgcn_update_dpp(v, v, 0x112, 0xf, 0xf, false));
+    v = pk_min(v, __builtin_amdgcn_update_dpp(v, v, 0x114, 0xf, 0xf, false));
+    v = pk_min(v, __builtin_amdgcn_update_dpp(v, v, 0x118, 0xf, 0xf, false));
+    v = pk_min(v, __builtin_amdgcn_update_dpp(v, v, 0x142, 0xa, 0xf, false));  // row_bcast 15, 31
+    v = pk_min(v, __builtin_amdgcn_update_dpp(v, v, 0x143, 0xc, 0xf, false));
+    return v;
+}
+template <int NW> __device__ __forceinline__ void block_bounds3(int& x, int& y, int& z, int4* sh) {
+    const int bx = wave_pk_min(x), by = wave_pk_min(y), bz = wave_pk_min(z);
+    if ((threadIdx.x & 63) == 63) sh[threadIdx.x >> 6] = make_int4(bx, by, bz, 0);
+    __syncthreads();
+    int4 r = sh[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) {
+        const int4 v = sh[w];
+        r.x = pk_min(r.x, v.x);
+        r.y = pk_min(r.y, v.y);
+        r.z = pk_min(r.z, v.z);
+    }
+    x = __builtin_amdgcn_readfirstlane(r.x);
+    y = __builtin_amdgcn_readfirstlane(r.y);
+    z = __builtin_amdgcn_readfirstlane(r.z);
+}
+
 // Window along one axis covering relative cells [lo, hi] of a chunk whose
 // reference cell is r: origin and width, or the whole axis when it would wrap.
 __device__ __forceinline__ void axis_window(int r, int lo, int hi, int H, int& o, int& W) {
@@ -109,16 +149,25 @@ __device__ __forceinline__ void axis_window(int r, int lo, int hi, int H, int& o
     }
 }
 
-// Periodic grid index onto [0, H): a mask when H is a power of two, else the
-// remainder, which holds for any int argument.
+// Periodic grid index onto [0, H), for any int argument: a mask when H is a
+// power of two, else one conditional step each way (arguments of the passes lie
+// within a period or two of the grid) and, past that, the quotient in FP64
+// (exact for every int up to the step that follows).  An integer remainder is
+// some 40 instructions and a particle takes about a dozen wraps.
 template <bool P2> struct Wrap {
     int H, m;  // m = H - 1
     __device__ __forceinline__ int operator()(int v) const {
         if constexpr (P2) {
             return v & m;
         } else {
-            const int r = v % H;
-            return r < 0 ? r + H : r;
+            int r = v < 0 ? v + H : v;
+            r = r >= H ? r - H : r;
+            if ((unsigned)r >= (unsigned)H) {
+                r = v - H * (int)floor((double)v * (1.0 / (double)H));
+                r = r < 0 ? r + H : r;
+                r = r >= H ? r - H : r;
+            }
+            return r;
         }
     }
 };
@@ -158,5 +207,26 @@ __device__ __forceinline__ int next_item(int* hdr, int n, int* slot) {
     __syncthreads();
     return *slot;
 }
+
+// The same queue with the draw ahead of time: draw() once per item, by the
+// whole workgroup and after a barrier, wherever its round trip is covered by
+// work that waits for no other memory; next() after the item.
+struct Ticket {
+    int* hdr;
+    int n;
+    int* slot;
+    __device__ __forceinline__ void draw() const {
+        if (n > (int)gridDim.x && threadIdx.x == 0) {
+            const int t = atomicAdd(hdr + 1, 1);
+            if (t == n - 1) atomicExch(hdr + 1, 0);
+            *slot = (int)gridDim.x + t;
+        }
+    }
+    __device__ __forceinline__ int next() const {
+        if (n <= (int)gridDim.x) return n;
+        __syncthreads();  // the item's use of LDS has ended, the slot is written
+        return *slot;
+    }
+};
 
 }  // namespace sipf

@@ -1,0 +1,94 @@
+"""Particle pass where its LDS windows do not hold the item: boxes wider than
+a window (tiles as large as the grid), particles that left their tile's
+neighbourhood, grids smaller than a window, items around the smallest size
+that takes windows, displacements of several periods.  One step (or a few)
+against the oracle at the tolerances of the step parity tests: FP32 grids 1e-5
+relative L2 and positions 1e-6 + 1e-5 of the drift, FP64 1e-12 and
+1e-12 + 1e-11 of the drift per step, times the largest coordinate met
+(positions are O(1) except where noise carries them across periods)."""
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import sipf as osipf  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():  # pragma: no cover - CPU containers
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+import paper_2512_03452_amd as pkg  # noqa: E402
+
+
+def rel_l2(a, b):
+    return float(np.linalg.norm((a - b).ravel()) / np.linalg.norm(b.ravel()))
+
+
+def _check(precision, kw, X0, tile, chunk, steps=1, resort=0, particle_pass="default"):
+    prm = osipf.Params(**kw)
+    rdt = np.float32 if precision == "fp32" else np.float64
+    X0 = osipf.wrap(X0, prm.L).astype(rdt)
+    sim = pkg.Sim(X0, precision=precision, tile=tile, chunk=chunk, resort_every=resort,
+                  particle_pass=particle_pass, **kw)
+    # one step makes a gradient (alpha starts at zero), then the steps under test
+    sim.step()
+    X, al = sim.positions().cpu().numpy().astype(np.float64), sim.field("alpha").cpu().numpy().astype(np.complex128)
+    full = osipf.full_spectrum(al)
+    rec = {}
+    for n in range(steps):
+        sim.step()
+    Xo, ao, n, drift = X, full, 2, 0.0
+    for n in range(2, 2 + steps):
+        Xo, ao = osipf.step(Xo, ao, n, prm, record=rec)
+        drift = max(drift, prm.chi * prm.dt * float(np.abs(rec["v"]).max()))
+    reach = max(1.0, 6.0 * np.sqrt(2 * prm.mu * prm.dt))
+    tol = (1e-5 if precision == "fp32" else 1e-12) * reach
+    ptol = ((1e-6 + 1e-5 * drift) if precision == "fp32" else (1e-12 + 1e-11 * drift)) * steps * reach
+    X1 = sim.positions().cpu().numpy().astype(np.float64)
+    A1 = sim.field("alpha").cpu().numpy().astype(np.complex128)
+    err = np.abs(osipf.min_image(X1 - Xo, prm.L)).max()
+    aerr = rel_l2(A1, osipf.half_spectrum(ao))
+    print(f" position error {err:.2e} (bound {ptol:.2e}), alpha {aerr:.2e} (bound {tol:.2e})", flush=True)
+    assert err < ptol
+    assert aerr < tol * steps
+    sim.close()
+
+
+@pytest.mark.parametrize("precision,H,tile,P,chunk,scheme", [
+    ("fp32", 64, 64, 6001, 0, "strang"), ("fp64", 64, 64, 3001, 512, "strang"), ("fp32", 46, 46, 4001, 0, "em"),
+    ("fp64", 22, 22, 3001, 256, "strang"), ("fp32", 16, 16, 5001, 0, "strang"), ("fp64", 16, 16, 2001, 0, "em"),
+    ("fp32", 8, 8, 777, 0, "strang"), ("fp32", 12, 12, 513, 256, "strang"), ("fp32", 32, 16, 2047, 1024, "strang"),
+    ("fp64", 32, 32, 2049, 0, "strang"), ("fp32", 128, 32, 8191, 0, "em")])
+@pytest.mark.parametrize("pp", ["two_phase", "sorted"])
+def test_boxes_wider_than_a_window(precision, H, tile, P, chunk, scheme, pp):
+    if precision == "fp64" and pp == "sorted":
+        pytest.skip("FP64 has one pass")
+    print("wide boxes", precision, H, tile, P, chunk, scheme, pp, flush=True)
+    kw = dict(L=2.0, chi=3.0, mu=0.5, eps=1.0, k=1.0, M0=50.0, dt=1e-3, H=H, seed=11, scheme=scheme)
+    X0 = np.random.default_rng(H + tile).uniform(-1.0, 1.0, (P, 3))
+    _check(precision, kw, X0, tile, chunk, particle_pass=pp)
+
+
+@pytest.mark.parametrize("precision,P", [("fp32", 63), ("fp32", 64), ("fp64", 63), ("fp64", 64), ("fp32", 513)])
+def test_small_items(precision, P):
+    print("small item", precision, P, flush=True)
+    kw = dict(L=2.0, chi=3.0, mu=0.5, eps=1.0, k=1.0, M0=50.0, dt=1e-3, H=64, seed=5)
+    _check(precision, kw, np.random.default_rng(P).normal(0.03, 0.02, (P, 3)), 8, 0)
+
+
+@pytest.mark.parametrize("H,P,resort", [(64, 20001, 40), (46, 9001, 40), (64, 3001, 3)])
+def test_strays_of_a_long_period(H, P, resort):
+    # noise of about a cell per step and no sort in between: boxes outgrow the windows step by step
+    print("strays", H, P, resort, flush=True)
+    kw = dict(L=2.0, chi=1.0, mu=0.5, eps=1.0, k=1.0, M0=50.0, dt=1e-3, H=H, seed=7)
+    _check("fp64", kw, np.random.default_rng(P).normal(0.0, 0.2, (P, 3)), 0, 0, steps=7, resort=resort)
+
+
+@pytest.mark.parametrize("H", [12, 16])
+@pytest.mark.parametrize("scheme", ["strang", "em"])
+def test_displacements_of_several_periods(H, scheme):
+    print("several periods", H, scheme, flush=True)
+    kw = dict(L=1.0, chi=1.0, mu=50.0, eps=1.0, k=1.0, M0=5.0, dt=1e-2, H=H, seed=9, scheme=scheme)
+    _check("fp64", kw, np.random.default_rng(H).uniform(-0.5, 0.5, (1500, 3)), 0, 0)
