@@ -180,8 +180,9 @@ typedef struct sipf_params {
     int32_t  resort_every; /* re-sort period in steps; 0 = default: 6 in 3-D, 4 in 2-D,
                               or fewer when sqrt(2 mu tau n) exceeds a quarter of a tile */
     int32_t  chunk;        /* max particles per work item of the particle pass (256..4096); 0 = default:
-                              4096 in 2-D and from 2^23 particles per 3-D group, else 3072;
-                              the adjoint's reverse pass then uses items of at most 2048 */
+                              4096 in 2-D and from 2^23 particles per 3-D group, else 3072.  3-D groups
+                              of P particles take items of about P/192 (at least 256) where that is
+                              smaller; the adjoint's reverse pass by default at most 2048 */
     uint64_t seed;         /* Philox key                                          */
     uint32_t instance;     /* fourth Philox counter word                          */
     uint32_t dim;          /* space dimension: 3 (0 means 3) or 2                 */

@@ -107,22 +107,35 @@ double filter_h0(const sipf_params* p) {
     return p->H0;
 }
 
-// Defaults where the parameters leave the tuning open (0): an 8-cell tile at
-// H = 128 and H/8 below (3-D), 16-cell tiles up to H = 1024 and H/64 above
-// (2-D), a re-sort every 4 steps (items: default_chunk).  A 3-D grid that is not
-// a power of two takes the same rule with ceil(H / 8) below H = 128 (the last
-// tile of an axis may be partial; the whole axis below H = 16).
-int default_tile(const sipf_params* p) {
+// FP32 3-D deposit + push pass: sorted items or the two-phase pass (the
+// choice is shared by a group's n instances).
+bool sorted_pass(const sipf_params* p, int n) {
+    if (p->precision != SIPF_FP32 || dim_of(p) != 3) return false;
+    if (p->particle_pass) return p->particle_pass == SIPF_PASS_SORTED;
+    return n > 1;
+}
+// The tile, where the parameters leave it open (0).  3-D: 8 cells from H = 128
+// on, else H/8 but at least 4 cells, and at least 8 in the sorted pass (the
+// whole axis on smaller grids): smaller tiles leave items of a few particles,
+// whose fixed cost outweighs their work.  Us per step at tiles of 2 / 4 / 8
+// cells: mixed P = 5e4, H = 16, 106 / 24 / 30; blob P = 2e5, H = 32, 48 / 31 /
+// 36; sorted pass, 30 balls of P = 2e4, H = 32, 146 / 91 / 69, 64-instance
+// ensemble (H = 32 and 64) 628 with 4 cells at H = 32 and 601 with 8.  A grid
+// that is not a power of two takes the same rule with ceil(H / 8) (the last
+// tile of an axis may be partial).  2-D: 16-cell tiles up to H = 1024 and H/64
+// above.
+int default_tile(const sipf_params* p, bool sorted) {
+    const int least = std::min(p->H, sorted ? 8 : 4);
     if (dim_of(p) == 3 && !is_pow2(p->H)) {
         if (p->tile) return p->tile;
-        return p->H < 16 ? p->H : (p->H >= 128 ? 8 : (p->H + 7) / 8);
+        return p->H < 16 ? p->H : (p->H >= 128 ? 8 : std::max(least, (p->H + 7) / 8));
     }
     if (dim_of(p) == 2) {
         int t = p->tile ? p->tile : std::min(p->H, std::max(16, p->H / 64));
         if (p->H / t > 64) t = p->H / 64;
         return t;
     }
-    int t = p->tile ? p->tile : (p->H >= 128 ? 8 : (p->H >= 16 ? p->H / 8 : p->H));
+    int t = p->tile ? p->tile : (p->H >= 128 ? 8 : (p->H >= 16 ? std::max(least, p->H / 8) : p->H));
     if (p->H / t > 16) t = p->H / 16;
     return t;
 }
@@ -132,38 +145,41 @@ int default_tile(const sipf_params* p) {
 // global atomics).  3-D, FP32 ms per step at periods 4 / 6 / 8: torus P = 1e7
 // 0.283 / 0.277 / 0.302 (the collapsing ring's drift outgrows the windows at
 // 8); blob P = 2e6 0.138 / 0.124 / 0.115; mixed P = 1e6 0.069 / 0.067 / 0.067.
-int default_resort(const sipf_params* p) {
+int default_resort(const sipf_params* p, bool sorted) {
     if (p->resort_every) return p->resort_every;
     const double cap = dim_of(p) == 2 ? 4.0 : 6.0;
-    const double q = default_tile(p) * p->L / p->H / 4.0;
+    const double q = default_tile(p, sorted) * p->L / p->H / 4.0;
     const double spread = 2.0 * p->mu * p->dt;
     if (spread <= 0) return (int)cap;
     const double n = std::floor(q * q / spread);
     return (int)std::max(1.0, std::min(cap, n));
 }
-// Work-item size: in 3-D, 3072, and 4096 from 2^23 particles per group; 2-D
-// keeps 4096.  The particle pass draws items from a ticket queue, so the size
-// trades per-item set-up (windows, barriers) against balance.  Measured
-// (FP32, ms per step, items of 4096 / 3072 / 2048): torus P = 1e7 0.289 /
-// 0.292 / 0.315; torus P = 6.5e6 0.224 / 0.215 / 0.231; blob P = 2e6 0.130 /
-// 0.119 / 0.132; mixed P = 1e6 0.087 / 0.070 / 0.072; 64-instance ensemble
-// 0.687 / 0.688 / 0.711.  2-D: P = 2^22 disk 0.265 / 0.272 (4096 / 2048).
-int default_chunk(const sipf_params* p, int64_t total_P) {
+// Largest work-item size where the parameters leave it open: in 3-D, 3072, and
+// 4096 from 2^23 particles per group; 2-D keeps 4096.  With several items per
+// CU the size trades per-item set-up (windows, barriers) against balance.
+// Measured (FP32, us per step, items of 4096 / 3072 / 2048): torus P = 1e7 289 /
+// 292 / 315; torus P = 6.5e6 224 / 215 / 231; 64-instance ensemble (P = 1.4e7)
+// 629 at 4096 / 741 at 2048.  2-D: P = 2^22 disk 265 / 272 (4096 / 2048).
+int max_chunk(const sipf_params* p, int64_t total_P) {
     if (p->chunk) return p->chunk;
-    if (dim_of(p) == 2) return 4096;
-    return total_P >= (int64_t(1) << 23) ? 4096 : 3072;
+    return dim_of(p) == 2 || total_P >= (int64_t(1) << 23) ? 4096 : 3072;
+}
+// Work-item size of a group: in 3-D, P / 192 in steps of 256 and at least 256,
+// where that is smaller.  An item is one workgroup's work from start to end, so
+// up to about one item per CU smaller items shorten the step.  Measured, us per
+// step: FP64 blob P = 1e4, H = 32, items of 256 / 1024 / 3072 particles: 28.3 /
+// 34.1 / 42.1; ball P = 97336, H = 46, 512 / 1024 / 3072: 38.0 / 40.1 / 49.2;
+// blob P = 2e5, H = 32, 512 / 1024 / 3072: 35.7 / 31.4 / 38.4; mixed P = 1e6,
+// H = 64, 1024 / 2048 / 3072: 71.1 / 56.1 / 56.9.
+int item_chunk(const sipf_params* p, int64_t total_P) {
+    const int most = max_chunk(p, total_P);
+    if (dim_of(p) == 2) return most;
+    return (int)std::min<int64_t>(most, std::max<int64_t>(256, (total_P / 192 + 128) / 256 * 256));
 }
 // Work-item size of the adjoint's per-segment sorts: its reverse item pass
 // holds one 512-thread workgroup per CU and prefers smaller items (adjoint
 // workload, P = 2e6: reverse sweep ~0.75 ms shorter at 2048 than at 3072).
-int default_adj_chunk(const sipf_params* p, int chunk) { return p->chunk ? p->chunk : std::min(chunk, 2048); }
-// FP32 3-D deposit + push pass: sorted items or the two-phase pass (the
-// choice is shared by a group's instances).
-bool sorted_pass(const sipf_params* p, int n) {
-    if (p->particle_pass) return p->particle_pass == SIPF_PASS_SORTED;
-    return n > 1;
-}
-
+int default_adj_chunk(const sipf_params* p, int chunk) { return p->chunk ? chunk : std::min(chunk, 2048); }
 }  // namespace
 
 // One instance: its parameters and device buffers.
@@ -1139,14 +1155,14 @@ int setup_group(Group* g, int32_t n, const sipf_params* prm, const int64_t* P, c
     g->tsize = ts;
     g->scheme = prm[0].scheme;
     g->stream = (hipStream_t)hip_stream;
-    g->resort = default_resort(&prm[0]);
-    for (int i = 1; i < n; ++i) g->resort = std::min(g->resort, default_resort(&prm[i]));
+    g->sorted = sorted_pass(&prm[0], n);
+    g->resort = default_resort(&prm[0], g->sorted);
+    for (int i = 1; i < n; ++i) g->resort = std::min(g->resort, default_resort(&prm[i], g->sorted));
     int64_t total_P = 0;
     for (int i = 0; i < n; ++i) total_P += P[i];
-    g->chunk = default_chunk(&prm[0], total_P);
+    g->chunk = item_chunk(&prm[0], total_P);
     g->adj_chunk = default_adj_chunk(&prm[0], g->chunk);
     g->win_bytes = particle_window_bytes(g->prec == SIPF_FP64);
-    g->sorted = sorted_pass(&prm[0], n);
     g->in.resize(n);
     for (int i = 0; i < n; ++i) {
         Inst& I = g->in[i];
@@ -1154,7 +1170,7 @@ int setup_group(Group* g, int32_t n, const sipf_params* prm, const int64_t* P, c
         I.P = P[i];
         I.H = prm[i].H;
         I.dim = dim_of(&prm[i]);
-        I.tile = default_tile(&prm[i]);
+        I.tile = default_tile(&prm[i], g->sorted);
         if (!is_pow2(I.H)) g->pow2 = false;
     }
     return SIPF_OK;
@@ -1769,7 +1785,7 @@ template <typename T> int deposit_noalloc_typed(const sipf_params* p, int64_t P,
     void* base = nullptr;
     size_t bytes = 0;
     HIPCHK(noalloc_scratch(&base, &bytes));
-    const int H = p->H, tile = default_tile(p), chunk = default_chunk(p, P);
+    const int H = p->H, tile = default_tile(p, false), chunk = item_chunk(p, P);
     const int mk = sort_max_keys(), sc = sort_chunk();
     const int nchunks = (int)((P + sc - 1) / sc);
     const int nt = (H + tile - 1) / tile;
@@ -2012,9 +2028,9 @@ int sipf_autotune(const sipf_params* prm, int64_t P, const void* X0, int x0_on_d
     if (nsteps < 1) return fail(SIPF_EINVAL, "nsteps must be >= 1");
     if (prm->method == SIPF_METHOD_DIRECT) return fail(SIPF_EINVAL, "the direct SIPF method has nothing to tune");
     sipf_params cur = *prm;
-    cur.tile = default_tile(prm);
-    cur.chunk = default_chunk(prm, P);
-    cur.resort_every = default_resort(prm);
+    cur.tile = default_tile(prm, sorted_pass(prm, 1));
+    cur.chunk = max_chunk(prm, P);
+    cur.resort_every = default_resort(prm, sorted_pass(prm, 1));
     double t_best = 0;
     if ((rc = time_config(&cur, P, X0, x0_on_device, nsteps, hip_stream, &t_best))) return rc;
     auto try_axis = [&](int32_t sipf_params::*field, const std::vector<int>& cands) -> int {

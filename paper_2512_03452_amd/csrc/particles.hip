@@ -37,7 +37,11 @@ constexpr int SORT_THREADS = SIPF_SORT_THREADS;  // threads per sort workgroup
 constexpr int SORT_PER_THREAD = SIPF_SORT_PER_THREAD;
 constexpr int SORT_CHUNK = SORT_THREADS * SORT_PER_THREAD;
 constexpr int MAX_KEYS = 4096;     // (H / tile)^3 <= 16^3, (H / tile)^2 <= 64^2
-constexpr int MIN_WINDOW_ITEM = 64;  // smaller items deposit and gather straight from global memory
+// Smaller items deposit and gather straight from global memory: 32 atomics and
+// 24 loads per particle against a window's clearing, flush and staging.  At 64
+// instead of 16, us per step: mixed P = 5e4, H = 64, 59.8 against 40.2 (FP64
+// 78.5 against 59.0), P = 2e4 42.9 against 36.1, P = 5e3 31.5 against 31.1.
+constexpr int MIN_WINDOW_ITEM = 16;
 
 // Waves per SIMD the registers of the two-phase FP64 step and of the
 // deposit-only and push-only passes of both precisions leave room for: four,
@@ -120,8 +124,10 @@ __device__ __forceinline__ uint32_t lane_runs(uint32_t key, int& head) {
 // for the 5^3 tiles within two of a reference tile (that of the item's first
 // particle before the push), one LDS add per run of equal tiles in
 // consecutive lanes, and adds the nonzero slots to the counts once per item;
-// a particle whose tile lies farther away (or every particle, on grids of
-// fewer than 5 tiles per axis) adds to the counts directly.
+// a particle whose tile lies farther away adds to the counts directly.  On
+// grids of at most 5 tiles per axis the slots are the tiles themselves (adding
+// to the counts directly there, a few device-wide counters for every wave,
+// took 1517 us instead of 54 for P = 1e6 on 2^3 tiles).
 // The slot and reference accesses go through LDS-address-space pointers: the
 // generic pointers of the struct let the compiler merge the LDS and the
 // global adds into one flat atomic, which the barrier that follows did not
@@ -149,9 +155,10 @@ __device__ __forceinline__ void tc_reference(const TileCount& tc, const PartDesc
 }
 
 // Slot of tile t relative to the reference (or -1 when it lies farther than
-// two tiles on an axis, or the grid has fewer than 5 tiles per axis).
+// two tiles on an axis); t itself on grids of at most 5 tiles per axis.
 __device__ __forceinline__ int tc_slot(const LDS_AS int* r, const uint32_t t[3], int nt) {
-    bool near = nt >= 5;
+    if (nt <= 5) return (int)((t[0] * 5u + t[1]) * 5u + t[2]);
+    bool near = true;
     int slot = 0;
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
@@ -218,7 +225,7 @@ template <typename T> __device__ __forceinline__ void tc_flush(const TileCount& 
             uint32_t t[3];
 #pragma unroll
             for (int d = 0; d < 3; ++d) {
-                int v = (r[d] + off[d]) % nt;
+                int v = (nt <= 5 ? off[d] + 2 : r[d] + off[d]) % nt;
                 t[d] = (uint32_t)(v < 0 ? v + nt : v);
             }
             __hip_atomic_fetch_add(gp(tc.counts) + key_of_tile<3>(t[0], t[1], t[2]), c, __ATOMIC_RELAXED,
@@ -373,8 +380,9 @@ __device__ __forceinline__ void plane_map(int ey, int ez, int& i0, int& j, int& 
 // (i, j, k) is at (i D + j) D + k and whose first cell (one node in from the
 // edge) is (cx, cy, cz); false, depositing nothing, when the particle's cell is
 // not one of the window's (nx, ny, nz).  The scale 2^S is folded into the x
-// factors (every Gamma_4 weight has exactly one).
-template <typename T, bool P2>
+// factors (every Gamma_4 weight has exactly one).  FINE: any S (weights rounded
+// and converted), else S <= Magic<T>::MAXS (one FMA and one subtraction each).
+template <bool FINE, typename T, bool P2>
 __device__ __forceinline__ bool deposit_fast(typename Fixed<T>::I* win, T x, T y, T z, T hl, const Wrap<P2>& wr, int cx,
                                              int cy, int cz, int nx, int ny, int nz, T scale) {
     constexpr int D = Win<T>::D;
@@ -389,7 +397,9 @@ __device__ __forceinline__ bool deposit_fast(typename Fixed<T>::I* win, T x, T y
     const T X[4] = {ax.wm * scale, ax.w0 * scale, ax.w1 * scale, ax.wp * scale};
     const T Y[4] = {ay.wm, ay.w0, ay.w1, ay.wp};
     const T Z[4] = {az.wm, az.w0, az.w1, az.wp};
-#define SIPF_ADD(i, j, k, a, b) atomicAdd(w + ((i) * D + (j)) * D + (k), (U)Magic<T>::take(fma(a, b, Magic<T>::M)))
+#define SIPF_ADD(i, j, k, a, b)             \
+    atomicAdd(w + ((i) * D + (j)) * D + (k), \
+              FINE ? (U)Fixed<T>::quant((a) * (b)) : (U)Magic<T>::take(fma(a, b, Magic<T>::M)))
 #pragma unroll
     for (int j = 1; j <= 2; ++j)
 #pragma unroll
@@ -573,6 +583,7 @@ __device__ __forceinline__ void item_pass(const PartDesc<T>& a, int64_t beg, int
     }
     block_bounds3<PT / 64>(bx, by, bz, sh);
     const bool windows = cnt >= MIN_WINDOW_ITEM;
+    const bool fine = cnt <= PT;  // one particle per thread: weights at the full scale of the item
     // the item's mean cell, where its box outgrows a window
     int mx = 0, my = 0, mz = 0;
     constexpr int LEAST = D - 3 < G - 1 ? D - 3 : G - 1;
@@ -625,19 +636,24 @@ __device__ __forceinline__ void item_pass(const PartDesc<T>& a, int64_t beg, int
             int i0, wj, wk, nrep;
             plane_map(ny + 3, nz + 3, i0, wj, wk, nrep);
             for (int i = i0; i < nx + 3; i += nrep) win[(i * D + wj) * D + wk] = 0;
+            // 2^S with S = BITS - bitlength(ceil(11 cnt / 8)): |sum of F| <= 1.375 cnt per node
             const int need = (11 * cnt + 7) / 8;
-            const int S = min(Magic<T>::MAXS, Fixed<T>::BITS - (32 - __clz(need)));
+            int S = Fixed<T>::BITS - (32 - __clz(need));
+            if (!fine) S = min(Magic<T>::MAXS, S);
             scale = (T)ldexp(1.0, S);
             back = a.wmass * (T)ldexp(1.0, -S);
         }
         __syncthreads();
         ticket.draw();
         bool out = !windows;  // some particle of the thread is outside the window
-        if (windows) {
+        if (windows && fine) {
+            if (tid < cnt)
+                out = !deposit_fast<true>(win, px[0], py[0], pz[0], hl, wr, cx, cy, cz, nx, ny, nz, scale);
+        } else if (windows) {
 #pragma unroll
             for (int k = 0; k < PPT; ++k)
                 if (k * PT < cnt && tid + k * PT < cnt)
-                    out |= !deposit_fast<T>(win, px[k], py[k], pz[k], hl, wr, cx, cy, cz, nx, ny, nz, scale);
+                    out |= !deposit_fast<false>(win, px[k], py[k], pz[k], hl, wr, cx, cy, cz, nx, ny, nz, scale);
         }
         if (__any(out)) {
             GlobalSink<T> sink{a.phi, a.wmass};

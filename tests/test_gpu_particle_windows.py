@@ -71,7 +71,8 @@ def test_boxes_wider_than_a_window(precision, H, tile, P, chunk, scheme, pp):
     _check(precision, kw, X0, tile, chunk, particle_pass=pp)
 
 
-@pytest.mark.parametrize("precision,P", [("fp32", 63), ("fp32", 64), ("fp64", 63), ("fp64", 64), ("fp32", 513)])
+@pytest.mark.parametrize("precision,P", [("fp32", 15), ("fp32", 16), ("fp32", 64), ("fp64", 15), ("fp64", 16),
+                                         ("fp64", 63), ("fp32", 512), ("fp32", 513)])
 def test_small_items(precision, P):
     print("small item", precision, P, flush=True)
     kw = dict(L=2.0, chi=3.0, mu=0.5, eps=1.0, k=1.0, M0=50.0, dt=1e-3, H=64, seed=5)
@@ -84,6 +85,14 @@ def test_strays_of_a_long_period(H, P, resort):
     print("strays", H, P, resort, flush=True)
     kw = dict(L=2.0, chi=1.0, mu=0.5, eps=1.0, k=1.0, M0=50.0, dt=1e-3, H=H, seed=7)
     _check("fp64", kw, np.random.default_rng(P).normal(0.0, 0.2, (P, 3)), 0, 0, steps=7, resort=resort)
+
+
+@pytest.mark.parametrize("H,tile", [(32, 32), (32, 16), (32, 8), (46, 11), (46, 8), (8, 2), (12, 4)])
+def test_tile_counts_on_few_tiles(H, tile):
+    # the pass before a sort counts tiles in slots: the tiles themselves up to 5 per axis, else around the item's
+    print("few tiles", H, tile, flush=True)
+    kw = dict(L=2.0, chi=1.0, mu=0.5, eps=1.0, k=1.0, M0=50.0, dt=1e-3, H=H, seed=3)
+    _check("fp64", kw, np.random.default_rng(tile).uniform(-1.0, 1.0, (5001, 3)), tile, 0, steps=6, resort=2)
 
 
 @pytest.mark.parametrize("H", [12, 16])
