@@ -973,9 +973,10 @@ template <typename T> int alloc_group(Group* g) {
             ar.want(&I.ids[s], P * sizeof(uint32_t));
         }
         ar.want(&I.phi, ng * sizeof(T));
-        ar.want(&I.B1, nspec * 2 * sizeof(T));
+        const size_t nwork = I.dim == 2 ? blocked_spec2(I.H) : nspec;  // spectra between the passes
+        ar.want(&I.B1, nwork * 2 * sizeof(T));
         ar.want(&I.alpha, nspec * 2 * sizeof(T));
-        ar.want(&I.gspec, I.dim * nspec * 2 * sizeof(T));
+        ar.want(&I.gspec, I.dim * nwork * 2 * sizeof(T));
         ar.want(&I.G, I.dim * ng * sizeof(T));
         if (g->positivity) {
             ar.want(&I.pos_sw, P * sizeof(uint32_t));
@@ -1279,7 +1280,7 @@ template <typename T> int diagnostics_typed(Group* g, sipf_diag* out) {
         d.dim = I.dim;
         d.pm = I.H > 256 ? I.H / 16 : I.H;
         d.pt = I.H > 256 ? 16 : 1;
-        d.n2 = fft_perm(d.pm, 1);
+        d.n2 = I.H > 256 ? 1 : fft_perm(d.pm, 1);
         d.n1 = d.pm / d.n2;
         d.nb = diag_blocks(I.P, (int64_t)grid_size(I.H, I.dim));
         nbmax = std::max(nbmax, d.nb);

@@ -38,7 +38,7 @@ int fft_perm(int N, int k) {
 #undef SIPF_SPLIT_CASE
         case 512: case 1024: case 2048: case 4096: {
             const int M = N / 16;
-            return (k % 16) * M + fft_perm(M, k / 16);
+            return (k % 16) * M + k / 16;
         }
         default: return -1;
     }
@@ -54,7 +54,7 @@ int fft_perm(int N, int k) {
 // 1.4 -> 0.05 ms at H = 128 and 14 -> 0.05 ms at H = 2048 in 2-D.
 // ---------------------------------------------------------------------------
 struct PermMap {
-    int pm, pt, n1, n2;  // length pm pt: pt blocks of pm, each in two-stage order pm = n1 n2
+    int pm, pt, n1, n2;  // length pm pt: pt blocks of pm, each in two-stage order pm = n1 n2 (natural: n2 = 1)
     __device__ __forceinline__ int pos(int k) const {
         const int r = k / pt;
         return (k % pt) * pm + (r % n1) * n2 + r / n1;
@@ -95,7 +95,7 @@ hipError_t launch_natural(int dim, int H, const cplx_t<T>* per, cplx_t<T>* nat, 
     PermMap m;
     m.pm = H > 256 ? H / 16 : H;
     m.pt = H > 256 ? 16 : 1;
-    m.n2 = fft_perm(m.pm, 1);
+    m.n2 = H > 256 ? 1 : fft_perm(m.pm, 1);
     m.n1 = m.pm / m.n2;
     const int HH = H / 2 + 1;
     if (dim == 2)

@@ -38,7 +38,8 @@ inline void launch_kernel(F kernel, dim3 grid, dim3 block, uint32_t shm, hipStre
 // FFT (see fft.hip); grids are H^3 row-major; G holds the three gradient
 // components one after another (d-major).  2-D (field2d.hip): spectra are
 // (H/2+1) x H, ky-major (ky = 0..H/2), kx in the digit-permuted order; grids
-// H^2 row-major; G holds two components.
+// H^2 row-major; G holds two components; B1 and gspec are ky-major in blocks of
+// a few frequencies (field2d.hip).
 template <typename T> struct FieldDesc {
     T* phi;                 // deposit accumulator (mass units); zeroed by the forward pass
     cplx_t<T>* B1;          // yz-plane pass output (x not yet transformed)
@@ -168,6 +169,7 @@ hipError_t launch_fwd_rows2(int H, const FieldDesc<T>* fd, int count, bool consu
 template <typename T> hipError_t launch_xrows2(int H, const FieldDesc<T>* fd, int count, int mode, hipStream_t s);
 template <typename T> hipError_t launch_inv_rows2(int H, const FieldDesc<T>* fd, int count, int ncomp, hipStream_t s);
 bool fft2d_size_supported(int H);
+size_t blocked_spec2(int H);  // values to allocate for one 2-D spectrum of B1 or gspec
 // digit permutation of the LDS FFT of length N: storage position of frequency k
 int fft_perm(int N, int k);
 // half spectrum in the FFT's storage order -> natural order (3-D or 2-D), out of place

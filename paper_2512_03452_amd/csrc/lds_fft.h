@@ -10,10 +10,10 @@
 // factors (12, 22, 46, 90 and their halves) serve grids that are not powers
 // of two.
 //
-// Lengths 512 .. 4096 (N = 16 M, M <= 256) add a first stage: 16-point DFTs
-// across the 16 blocks of M elements with twiddles w_N^(m k1), then the
-// M-point two-stage transform of every block; frequency k1 + 16 k' sits at
-// position k1 M + pos_M(k').  The inverse runs the stages in reverse order.
+// Lengths 512 .. 4096 (N = 16 M, M <= 256; Fft16) add a first stage: 16-point
+// DFTs across the 16 blocks of M elements with twiddles w_N^(m k1), then the
+// M-point two-stage transform of every block; frequency k1 + 16 k' is stored
+// at position k1 M + k'.  The inverse runs the stages in reverse order.
 #pragma once
 
 #include "common.h"
@@ -337,58 +337,88 @@ __device__ __forceinline__ void fft_2s(cplx_t<T>* buf, int ntr, int inner, int b
     }
 }
 
-// first stage of N = 16 M: 16-point DFTs across the blocks (forward: then the
-// twiddles; inverse: the conjugate twiddles first)
-template <typename T, int M, int DIR>
-__device__ __forceinline__ void fft_stage16(cplx_t<T>* buf, int count, int bs, int es, const cplx_t<T>* tw,
-                                            int tws) {
+// ---------------------------------------------------------------------------
+// Transforms of length N = 16 M, M = N1 N2, whose first and last stages are in
+// the caller's registers, so that they read and write HBM directly.  Forward:
+// first (elements m + M i of one transform in r), middle, load_group (group
+// (k1, j1): frequencies k = k1 + 16 (j1 + N1 i) in r[i]); inverse: store_group,
+// middle, last.  A barrier goes between any two of them, except load_group
+// before store_group of the same group by the same thread.  In between, element
+// q of block k1 of transform b is at
+//   b LEN + k1 MP + q + q / N2,
+// i.e. one value of padding after every N2 and a block pitch of 8 or 24 mod 32
+// values, so that the lanes of a wave spread over the LDS banks in every stage
+// (unpadded blocks, lanes a block apart, met 16 to a bank: the x rows of
+// H = 2048 took 57 us).  tw[j tws] = exp(-2 pi i j / N).
+// ---------------------------------------------------------------------------
+template <typename T, int N> struct Fft16 {
     using V = cplx_t<T>;
-    const int tid = threadIdx.x, nt = blockDim.x;
-    for (int u = tid; u < count * M; u += nt) {
-        const int b = u % count, m = u / count;
-        V* p = buf + b * bs + m * es;
-        V r[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) r[i] = p[i * M * es];
-        if constexpr (DIR > 0) {
-#pragma unroll
-            for (int k1 = 1; k1 < 16; ++k1) r[k1] = cmul(r[k1], cconj(tw[m * k1 * tws]));
-        }
-        Dft<T, 16, DIR>::run(r);
-        if constexpr (DIR < 0) {
-#pragma unroll
-            for (int k1 = 1; k1 < 16; ++k1) r[k1] = cmul(r[k1], tw[m * k1 * tws]);
-        }
-#pragma unroll
-        for (int i = 0; i < 16; ++i) p[i * M * es] = r[i];
-    }
-}
+    static constexpr int M = N / 16, N1 = Split<M>::N1, N2 = Split<M>::N2;
+    static constexpr int BARE = M + M / N2;
+    static constexpr int MP = BARE + (24 - BARE % 16) % 16;
+    static_assert(MP % 32 == 8 || MP % 32 == 24, "block pitch");
+    static constexpr int LEN = 16 * MP + 16;  // LDS values per transform (the next one starts half the banks away)
+    static constexpr int G3 = 16 * N1;   // groups of N2 frequencies per transform
+    __device__ __forceinline__ static int at(int k1, int q) { return k1 * MP + q + q / N2; }
 
-// count transforms of length N (4 .. 4096) at buf + b * bs, element stride es
-template <typename T, int N, int DIR>
-__device__ __forceinline__ void lds_fft_g(cplx_t<T>* buf, int count, int bs, int es, const cplx_t<T>* tw, int tws) {
-    if constexpr (N <= 256) {
-        fft_2s<T, Split<N>::N1, Split<N>::N2, DIR>(buf, count, 1, bs, 0, es, tw, tws);
-    } else {
-        constexpr int M = N / 16;
-        if constexpr (DIR < 0) {
-            fft_stage16<T, M, -1>(buf, count, bs, es, tw, tws);
-            __syncthreads();
-            fft_2s<T, Split<M>::N1, Split<M>::N2, -1>(buf, count * 16, 16, bs, M * es, es, tw, tws * 16);
-        } else {
-            fft_2s<T, Split<M>::N1, Split<M>::N2, +1>(buf, count * 16, 16, bs, M * es, es, tw, tws * 16);
-            __syncthreads();
-            fft_stage16<T, M, +1>(buf, count, bs, es, tw, tws);
+    // first stage of one transform (at p) from its elements r[i] = x[m + M i]
+    __device__ __forceinline__ static void first(V* p, const V* tw, int tws, int m, V* r) {
+        Dft<T, 16, -1>::run(r);
+#pragma unroll
+        for (int k1 = 1; k1 < 16; ++k1) r[k1] = cmul(r[k1], tw[m * k1 * tws]);
+#pragma unroll
+        for (int k1 = 0; k1 < 16; ++k1) p[at(k1, m)] = r[k1];
+    }
+    template <int COUNT, int DIR>
+    __device__ __forceinline__ static void middle(V* buf, const V* tw, int tws) {
+        for (int u = threadIdx.x; u < COUNT * 16 * N2; u += blockDim.x) {
+            const int n2 = u % N2, k1 = (u / N2) % 16, b = u / (16 * N2);
+            V* p = buf + b * LEN + k1 * MP + n2;
+            V r[N1];
+#pragma unroll
+            for (int i = 0; i < N1; ++i) r[i] = p[i * (N2 + 1)];
+            Dft<T, N1, DIR>::run(r);
+            if constexpr (DIR < 0) {
+#pragma unroll
+                for (int j = 1; j < N1; ++j) r[j] = cmul(r[j], tw[n2 * j * 16 * tws]);
+            }
+#pragma unroll
+            for (int i = 0; i < N1; ++i) p[i * (N2 + 1)] = r[i];
         }
     }
-}
+    // group g of transform b = g / G3: its block k1 and j1
+    __device__ __forceinline__ static int k1_of(int g) { return (g / N1) % 16; }
+    __device__ __forceinline__ static int j1_of(int g) { return g % N1; }
+    __device__ __forceinline__ static void load_group(const V* buf, int g, V* r) {
+        const V* p = buf + (g / G3) * LEN + k1_of(g) * MP + j1_of(g) * (N2 + 1);
+#pragma unroll
+        for (int i = 0; i < N2; ++i) r[i] = p[i];
+        Dft<T, N2, -1>::run(r);
+    }
+    __device__ __forceinline__ static void store_group(V* buf, int g, V* r, const V* tw, int tws) {
+        V* p = buf + (g / G3) * LEN + k1_of(g) * MP + j1_of(g) * (N2 + 1);
+        Dft<T, N2, +1>::run(r);
+#pragma unroll
+        for (int i = 1; i < N2; ++i) r[i] = cmul(r[i], cconj(tw[i * j1_of(g) * 16 * tws]));
+#pragma unroll
+        for (int i = 0; i < N2; ++i) p[i] = r[i];
+    }
+    // elements r[i] = x[m + M i] of one transform (at p)
+    __device__ __forceinline__ static void last(const V* p, const V* tw, int tws, int m, V* r) {
+#pragma unroll
+        for (int k1 = 0; k1 < 16; ++k1) r[k1] = p[at(k1, m)];
+#pragma unroll
+        for (int k1 = 1; k1 < 16; ++k1) r[k1] = cmul(r[k1], cconj(tw[m * k1 * tws]));
+        Dft<T, 16, +1>::run(r);
+    }
+};
 
+// storage order of the frequencies along a transformed axis (2-D)
 template <int N> __device__ __forceinline__ int perm_pos_g(int k) {
     if constexpr (N <= 256) {
         return perm_pos<N>(k);
     } else {
-        constexpr int M = N / 16;
-        return (k % 16) * M + perm_pos<M>(k / 16);
+        return (k % 16) * (N / 16) + k / 16;
     }
 }
 template <int N> __device__ __forceinline__ int perm_freq_g(int pos) {
@@ -396,7 +426,7 @@ template <int N> __device__ __forceinline__ int perm_freq_g(int pos) {
         return perm_freq<N>(pos);
     } else {
         constexpr int M = N / 16;
-        return pos / M + 16 * perm_freq<M>(pos % M);
+        return pos / M + 16 * (pos % M);
     }
 }
 

@@ -14,6 +14,25 @@ namespace sipf {
 template <typename T> __device__ __forceinline__ GLOBAL T* gp(T* p) { return (GLOBAL T*)p; }
 template <typename T> __device__ __forceinline__ const GLOBAL T* gp(const T* p) { return (const GLOBAL T*)p; }
 
+// Complex values through global-address-space pointers (a pointer read from a
+// descriptor in memory is generic to the compiler, its accesses flat).
+template <typename V> struct PairOf;
+template <> struct PairOf<float2> { typedef float type __attribute__((ext_vector_type(2))); };
+template <> struct PairOf<double2> { typedef double type __attribute__((ext_vector_type(2))); };
+template <typename V> __device__ __forceinline__ V ldg(const V* p) {
+    const typename PairOf<V>::type v = *(const GLOBAL typename PairOf<V>::type*)p;
+    V r;
+    r.x = v.x;
+    r.y = v.y;
+    return r;
+}
+template <typename V> __device__ __forceinline__ void stg(V* p, const V& v) {
+    typename PairOf<V>::type r;
+    r.x = v.x;
+    r.y = v.y;
+    *(GLOBAL typename PairOf<V>::type*)p = r;
+}
+
 __device__ __forceinline__ void gatomic_add(float* p, float v) { __builtin_amdgcn_global_atomic_fadd_f32(gp(p), v); }
 __device__ __forceinline__ void gatomic_add(double* p, double v) { __builtin_amdgcn_global_atomic_fadd_f64(gp(p), v); }
 
