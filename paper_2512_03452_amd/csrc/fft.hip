@@ -6,8 +6,8 @@
 // Transform convention (Sec. 3.1): beta_q = L^-3 sum_j phi_j e^{-2 pi i q.j/H},
 // grad c(x_j) = sum_q i xi_q Phi_q alpha_q e^{+2 pi i q.j/H}.
 //
-// Three passes over HBM per step, each staged through LDS (five at H = 256,
-// where a plane pass splits into a row pass and a column pass, see below):
+// Three passes over HBM per step (five at H = 256, where a plane pass splits
+// into a row pass and a column pass, see below):
 //   fwd_planes  one workgroup per x-plane: each real row along z is read as
 //               H/2 complex values, transformed, and split into its half
 //               spectrum (kz = 0..H/2); then the plane is transformed along y.
@@ -19,11 +19,23 @@
 //   inv_planes  one workgroup per (component, x-plane): inverse along y, then
 //               the half-length complex-to-real inverse along z.
 //
+// What bounds them: latency on a single grid (a launch of 3 to 7 us is a chain
+// of a memory round trip, LDS exchanges and barriers), memory in batches and at
+// H = 256.  So the first and last register DFT of every pass read and write
+// HBM themselves, the mode update works on the registers between the forward
+// and the inverse x transform, and LDS only carries the exchange between two
+// stages (one write and one read each).  Measured against passes that staged
+// every value through LDS, us per launch, forward / x pencils / inverse: H = 256
+// 81 / 146 / 187 -> 79 / 93 / 196; 30 grids of H = 64 24 / 41 / 52 -> 26 / 42 /
+// 37; H = 128 11.9 / 17.5 / 18.2 -> 11.4 / 16.0 / 19.7; H = 64 5.0 / 6.0 / 7.1 ->
+// 5.3 / 6.6 / 6.9; H = 8 4.4 / 3.7 / 3.3 -> 3.5 / 2.8 / 2.6.
+//
 // The LDS FFT (lds_fft.h) leaves the forward transform in a digit-permuted
 // order and takes that order back in the inverse; the x and y frequency axes
 // of the stored spectra use it.
 #include "internal.h"
 #include "lds_fft.h"
+#include "pass_common.h"
 
 namespace sipf {
 
@@ -118,133 +130,259 @@ bool fft_size_supported(int H, bool fp64) {
     }
 }
 
-// threads of the plane passes: the forward pass has only H workgroups and the
-// inverse 3H, so a plane gets 1024 threads (measured at H = 128: 16.9 -> 13.3
-// us forward, 19.6 -> 17.6 us inverse, against 512)
-#ifndef SIPF_FWD_THREADS
-#define SIPF_FWD_THREADS 1024
-#endif
-#ifndef SIPF_INV_THREADS
-#define SIPF_INV_THREADS 1024
-#endif
-constexpr int FWD_THREADS = SIPF_FWD_THREADS;
-constexpr int PLANE_THREADS = SIPF_INV_THREADS;
-// x-pencil and y-column passes: 512 threads (measured x-pencil pass: H = 128
-// 25.1 / 22.1 / 31.4 us and H = 64 11.0 / 8.7 / 7.9 us at 256 / 512 / 1024)
-constexpr int PENCIL_THREADS = 512;
-#ifndef SIPF_KB
-#define SIPF_KB 16
-#endif
-constexpr int KB = SIPF_KB;  // kz columns per x-pencil workgroup
+constexpr int KB = 16;  // columns per workgroup of the x-pencil and y-column passes: one 128-byte line of FP32 per row
 
-// v, or zero when ok is false (per component: a select of whole vector
-// values goes through scratch memory).
-template <typename V> __device__ __forceinline__ V keep_if(bool ok, const V& v) {
-    V r;
-    r.x = ok ? v.x : 0;
-    r.y = ok ? v.y : 0;
-    return r;
-}
+// ---------------------------------------------------------------------------
+// Rows along z and planes in LDS.  A row of H reals is read as M = H/2 complex
+// values z[m] = x[2m] + i x[2m+1] and transformed with an M-point FFT; then
+//   E_k = (Z_k + conj Z_{M-k}) / 2,  O_k = (Z_k - conj Z_{M-k}) / (2i),
+//   X_k = E_k + exp(-2 pi i k / H) O_k,   k = 0 .. M.
+// The inverse takes Z_k = (X_k + conj X_{M-k}) + i exp(+2 pi i k / H)
+// (X_k - conj X_{M-k}) to z[m] (unnormalised, as the gradient synthesis needs).
+//
+// M = M1 M2: value q of row r is at r PITCH + q + q / M2 (no padding when M2 =
+// 1), with PITCH 8 mod 16 values (odd when M2 = 1), so that the lanes of a wave,
+// M2 of one row beside each other, spread over the banks in both stages.
+// Frequency k is at q = perm_pos<M>(k); the column k = M of a plane lies behind
+// the rows.  tw[j] = exp(-2 pi i j / H).
+// ---------------------------------------------------------------------------
+template <typename T, int H, int NR> struct ZRows {
+    using V = cplx_t<T>;
+    static constexpr int M = H / 2, M1 = Split<M>::N1, M2 = Split<M>::N2;
+    static constexpr int BARE = M2 > 1 ? M + M / M2 : M;
+    static constexpr int PITCH = M2 > 1 ? BARE + (24 - BARE % 16) % 16 : BARE | 1;
+    static constexpr int EXTRA = NR * PITCH;        // column k = M of the rows
+    static constexpr int SIZE = NR * PITCH + NR;
+    __device__ __forceinline__ static int at(int r, int q) { return r * PITCH + (M2 > 1 ? q + q / M2 : q); }
+    // value k = 0 .. M of row r
+    __device__ __forceinline__ static int freq_at(int r, int k) { return k == M ? EXTRA + r : at(r, perm_pos<M>(k)); }
 
-// Copy of N elements by the NT threads of a workgroup, element u read by
-// ld(u) and written by st(u, v): every read of a thread is issued before its
-// first write, so a copy between HBM and LDS costs one memory round trip (a
-// loop of read-then-write pairs waits for each read in turn).  Threads past
-// the end re-read element N - 1 and write nothing.
-template <int NT, int N, typename V, typename Ld, typename St>
-__device__ __forceinline__ void stage(const Ld& ld, const St& st) {
-    constexpr int R = (N + NT - 1) / NT;
-    V v[R];
+    // rows from HBM (row r at src + r M), transformed: Z_k at freq_at(r, k).
+    // clear: zero the rows.  Ends with a barrier; tw is made on the way.
+    // One register DFT per row longer than 8 values (M = 11, 23): rows pass through LDS on the
+    // way, since a thread's own row is not contiguous across the wave (H = 46: 7.4 -> 6.8
+    // us forward).
+    static constexpr bool STAGED = M2 == 1 && M1 > 8;
+    template <int NT> __device__ __forceinline__ static void forward(V* buf, V* tw, V* src, bool clear) {
+        if constexpr (STAGED) {
+            constexpr int NL = NR * M, QL = (NL + NT - 1) / NT;
+            V v[QL];
 #pragma unroll
-    for (int q = 0; q < R; ++q) {
-        const int u = (int)threadIdx.x + q * NT;
-        v[q] = ld(N % NT == 0 ? u : min(u, N - 1));
-    }
+            for (int q = 0; q < QL; ++q) v[q] = ldg(src + min((int)threadIdx.x + q * NT, NL - 1));
+            make_twiddles<T, H>(tw);
 #pragma unroll
-    for (int q = 0; q < R; ++q) {
-        const int u = (int)threadIdx.x + q * NT;
-        if (N % NT == 0 || u < N) st(u, v[q]);
+            for (int q = 0; q < QL; ++q) {
+                const int u = (int)threadIdx.x + q * NT;
+                if (u < NL) {
+                    buf[at(u / M, u % M)] = v[q];
+                    if (clear) stg(src + u, cmake<V, T>(0, 0));
+                }
+            }
+            __syncthreads();
+            for (int u = threadIdx.x; u < NR; u += NT) {
+                V r[M1];
+#pragma unroll
+                for (int i = 0; i < M1; ++i) r[i] = buf[at(u, i)];
+                Dft<T, M1, -1>::run(r);
+#pragma unroll
+                for (int i = 0; i < M1; ++i) buf[at(u, i)] = r[i];
+            }
+            __syncthreads();
+            return;
+        }
+        constexpr int NI = NR * M2;  // first-stage items (r, m2)
+        constexpr int Q = (NI + NT - 1) / NT;
+        V r[Q][M1];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int u = min((int)threadIdx.x + q * NT, NI - 1);
+#pragma unroll
+            for (int i = 0; i < M1; ++i) r[q][i] = ldg(src + (u / M2) * M + u % M2 + i * M2);
+        }
+        make_twiddles<T, H>(tw);
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int u = (int)threadIdx.x + q * NT;
+            if (u < NI) {
+                const int row = u / M2, m2 = u % M2;
+                if (clear) {
+#pragma unroll
+                    for (int i = 0; i < M1; ++i) stg(src + row * M + m2 + i * M2, cmake<V, T>(0, 0));
+                }
+                Dft<T, M1, -1>::run(r[q]);
+                if constexpr (M2 > 1) {
+#pragma unroll
+                    for (int j = 1; j < M1; ++j) r[q][j] = cmul(r[q][j], tw[2 * m2 * j]);
+                }
+#pragma unroll
+                for (int j = 0; j < M1; ++j) buf[at(row, j * M2 + m2)] = r[q][j];
+            }
+        }
+        __syncthreads();
+        if constexpr (M2 > 1) {
+            for (int u = threadIdx.x; u < NR * M1; u += NT) {
+                V* p = buf + at(u / M1, u % M1 * M2);
+                V v[M2];
+#pragma unroll
+                for (int i = 0; i < M2; ++i) v[i] = p[i];
+                Dft<T, M2, -1>::run(v);
+#pragma unroll
+                for (int i = 0; i < M2; ++i) p[i] = v[i];
+            }
+            __syncthreads();
+        }
     }
+    // X_k of row r from the transformed row
+    __device__ __forceinline__ static V split(const V* buf, const V* tw, int r, int k) {
+        const V za = buf[freq_at(r, k % M)], zc = cconj(buf[freq_at(r, (M - k) % M)]);
+        const V e = cscale(cadd(za, zc), (T)0.5);
+        const V d = csub(za, zc);
+        return cadd(e, cmul(tw[k], cmake<V, T>(d.y * (T)0.5, -d.x * (T)0.5)));
+    }
+    // rows X_k (at freq_at) to real rows in HBM (row r at dst + r M); starts after a barrier
+    template <int NT> __device__ __forceinline__ static void inverse(V* buf, const V* tw, V* dst) {
+        constexpr int NG = NR * M1, Q = (NG + NT - 1) / NT;  // groups (r, j1): k = j1 + M1 i
+        V z[Q][M2];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int u = min((int)threadIdx.x + q * NT, NG - 1);
+            const int row = u / M1, j1 = u % M1;
+#pragma unroll
+            for (int i = 0; i < M2; ++i) {
+                const int k = j1 + M1 * i;
+                const V xa = buf[freq_at(row, k)], xc = cconj(buf[freq_at(row, M - k)]);
+                const V s = cadd(xa, xc), t = cmul(cconj(tw[k]), csub(xa, xc));
+                z[q][i] = cmake<V, T>(s.x - t.y, s.y + t.x);
+            }
+            if constexpr (M2 > 1) {
+                Dft<T, M2, +1>::run(z[q]);
+#pragma unroll
+                for (int i = 1; i < M2; ++i) z[q][i] = cmul(z[q][i], cconj(tw[2 * i * j1]));
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int u = (int)threadIdx.x + q * NT;
+            if (u < NG) {
+                V* p = buf + at(u / M1, u % M1 * M2);
+#pragma unroll
+                for (int i = 0; i < M2; ++i) p[i] = z[q][i];
+            }
+        }
+        __syncthreads();
+        for (int u = threadIdx.x; u < NR * M2; u += NT) {
+            const int row = u / M2, m2 = u % M2;
+            V r[M1];
+#pragma unroll
+            for (int j = 0; j < M1; ++j) r[j] = buf[at(row, j * M2 + m2)];
+            Dft<T, M1, +1>::run(r);
+#pragma unroll
+            for (int i = 0; i < M1; ++i) {
+                if constexpr (STAGED) buf[at(row, i)] = r[i];
+                else stg(dst + row * M + m2 + i * M2, r[i]);
+            }
+        }
+        if constexpr (STAGED) {
+            __syncthreads();
+            for (int u = threadIdx.x; u < NR * M; u += NT) stg(dst + u, buf[at(u / M, u % M)]);
+        }
+    }
+};
+
+// threads of a plane workgroup
+template <int H> constexpr int plane_threads() {
+    return H <= 16 ? 64 : (H <= 32 ? 256 : (H < 128 ? 512 : 1024));
 }
 
 // ---------------------------------------------------------------------------
 // Pass 1: x-plane -> half spectrum along z, transformed along y.
-//
-// Real rows along z by the half-length method: row x (length H = 2M) is read
-// as z[m] = x[2m] + i x[2m+1], transformed with an M-point FFT, and
-//   E_k = (Z_k + conj Z_{M-k}) / 2,  O_k = (Z_k - conj Z_{M-k}) / (2i),
-//   X_k = E_k + exp(-2 pi i k / H) O_k,   k = 0 .. M,
-// so one plane buffer of H x (M+1) values holds both stages.  The pairs
-// (k, M-k) are read into registers before they are written back, since the
-// FFT leaves Z in permuted order.
 // ---------------------------------------------------------------------------
 template <typename T, int H>
-__global__ __launch_bounds__(FWD_THREADS) void k_fwd_planes(const FieldDesc<T>* __restrict__ fds, int consume) {
+__global__ __launch_bounds__(plane_threads<H>()) void k_fwd_planes(const FieldDesc<T>* __restrict__ fds, int consume) {
     using V = cplx_t<T>;
-    constexpr int M = H / 2;
-    constexpr int HH = M + 1;
-    constexpr int OP = HH;  // row pitch (complex)
-    constexpr int NP = M / 2 + 1;  // pairs (k, M - k) per row, k = 0 .. M/2
-    constexpr int PPT = (H * NP + FWD_THREADS - 1) / FWD_THREADS;
-    __shared__ V buf[H * OP];
+    using Z = ZRows<T, H, H>;
+    constexpr int HH = H / 2 + 1, NT = plane_threads<H>();
+    constexpr int N1 = Split<H>::N1, N2 = Split<H>::N2;
+    __shared__ V buf[Z::SIZE];
     __shared__ V tw[H];
-    __shared__ V twm[M];
     const FieldDesc<T>& fd = fds[blockIdx.y];
     const int ix = blockIdx.x % H;
     const int comp = blockIdx.x / H;  // component of a multi-grid input (phi + comp H^3)
-    const int tid = threadIdx.x, nt = blockDim.x;
-    make_twiddles<T, H>(tw);
-    make_twiddles<T, M>(twm);
-    T* plane = fd.phi + ((size_t)comp * H + ix) * H * H;
-    V* pv = reinterpret_cast<V*>(plane);  // (x[2m], x[2m+1]) of row r at r M + m
-    stage<FWD_THREADS, H * M, V>([&](int u) { return pv[u]; },
-                                 [&](int u, const V& v) { buf[(u / M) * OP + u % M] = v; });
-    __syncthreads();
-    if (consume) {
-        // the deposit grid is consumed: clear it for the next step's particle pass
-        for (int u = tid; u < H * M; u += nt) pv[u] = cmake<V, T>(0, 0);
-        if (ix == 0 && comp == 0 && tid == 0 && fd.step != nullptr) *fd.step += 1u;
-    }
-    lds_fft<T, M, -1>(buf, H, OP, 1, twm);
-    __syncthreads();
-    V za[PPT], zb[PPT];
-#pragma unroll
-    for (int q = 0; q < PPT; ++q) {
-        const int u = tid + q * FWD_THREADS;
-        if (u < H * NP) {
-            const int row = u / NP, k = u % NP;
-            za[q] = buf[row * OP + perm_pos<M>(k % M)];
-            zb[q] = buf[row * OP + perm_pos<M>((M - k) % M)];
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < PPT; ++q) {
-        const int u = tid + q * FWD_THREADS;
-        if (u < H * NP) {
-            const int row = u / NP, k = u % NP;
-            const V zc = cconj(zb[q]);
-            const V e = cscale(cadd(za[q], zc), (T)0.5);
-            const V dd = csub(za[q], zc);
-            const V o = cmake<V, T>(dd.y * (T)0.5, -dd.x * (T)0.5);  // (Z_k - conj Z_{M-k}) / (2i)
-            buf[row * OP + k] = cadd(e, cmul(tw[k], o));
-            if (k != M - k) buf[row * OP + (M - k)] = cadd(cconj(e), cmul(tw[M - k], cconj(o)));
-        }
-    }
-    __syncthreads();
-    lds_fft<T, H, -1>(buf, HH, 1, OP, tw);
-    __syncthreads();
+    const int tid = threadIdx.x;
+    if (consume && ix == 0 && comp == 0 && tid == 0 && fd.step != nullptr) *fd.step += 1u;
+    // the deposit grid is consumed: cleared for the next step's particle pass
+    Z::template forward<NT>(buf, tw, reinterpret_cast<V*>(fd.phi + ((size_t)comp * H + ix) * H * H), consume != 0);
     V* out = fd.B1 + ((size_t)comp * H + ix) * H * HH;
-    stage<FWD_THREADS, H * HH, V>([&](int u) { return buf[u]; }, [&](int u, const V& v) { out[u] = v; });
+    // along y, first stage: items (n2, kz) take rows n2 + i N2 of column kz
+    constexpr int NI = HH * N2, Q = (NI + NT - 1) / NT;
+    constexpr bool WIDE = N1 > 16;  // few items of many rows (H = 46): X_k from Z_k first, by all threads
+    if constexpr (WIDE) {
+        constexpr int QX = (H * HH + NT - 1) / NT;
+        V x[QX];
+#pragma unroll
+        for (int q = 0; q < QX; ++q) {
+            const int u = min(tid + q * NT, H * HH - 1);
+            x[q] = Z::split(buf, tw, u / HH, u % HH);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < QX; ++q) {
+            const int u = tid + q * NT;
+            if (u < H * HH) buf[Z::freq_at(u / HH, u % HH)] = x[q];
+        }
+        __syncthreads();
+    }
+    V r[Q][N1];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int u = min(tid + q * NT, NI - 1);
+        const int kz = u % HH, n2 = u / HH;
+#pragma unroll
+        for (int i = 0; i < N1; ++i)
+            r[q][i] = WIDE ? buf[Z::freq_at(n2 + i * N2, kz)] : Z::split(buf, tw, n2 + i * N2, kz);
+        Dft<T, N1, -1>::run(r[q]);
+        if constexpr (N2 > 1) {
+#pragma unroll
+            for (int k = 1; k < N1; ++k) r[q][k] = cmul(r[q][k], tw[n2 * k]);
+        }
+    }
+    if constexpr (N2 > 1) {
+        __syncthreads();  // the rows are read, the columns overwrite them
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int u = tid + q * NT;
+            if (u < NI) {
+#pragma unroll
+                for (int k = 0; k < N1; ++k) buf[Z::freq_at(k * N2 + u / HH, u % HH)] = r[q][k];
+            }
+        }
+        __syncthreads();
+        for (int u = tid; u < HH * N1; u += NT) {
+            const int kz = u % HH, k1 = u / HH;
+            V v[N2];
+#pragma unroll
+            for (int i = 0; i < N2; ++i) v[i] = buf[Z::freq_at(k1 * N2 + i, kz)];
+            Dft<T, N2, -1>::run(v);
+#pragma unroll
+            for (int i = 0; i < N2; ++i) stg(out + (k1 * N2 + i) * HH + kz, v[i]);
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int u = tid + q * NT;
+            if (u < NI) {
+#pragma unroll
+                for (int k = 0; k < N1; ++k) stg(out + k * HH + u, r[q][k]);
+            }
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
 // Pass 2: x-pencils, mode update, filtered gradient spectra, inverse along x.
 // ---------------------------------------------------------------------------
-template <typename T, int H, int MODE>
-__device__ __forceinline__ void adjoint_pencils(const FieldDesc<T>& fd, int c0, int ncol, T qy, int ky, int kz,
-                                                cplx_t<T>* lds, const cplx_t<T>* tw);
-
 // MODE_STEP: forward x of B1, mode update of alpha, three gradient spectra
 //            i xi_d Phi alpha, inverse x into gspec.
 // MODE_GRAD: the three gradient spectra of alpha (no update).
@@ -264,259 +402,222 @@ enum { MODE_STEP = 0, MODE_GRAD = 1, MODE_ADJ_SRC = 2, MODE_ADJ_ACC = 3, MODE_RH
 // (ky, kz) (column c = ky_position (H/2 + 1) + kz), all H x rows of each: a
 // row of the block is KB contiguous values starting at a multiple of KB, one
 // aligned 128-byte line in FP32 (blocks of KB kz values of one ky straddled
-// two lines, since H/2 + 1 is odd).  Every entry a thread touches lies in the
-// same column (the thread count is a multiple of KB), so ky and kz are the
-// thread's own.
+// two lines, since H/2 + 1 is odd).  Grids whose x transform is one register
+// DFT take 64 columns, a pencil per thread, and no LDS.
 //
-// At H = 128 (FP32) the registers are budgeted for three workgroups per CU
-// (six waves per SIMD), so that all 520 blocks are resident at once; smaller
-// grids have fewer blocks than CUs and leave the count to the compiler.
-template <typename T, int H, int MODE>
-__global__ __launch_bounds__(PENCIL_THREADS) __attribute__((amdgpu_waves_per_eu(H >= 128 ? 6 : 1))) void k_xpencils(
-    const FieldDesc<T>* __restrict__ fds) {
-    constexpr bool UPDATE = MODE == MODE_STEP;
-    using V = cplx_t<T>;
-    constexpr int HH = H / 2 + 1;
-    constexpr int NC = H * HH;       // columns (ky, kz): the pitch of an x row in HBM
-    constexpr int BP = KB + 1;       // pitch (complex) of one x row in LDS, one grid
-    constexpr int BP3 = 3 * KB + 1;  // the same for the three gradient components side by side
-    constexpr int NB = H * KB;       // entries of the block
-    constexpr int NT = PENCIL_THREADS;
-    constexpr int R = (NB + NT - 1) / NT;
-    static_assert(NT % KB == 0, "a thread's entries share one column");
-    __shared__ V lds[H * BP3];
-    __shared__ V tw[H];
-    V* buf = lds;
-    const FieldDesc<T>& fd = fds[blockIdx.y];
-    const int c0 = blockIdx.x * KB;
-    const int ncol = min(KB, NC - c0);
-    const int tid = threadIdx.x;
-    make_twiddles<T, H>(tw);
-    // the thread's column (a column past ncol takes the last valid one)
-    const int cc = c0 + min(tid % KB, ncol - 1);
-    const int kyp = cc / HH;
-    const int kz = cc - kyp * HH;
-    const int ky = perm_freq<H>(kyp);
-    const T qy = (T)(ky < H / 2 ? ky : ky - H);
-    // entry u of the block: x row (or permuted kx position) u / KB, column u % KB
-    // (columns past ncol read the last valid one and are written as zero)
-    auto gidx = [&](int u) { return (size_t)(u / KB) * NC + c0 + min(u % KB, ncol - 1); };
-    if constexpr (MODE == MODE_ADJ_SRC || MODE == MODE_ADJ_ACC || MODE == MODE_ADJ_ACC_SRC) {
-        adjoint_pencils<T, H, MODE>(fd, c0, ncol, qy, ky, kz, lds, tw);
-        return;
-    }
-    const V zero = cmake<V, T>(0, 0);
-    if constexpr (MODE == MODE_RHO) {
-        stage<NT, NB, V>([&](int u) { return fd.B1[gidx(u)]; },
-                         [&](int u, const V& v) { buf[(u / KB) * BP + u % KB] = keep_if(u % KB < ncol, v); });
-        __syncthreads();
-        lds_fft<T, H, -1>(buf, KB, 1, BP, tw);
-        __syncthreads();
-        for (int u = tid; u < NB; u += NT) {
-            const int p = u / KB, j = u % KB;
-            const int kx = perm_freq<H>(p);
-            const T qx = (T)(kx < H / 2 ? kx : kx - H);
-            const T qz = (T)kz;
-            const T q2 = qx * qx + qy * qy + qz * qz;
-            const T f = (fd.filt > (T)0 ? exp(-fd.filt * q2) : (T)1) * fd.inv_Ld;
-            const V b = buf[p * BP + j];
-            buf[p * BP + j] = j < ncol ? cmake<V, T>(b.x * f, b.y * f) : zero;
-        }
-        __syncthreads();
-        lds_fft<T, H, +1>(buf, KB, 1, BP, tw);
-        __syncthreads();
-        stage<NT, NB, V>([&](int u) { return buf[(u / KB) * BP + u % KB]; },
-                         [&](int u, const V& v) { if (u % KB < ncol) fd.gspec[gidx(u)] = v; });
-        return;
-    }
-    // alpha of the block, read together with B1 (before the transform)
-    V av[R];
-#pragma unroll
-    for (int q = 0; q < R; ++q) av[q] = fd.alpha[gidx(min(tid + q * NT, NB - 1))];
-    if (UPDATE) {
-        stage<NT, NB, V>([&](int u) { return fd.B1[gidx(u)]; },
-                         [&](int u, const V& v) { buf[(u / KB) * BP + u % KB] = keep_if(u % KB < ncol, v); });
-        __syncthreads();
-        lds_fft<T, H, -1>(buf, KB, 1, BP, tw);
-        __syncthreads();
-    }
-    // spectral update in permuted kx order (position p holds kx = perm_freq(p)),
-    // then Phi alpha, kept in registers
-#pragma unroll
-    for (int q = 0; q < R; ++q) {
-        const int u = tid + q * NT;
-        const int p = u / KB, j = u % KB;
-        V a = zero;
-        if (u < NB && j < ncol) {
-            const int kx = perm_freq<H>(p);
-            const T qx = (T)(kx < H / 2 ? kx : kx - H);
-            const T qz = (T)kz;
-            const T q2 = qx * qx + qy * qy + qz * qz;
-            a = av[q];
-            if (UPDATE) {
-                const T xi2 = q2 * fd.two_pi_over_L * fd.two_pi_over_L;
-                T A, B;
-                mode_ab(fd, xi2 + fd.k2, A, B);
-                const V beta = buf[p * BP + j];
-                const T bs = B * fd.inv_Ld;
-                a = cmake<V, T>(A * a.x + bs * beta.x, A * a.y + bs * beta.y);
-                fd.alpha[gidx(u)] = a;
-            }
-            const T phi = fd.filt > (T)0 ? exp(-fd.filt * q2) : (T)1;
-            a = cmake<V, T>(a.x * phi, a.y * phi);
-        }
-        av[q] = a;
-    }
-    if (UPDATE) __syncthreads();  // beta is read: the three components overwrite it
-    // i xi_d Phi alpha for d = 0, 1, 2 in columns d KB + j (zero at the Nyquist
-    // frequency |q_d| = H/2), transformed along x together
-#pragma unroll
-    for (int q = 0; q < R; ++q) {
-        const int u = tid + q * NT;
-        if (u < NB) {
-            const int p = u / KB, j = u % KB;
-            const int kd[3] = {perm_freq<H>(p), ky, kz};
-            const V a = av[q];
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                const T qd = (T)(kd[d] == H / 2 ? 0 : (kd[d] < H / 2 ? kd[d] : kd[d] - H));
-                const T xi = qd * fd.two_pi_over_L;
-                lds[p * BP3 + d * KB + j] = cmake<V, T>(-xi * a.y, xi * a.x);
-            }
-        }
-    }
-    __syncthreads();
-    lds_fft<T, H, +1>(lds, 3 * KB, 1, BP3, tw);
-    __syncthreads();
-    // component d of entry u at column d KB + u % KB
-#pragma unroll
-    for (int d = 0; d < 3; ++d)
-        stage<NT, NB, V>([&](int u) { return lds[(u / KB) * BP3 + d * KB + u % KB]; },
-                         [&](int u, const V& v) { if (u % KB < ncol) fd.gspec[(size_t)d * H * H * HH + gidx(u)] = v; });
-}
+// H = N1 N2.  First- and last-stage items (n2, column) hold rows n2 + i N2,
+// groups (k1, column) hold the storage positions k1 N2 + i, i.e. the
+// frequencies k1 + N1 i: one group per thread, whose registers carry the modes
+// from the forward transform through the update into the inverse.  LDS carries
+// value q of a column at (q + q / N2) KB + column: four rows of a wave lie on
+// different banks in both stages.
+template <int H> constexpr int pencil_cols() { return Split<H>::N2 > 1 ? KB : 64; }
+template <int H> constexpr int pencil_threads() { return (pencil_cols<H>() * Split<H>::N1 * (Split<H>::N2 > 1) + 63) / 64 * 64 + (Split<H>::N2 > 1 ? 0 : 64); }
 
-// lds holds H (3 KB + 1) values: one grid block at pitch KB + 1, or the three
-// components side by side at pitch 3 KB + 1.
 template <typename T, int H, int MODE>
-__device__ __forceinline__ void adjoint_pencils(const FieldDesc<T>& fd, int c0, int ncol, T qy, int ky, int kz,
-                                                cplx_t<T>* lds, const cplx_t<T>* tw) {
+__global__ __launch_bounds__(pencil_threads<H>()) void k_xpencils(const FieldDesc<T>* __restrict__ fds) {
     using V = cplx_t<T>;
     constexpr int HH = H / 2 + 1;
-    constexpr int BP = KB + 1;
-    constexpr int BP3 = 3 * KB + 1;
-    constexpr int NB = H * KB;
-    constexpr int NT = PENCIL_THREADS;
-    constexpr int R = (NB + NT - 1) / NT;
+    constexpr int NC = H * HH;  // columns (ky, kz): the pitch of an x row in HBM
+    constexpr int N1 = Split<H>::N1, N2 = Split<H>::N2;
+    constexpr int CB = pencil_cols<H>(), NT = pencil_threads<H>();
+    constexpr int NIN = MODE == MODE_ADJ_ACC || MODE == MODE_ADJ_ACC_SRC ? 3 : (MODE == MODE_STEP || MODE == MODE_RHO ? 1 : 0);
+    constexpr int NOUT = MODE == MODE_STEP || MODE == MODE_GRAD ? 3 : (MODE == MODE_ADJ_ACC ? 0 : 1);
+    // LDS for three grids at once where a block is small, so that their stages
+    // share their barriers; above H = 64 one after the other, for more
+    // workgroups per CU (H = 256: 35 KB against 104)
+    constexpr int NBUF = NIN == 3 || (NOUT == 3 && H <= 64) ? 3 : 1;
+    constexpr int LEN = (H + N1) * CB;  // values per grid
+    __shared__ V lds[N2 > 1 ? NBUF * LEN : 1];
+    __shared__ V tw[N2 > 1 ? H : 1];
+    const FieldDesc<T>& fd = fds[blockIdx.y];
+    const int c0 = blockIdx.x * CB;
     const int tid = threadIdx.x;
-    const V zero = cmake<V, T>(0, 0);
-    constexpr int NC = H * HH;
-    auto gidx = [&](int u) { return (size_t)(u / KB) * NC + c0 + min(u % KB, ncol - 1); };
-    auto factors = [&](int p, T& A, T& B, T& phi, T (&xi)[3]) {
-        const int kx = perm_freq<H>(p);
-        const T qx = (T)(kx < H / 2 ? kx : kx - H);
-        const T qz = (T)kz;
-        const T q2 = qx * qx + qy * qy + qz * qz;
-        const T xi2 = q2 * fd.two_pi_over_L * fd.two_pi_over_L;
-        mode_ab(fd, xi2 + fd.k2, A, B);
-        phi = fd.filt > (T)0 ? exp(-fd.filt * q2) : (T)1;
-        const int kd[3] = {kx, ky, kz};
+    // the thread's column (threads past the last column, or past the groups, compute on a valid one and store nothing)
+    const int col = c0 + tid % CB;
+    const bool ok = col < NC && tid < CB * N1;
+    const int cc = min(col, NC - 1);
+    const int kyp = cc / HH, kz = cc - kyp * HH;
+    const int ky = perm_freq<H>(kyp);
+    const int k1 = N2 > 1 ? min(tid / CB, N1 - 1) : 0;  // the thread's group
+    constexpr int GN = N2 > 1 ? N2 : N1;                // its modes: position pos(i), frequency kx(i)
+    auto pos = [&](int i) { return k1 * N2 + i; };
+    auto kx_of = [&](int i) { return N2 > 1 ? k1 + N1 * i : i; };
+    auto lat = [&](int q) { return (q + q / N2) * CB + tid % CB; };
+    V al[GN];
+    if constexpr (MODE != MODE_RHO) {
 #pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            const T q = (T)(kd[d] == H / 2 ? 0 : (kd[d] < H / 2 ? kd[d] : kd[d] - H));
-            xi[d] = q * fd.two_pi_over_L;
+        for (int i = 0; i < GN; ++i) al[i] = ldg(fd.alpha + (size_t)pos(i) * NC + cc);
+    }
+    // factors of the thread's modes; up to 9 modes they are made while the loads are in flight
+    constexpr bool AHEAD = GN <= 9;
+    const T qy = (T)(ky < H / 2 ? ky : ky - H), qz = (T)kz;
+    auto xi_of = [&](int k) { return (T)(k == H / 2 ? 0 : (k < H / 2 ? k : k - H)) * fd.two_pi_over_L; };
+    T fA[GN], fB[GN], fP[GN];
+    auto factors = [&](int i) {
+        const int kx = kx_of(i);
+        const T qx = (T)(kx < H / 2 ? kx : kx - H);
+        const T q2 = qx * qx + qy * qy + qz * qz;
+        if constexpr (MODE != MODE_ADJ_SRC) fP[i] = fd.filt > (T)0 ? exp(-fd.filt * q2) : (T)1;
+        if constexpr (MODE != MODE_RHO && MODE != MODE_GRAD)
+            mode_ab(fd, q2 * fd.two_pi_over_L * fd.two_pi_over_L + fd.k2, fA[i], fB[i]);
+    };
+    auto factors_ahead = [&]() {
+        if constexpr (AHEAD) {
+#pragma unroll
+            for (int i = 0; i < GN; ++i) factors(i);
         }
     };
-    // L^-3 B a of the block into lds (pitch BP), inverse along x, into gspec component 0
-    auto source_out = [&]() {
-        __syncthreads();
-        lds_fft<T, H, +1>(lds, KB, 1, BP, tw);
-        __syncthreads();
-        stage<NT, NB, V>([&](int u) { return lds[(u / KB) * BP + u % KB]; },
-                         [&](int u, const V& v) { if (u % KB < ncol) fd.gspec[gidx(u)] = v; });
-    };
-    if constexpr (MODE == MODE_ADJ_SRC) {
-        stage<NT, NB, V>([&](int u) { return fd.alpha[gidx(u)]; },
-                         [&](int u, const V& a) {
-                             const int p = u / KB, j = u % KB;
-                             V v = zero;
-                             if (j < ncol) {
-                                 T A, B, phi, xi[3];
-                                 factors(p, A, B, phi, xi);
-                                 const T sc = B * fd.inv_Ld;
-                                 v = cmake<V, T>(a.x * sc, a.y * sc);
-                             }
-                             lds[p * BP + j] = v;
-                         });
-        source_out();
-    } else {
-        // abar of the block, read together with the three transformed grids
-        V av[R];
+    // forward: the modes of the NIN input grids, z[d][i]
+    V z[NIN > 0 ? NIN : 1][GN];
+    if constexpr (NIN > 0 && N2 == 1) {
 #pragma unroll
-        for (int q = 0; q < R; ++q) av[q] = fd.alpha[gidx(min(tid + q * NT, NB - 1))];
+        for (int d = 0; d < NIN; ++d) {
 #pragma unroll
-        for (int d = 0; d < 3; ++d)
-            stage<NT, NB, V>([&](int u) { return fd.B1[(size_t)d * H * H * HH + gidx(u)]; },
-                             [&](int u, const V& v) { lds[(u / KB) * BP3 + d * KB + u % KB] = keep_if(u % KB < ncol, v); });
-        __syncthreads();
-        lds_fft<T, H, -1>(lds, 3 * KB, 1, BP3, tw);
-        __syncthreads();
-        // abar <- A abar + sum_d (-i xi_d Phi) F(Gbar_d)
+            for (int i = 0; i < N1; ++i) z[d][i] = ldg(fd.B1 + (size_t)d * H * NC + (size_t)i * NC + cc);
+        }
+        factors_ahead();
 #pragma unroll
-        for (int q = 0; q < R; ++q) {
+        for (int d = 0; d < NIN; ++d) Dft<T, N1, -1>::run(z[d]);
+    } else if constexpr (NIN > 0) {
+        constexpr int NI = NIN * CB * N2, Q = (NI + NT - 1) / NT;  // items (d, n2, column)
+        V r[Q][N1];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int u = min(tid + q * NT, NI - 1);
+            const int c = min(c0 + u % CB, NC - 1), n2 = u / CB % N2, d = u / (CB * N2);
+#pragma unroll
+            for (int i = 0; i < N1; ++i) r[q][i] = ldg(fd.B1 + (size_t)d * H * NC + (size_t)(n2 + i * N2) * NC + c);
+        }
+        make_twiddles<T, H>(tw);
+        factors_ahead();
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
             const int u = tid + q * NT;
-            const int p = u / KB, j = u % KB;
-            V out = zero;
-            if (u < NB && j < ncol) {
-                T A, B, phi, xi[3];
-                factors(p, A, B, phi, xi);
-                V acc = zero;
+            if (u < NI) {
+                const int n2 = u / CB % N2, d = u / (CB * N2);
+                Dft<T, N1, -1>::run(r[q]);
+#pragma unroll
+                for (int k = 1; k < N1; ++k) r[q][k] = cmul(r[q][k], tw[n2 * k]);
+#pragma unroll
+                for (int k = 0; k < N1; ++k) lds[d * LEN + (k * N2 + n2 + k) * CB + u % CB] = r[q][k];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int d = 0; d < NIN; ++d) {
+#pragma unroll
+            for (int i = 0; i < N2; ++i) z[d][i] = lds[d * LEN + lat(pos(i))];
+            Dft<T, N2, -1>::run(z[d]);
+        }
+    } else {
+        if constexpr (N2 > 1) make_twiddles<T, H>(tw);
+        factors_ahead();
+        if constexpr (N2 > 1) __syncthreads();
+    }
+    // the modes: al[i] becomes the spectrum whose (derivatives') inverse transform goes out
+#pragma unroll
+    for (int i = 0; i < GN; ++i) {
+        if constexpr (!AHEAD) factors(i);
+        if constexpr (MODE == MODE_RHO) {
+            al[i] = cscale(z[0][i], fP[i] * fd.inv_Ld);
+        } else if constexpr (MODE == MODE_GRAD) {
+            al[i] = cscale(al[i], fP[i]);
+        } else {
+            const T A = fA[i], B = fB[i];
+            V a = al[i];
+            if constexpr (MODE == MODE_STEP) {
+                const T bs = B * fd.inv_Ld;
+                a = cmake<V, T>(A * a.x + bs * z[0][i].x, A * a.y + bs * z[0][i].y);
+            } else if constexpr (MODE != MODE_ADJ_SRC) {
+                // abar <- A abar + sum_d (-i xi_d Phi) F(Gbar_d)
+                const T xi[3] = {xi_of(kx_of(i)), xi_of(ky), xi_of(kz)};
+                V acc = cmake<V, T>(0, 0);
 #pragma unroll
                 for (int d = 0; d < 3; ++d) {
-                    const V g = lds[p * BP3 + d * KB + j];
-                    const T c = xi[d] * phi;
-                    // (-i c) g = (c g.y, -c g.x)
-                    acc.x += c * g.y;
-                    acc.y -= c * g.x;
+                    const T c = xi[d] * fP[i];
+                    acc.x += c * z[NIN == 3 ? d : 0][i].y;  // (-i c) g = (c g.y, -c g.x)
+                    acc.y -= c * z[NIN == 3 ? d : 0][i].x;
                 }
-                const V a = av[q];
-                const V na = cmake<V, T>(A * a.x + acc.x, A * a.y + acc.y);
-                fd.alpha[gidx(u)] = na;
-                const T sc = B * fd.inv_Ld;
-                out = cmake<V, T>(na.x * sc, na.y * sc);
+                a = cmake<V, T>(A * a.x + acc.x, A * a.y + acc.y);
             }
-            av[q] = out;
+            if (MODE != MODE_ADJ_SRC && ok) stg(fd.alpha + (size_t)pos(i) * NC + cc, a);
+            if constexpr (MODE == MODE_STEP) al[i] = cscale(a, fP[i]);
+            else al[i] = cscale(a, B * fd.inv_Ld);
         }
-        if constexpr (MODE == MODE_ADJ_ACC_SRC) {
-            __syncthreads();  // the transformed grids are read
-#pragma unroll
-            for (int q = 0; q < R; ++q) {
-                const int u = tid + q * NT;
-                if (u < NB) lds[(u / KB) * BP + u % KB] = av[q];
+    }
+    if constexpr (NOUT > 0) {
+        // mode i of output grid d
+        auto out_of = [&](int d, int i) -> V {
+            if constexpr (NOUT == 1) {
+                return al[i];
+            } else {
+                const T xi = xi_of(d == 0 ? kx_of(i) : (d == 1 ? ky : kz));
+                return cmake<V, T>(-xi * al[i].y, xi * al[i].x);
             }
-            source_out();
+        };
+        if constexpr (N2 == 1) {
+#pragma unroll
+            for (int d = 0; d < NOUT; ++d) {
+                V r[N1];
+#pragma unroll
+                for (int i = 0; i < N1; ++i) r[i] = out_of(d, i);
+                Dft<T, N1, +1>::run(r);
+                if (ok) {
+#pragma unroll
+                    for (int i = 0; i < N1; ++i) stg(fd.gspec + (size_t)d * H * NC + (size_t)i * NC + cc, r[i]);
+                }
+            }
+        } else {
+            constexpr int ND = NBUF == 3 && NOUT == 3 ? 3 : 1;  // grids per exchange
+            constexpr int NI = ND * CB * N2;
+            if constexpr (NIN == 3) __syncthreads();  // groups of all three grids are read
+#pragma unroll 1
+            for (int d0 = 0; d0 < NOUT; d0 += ND) {
+                if (d0 > 0) __syncthreads();  // the previous grid has been read
+                if (tid < CB * N1) {
+#pragma unroll
+                    for (int d = 0; d < ND; ++d) {
+                        V r[N2];
+#pragma unroll
+                        for (int i = 0; i < N2; ++i) r[i] = out_of(d0 + d, i);
+                        Dft<T, N2, +1>::run(r);
+#pragma unroll
+                        for (int i = 1; i < N2; ++i) r[i] = cmul(r[i], cconj(tw[i * k1]));
+#pragma unroll
+                        for (int i = 0; i < N2; ++i) lds[d * LEN + lat(pos(i))] = r[i];
+                    }
+                }
+                __syncthreads();
+                for (int u = tid; u < NI; u += NT) {
+                    const int c = c0 + u % CB, n2 = u / CB % N2, d = u / (CB * N2);
+                    V r[N1];
+#pragma unroll
+                    for (int k = 0; k < N1; ++k) r[k] = lds[d * LEN + (k * N2 + n2 + k) * CB + u % CB];
+                    Dft<T, N1, +1>::run(r);
+                    if (c < NC) {
+                        V* o = fd.gspec + (size_t)(d0 + d) * H * NC + c;
+#pragma unroll
+                        for (int i = 0; i < N1; ++i) stg(o + (size_t)(n2 + i * N2) * NC, r[i]);
+                    }
+                }
+            }
         }
     }
 }
 
 // ---------------------------------------------------------------------------
 // Pass 3: inverse along y, complex-to-real inverse along z, per component.
-//
-// Along z the half spectrum X_0 .. X_M of each row gives the M-point input
-//   Z_k = (X_k + conj X_{M-k}) + i exp(+2 pi i k / H) (X_k - conj X_{M-k}),
-// whose inverse transform is z[m] = x[2m] + i x[2m+1] (unnormalised, as the
-// gradient synthesis needs).
 // ---------------------------------------------------------------------------
 template <typename T, int H>
-__global__ __launch_bounds__(PLANE_THREADS) void k_inv_planes(const FieldDesc<T>* __restrict__ fds, int ncomp) {
+__global__ __launch_bounds__(plane_threads<H>()) void k_inv_planes(const FieldDesc<T>* __restrict__ fds, int ncomp) {
     using V = cplx_t<T>;
-    constexpr int M = H / 2;
-    constexpr int HH = M + 1;
-    constexpr int OP = HH;
-    constexpr int NP = M / 2 + 1;
-    constexpr int PPT = (H * NP + PLANE_THREADS - 1) / PLANE_THREADS;
-    __shared__ V buf[H * OP];
+    using Z = ZRows<T, H, H>;
+    constexpr int HH = H / 2 + 1, NT = plane_threads<H>();
+    constexpr int N1 = Split<H>::N1, N2 = Split<H>::N2;
+    __shared__ V buf[Z::SIZE];
     __shared__ V tw[H];
-    __shared__ V twm[M];
     const FieldDesc<T>& fd = fds[blockIdx.y];
     // blocks 8c + r (c = (ix / 8) ncomp + d) keep the components of a plane on
     // one XCD; grids that are not a multiple of 8 take block ix ncomp + d
@@ -531,46 +632,65 @@ __global__ __launch_bounds__(PLANE_THREADS) void k_inv_planes(const FieldDesc<T>
         ix = b / ncomp;
     }
     const int tid = threadIdx.x;
-    make_twiddles<T, H>(tw);
-    make_twiddles<T, M>(twm);
     const V* in = fd.gspec + ((size_t)d * H + ix) * H * HH;
-    stage<PLANE_THREADS, H * HH, V>([&](int u) { return in[u]; }, [&](int u, const V& v) { buf[u] = v; });
-    __syncthreads();
-    lds_fft<T, H, +1>(buf, HH, 1, OP, tw);
-    __syncthreads();
-    V xa[PPT], xb[PPT];
+    // along y: groups (k1, kz) of the positions k1 N2 + i, then items (n2, kz)
+    constexpr int NG = HH * N1, NI = HH * N2;
+    if constexpr (N2 > 1) {
+        constexpr int Q = (NG + NT - 1) / NT;
+        V r[Q][N2];
 #pragma unroll
-    for (int q = 0; q < PPT; ++q) {
-        const int u = tid + q * PLANE_THREADS;
-        if (u < H * NP) {
-            const int row = u / NP, k = u % NP;
-            xa[q] = buf[row * OP + k];
-            xb[q] = buf[row * OP + (M - k)];
+        for (int q = 0; q < Q; ++q) {
+            const int u = tid + q * NT;
+            if (u < NG) {
+#pragma unroll
+                for (int i = 0; i < N2; ++i) r[q][i] = ldg(in + (u / HH * N2 + i) * HH + u % HH);
+            }
         }
-    }
-    __syncthreads();
+        make_twiddles<T, H>(tw);
+        __syncthreads();
 #pragma unroll
-    for (int q = 0; q < PPT; ++q) {
-        const int u = tid + q * PLANE_THREADS;
-        if (u < H * NP) {
-            const int row = u / NP, k = u % NP;
-            // Z_k from (X_k, X_{M-k}); Z_{M-k} from (X_{M-k}, X_k) for 0 < k < M - k
-            const V s1 = cadd(xa[q], cconj(xb[q])), d1 = csub(xa[q], cconj(xb[q]));
-            const V t1 = cmul(cconj(tw[k]), d1);
-            buf[row * OP + perm_pos<M>(k % M)] = cmake<V, T>(s1.x - t1.y, s1.y + t1.x);
-            if (k != 0 && k != M - k) {
-                const V s2 = cadd(xb[q], cconj(xa[q])), d2 = csub(xb[q], cconj(xa[q]));
-                const V t2 = cmul(cconj(tw[M - k]), d2);
-                buf[row * OP + perm_pos<M>(M - k)] = cmake<V, T>(s2.x - t2.y, s2.y + t2.x);
+        for (int q = 0; q < Q; ++q) {
+            const int u = tid + q * NT;
+            if (u < NG) {
+                Dft<T, N2, +1>::run(r[q]);
+#pragma unroll
+                for (int i = 1; i < N2; ++i) r[q][i] = cmul(r[q][i], cconj(tw[i * (u / HH)]));
+#pragma unroll
+                for (int i = 0; i < N2; ++i) buf[Z::freq_at(u / HH * N2 + i, u % HH)] = r[q][i];
+            }
+        }
+        __syncthreads();
+        for (int u = tid; u < NI; u += NT) {
+            const int kz = u % HH, n2 = u / HH;
+            V v[N1];
+#pragma unroll
+            for (int k = 0; k < N1; ++k) v[k] = buf[Z::freq_at(k * N2 + n2, kz)];
+            Dft<T, N1, +1>::run(v);
+#pragma unroll
+            for (int i = 0; i < N1; ++i) buf[Z::freq_at(i * N2 + n2, kz)] = v[i];
+        }
+    } else {
+        constexpr int Q = (NI + NT - 1) / NT;
+        V v[Q][N1];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int u = min(tid + q * NT, NI - 1);
+#pragma unroll
+            for (int k = 0; k < N1; ++k) v[q][k] = ldg(in + k * HH + u);
+        }
+        make_twiddles<T, H>(tw);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int u = tid + q * NT;
+            if (u < NI) {
+                Dft<T, N1, +1>::run(v[q]);
+#pragma unroll
+                for (int i = 0; i < N1; ++i) buf[Z::freq_at(i, u)] = v[q][i];
             }
         }
     }
     __syncthreads();
-    lds_fft<T, M, +1>(buf, H, OP, 1, twm);
-    __syncthreads();
-    V* outp = reinterpret_cast<V*>(fd.G + ((size_t)d * H + ix) * H * H);  // (x[2m], x[2m+1]) pairs
-    stage<PLANE_THREADS, H * M, V>([&](int u) { return buf[(u / M) * OP + u % M]; },
-                                   [&](int u, const V& v) { outp[u] = v; });
+    Z::template inverse<NT>(buf, tw, reinterpret_cast<V*>(fd.G + ((size_t)d * H + ix) * H * H));
 }
 
 // ---------------------------------------------------------------------------
@@ -591,140 +711,91 @@ constexpr int ROW_THREADS = 256;
 template <typename T, int H>
 __global__ __launch_bounds__(ROW_THREADS) void k_fwd_zrows(const FieldDesc<T>* __restrict__ fds, int consume) {
     using V = cplx_t<T>;
-    constexpr int M = H / 2;
-    constexpr int HH = M + 1;
-    constexpr int OP = HH;
-    constexpr int NP = M / 2 + 1;
-    constexpr int PPT = (ZROWS * NP + ROW_THREADS - 1) / ROW_THREADS;
+    using Z = ZRows<T, H, ZROWS>;
+    constexpr int HH = H / 2 + 1;
     constexpr int NRB = H * H / ZROWS;  // row blocks per component
-    __shared__ V buf[ZROWS * OP];
+    __shared__ V buf[Z::SIZE];
     __shared__ V tw[H];
-    __shared__ V twm[M];
     const FieldDesc<T>& fd = fds[blockIdx.y];
     const int comp = blockIdx.x / NRB;
     const size_t row0 = (size_t)(blockIdx.x % NRB) * ZROWS;  // row r = x H + y
-    const int tid = threadIdx.x, nt = blockDim.x;
-    make_twiddles<T, H>(tw);
-    make_twiddles<T, M>(twm);
-    T* rows = fd.phi + ((size_t)comp * H * H + row0) * H;
-    V* rv = reinterpret_cast<V*>(rows);
-    stage<ROW_THREADS, ZROWS * M, V>([&](int u) { return rv[u]; },
-                                     [&](int u, const V& v) { buf[(u / M) * OP + u % M] = v; });
-    __syncthreads();
-    if (consume) {
-        for (int u = tid; u < ZROWS * M; u += nt) rv[u] = cmake<V, T>(0, 0);
-        if (blockIdx.x == 0 && tid == 0 && fd.step != nullptr) *fd.step += 1u;
-    }
-    lds_fft<T, M, -1>(buf, ZROWS, OP, 1, twm);
-    __syncthreads();
-    V za[PPT], zb[PPT];
-#pragma unroll
-    for (int q = 0; q < PPT; ++q) {
-        const int u = tid + q * ROW_THREADS;
-        if (u < ZROWS * NP) {
-            const int row = u / NP, k = u % NP;
-            za[q] = buf[row * OP + perm_pos<M>(k % M)];
-            zb[q] = buf[row * OP + perm_pos<M>((M - k) % M)];
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < PPT; ++q) {
-        const int u = tid + q * ROW_THREADS;
-        if (u < ZROWS * NP) {
-            const int row = u / NP, k = u % NP;
-            const V zc = cconj(zb[q]);
-            const V e = cscale(cadd(za[q], zc), (T)0.5);
-            const V dd = csub(za[q], zc);
-            const V o = cmake<V, T>(dd.y * (T)0.5, -dd.x * (T)0.5);
-            buf[row * OP + k] = cadd(e, cmul(tw[k], o));
-            if (k != M - k) buf[row * OP + (M - k)] = cadd(cconj(e), cmul(tw[M - k], cconj(o)));
-        }
-    }
-    __syncthreads();
+    const int tid = threadIdx.x;
+    if (consume && blockIdx.x == 0 && tid == 0 && fd.step != nullptr) *fd.step += 1u;
+    Z::template forward<ROW_THREADS>(buf, tw, reinterpret_cast<V*>(fd.phi + ((size_t)comp * H * H + row0) * H), consume != 0);
     V* out = fd.B1 + ((size_t)comp * H * H + row0) * HH;
-    stage<ROW_THREADS, ZROWS * HH, V>([&](int u) { return buf[u]; }, [&](int u, const V& v) { out[u] = v; });
+    for (int u = tid; u < ZROWS * HH; u += ROW_THREADS) stg(out + u, Z::split(buf, tw, u / HH, u % HH));
 }
 
 template <typename T, int H, int DIR>
-__global__ __launch_bounds__(PENCIL_THREADS) void k_ycols(const FieldDesc<T>* __restrict__ fds) {
+__global__ __launch_bounds__(KB * Split<H>::N1) void k_ycols(const FieldDesc<T>* __restrict__ fds) {
     using V = cplx_t<T>;
     constexpr int HH = H / 2 + 1;
     constexpr int NKB = (HH + KB - 1) / KB;
-    constexpr int BP = KB + 1;
-    __shared__ V buf[H * BP];
+    constexpr int N1 = Split<H>::N1, N2 = Split<H>::N2;
+    static_assert(N1 == N2, "one item of each stage per thread");
+    __shared__ V lds[(H + N1) * KB];  // as in k_xpencils
     __shared__ V tw[H];
     const FieldDesc<T>& fd = fds[blockIdx.y];
     const int kb = blockIdx.x % NKB, rest = blockIdx.x / NKB;
     const int x = rest % H, comp = rest / H;
-    const int kz0 = kb * KB;
-    const int ncol = min(KB, HH - kz0);
-    V* base = (DIR < 0 ? fd.B1 : fd.gspec) + ((size_t)comp * H + x) * H * HH;
+    const int tid = threadIdx.x, a = tid / KB, c = tid % KB;  // a: n2 or k1
+    const bool ok = kb * KB + c < HH;
+    V* base = (DIR < 0 ? fd.B1 : fd.gspec) + ((size_t)comp * H + x) * H * HH + min(kb * KB + c, HH - 1);
+    V r[N1];
+    // forward: rows n2 + i N2 in, positions k1 N2 + i out; inverse: the other way round
+    auto item = [&](int i) { return a + i * N2; };
+    auto group = [&](int i) { return a * N2 + i; };
+#pragma unroll
+    for (int i = 0; i < N1; ++i) r[i] = ldg(base + (size_t)(DIR < 0 ? item(i) : group(i)) * HH);
     make_twiddles<T, H>(tw);
-    auto gi = [&](int u) { return (size_t)(u / KB) * HH + kz0 + min(u % KB, ncol - 1); };
-    stage<PENCIL_THREADS, H * KB, V>(
-        [&](int u) { return base[gi(u)]; },
-        [&](int u, const V& v) { buf[(u / KB) * BP + u % KB] = keep_if(u % KB < ncol, v); });
     __syncthreads();
-    lds_fft<T, H, DIR>(buf, KB, 1, BP, tw);
+    Dft<T, N1, DIR>::run(r);
+#pragma unroll
+    for (int i = 1; i < N1; ++i) r[i] = cmul(r[i], DIR < 0 ? tw[a * i] : cconj(tw[a * i]));
+    // forward: r[k1] at position k1 N2 + n2; inverse: r[n2] at position k1 N2 + n2
+#pragma unroll
+    for (int i = 0; i < N1; ++i) {
+        const int q = DIR < 0 ? i * N2 + a : a * N2 + i;
+        lds[(q + q / N2) * KB + c] = r[i];
+    }
     __syncthreads();
-    stage<PENCIL_THREADS, H * KB, V>([&](int u) { return buf[(u / KB) * BP + u % KB]; },
-                                     [&](int u, const V& v) { if (u % KB < ncol) base[gi(u)] = v; });
+#pragma unroll
+    for (int i = 0; i < N1; ++i) {
+        const int q = DIR < 0 ? a * N2 + i : i * N2 + a;
+        r[i] = lds[(q + q / N2) * KB + c];
+    }
+    Dft<T, N1, DIR>::run(r);
+    if (ok) {
+#pragma unroll
+        for (int i = 0; i < N1; ++i) stg(base + (size_t)(DIR < 0 ? group(i) : item(i)) * HH, r[i]);
+    }
 }
 
 template <typename T, int H>
 __global__ __launch_bounds__(ROW_THREADS) void k_inv_zrows(const FieldDesc<T>* __restrict__ fds) {
     using V = cplx_t<T>;
-    constexpr int M = H / 2;
-    constexpr int HH = M + 1;
-    constexpr int OP = HH;
-    constexpr int NP = M / 2 + 1;
-    constexpr int PPT = (ZROWS * NP + ROW_THREADS - 1) / ROW_THREADS;
+    using Z = ZRows<T, H, ZROWS>;
+    constexpr int HH = H / 2 + 1;
     constexpr int NRB = H * H / ZROWS;
-    __shared__ V buf[ZROWS * OP];
+    constexpr int NL = ZROWS * HH, Q = (NL + ROW_THREADS - 1) / ROW_THREADS;
+    __shared__ V buf[Z::SIZE];
     __shared__ V tw[H];
-    __shared__ V twm[M];
     const FieldDesc<T>& fd = fds[blockIdx.y];
     const int d = blockIdx.x / NRB;
     const size_t row0 = (size_t)(blockIdx.x % NRB) * ZROWS;
     const int tid = threadIdx.x;
-    make_twiddles<T, H>(tw);
-    make_twiddles<T, M>(twm);
     const V* in = fd.gspec + ((size_t)d * H * H + row0) * HH;
-    stage<ROW_THREADS, ZROWS * HH, V>([&](int u) { return in[u]; }, [&](int u, const V& v) { buf[u] = v; });
-    __syncthreads();
-    V xa[PPT], xb[PPT];
+    V v[Q];
 #pragma unroll
-    for (int q = 0; q < PPT; ++q) {
+    for (int q = 0; q < Q; ++q) v[q] = ldg(in + min(tid + q * ROW_THREADS, NL - 1));
+    make_twiddles<T, H>(tw);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
         const int u = tid + q * ROW_THREADS;
-        if (u < ZROWS * NP) {
-            const int row = u / NP, k = u % NP;
-            xa[q] = buf[row * OP + k];
-            xb[q] = buf[row * OP + (M - k)];
-        }
+        if (u < NL) buf[Z::freq_at(u / HH, u % HH)] = v[q];
     }
     __syncthreads();
-#pragma unroll
-    for (int q = 0; q < PPT; ++q) {
-        const int u = tid + q * ROW_THREADS;
-        if (u < ZROWS * NP) {
-            const int row = u / NP, k = u % NP;
-            const V s1 = cadd(xa[q], cconj(xb[q])), d1 = csub(xa[q], cconj(xb[q]));
-            const V t1 = cmul(cconj(tw[k]), d1);
-            buf[row * OP + perm_pos<M>(k % M)] = cmake<V, T>(s1.x - t1.y, s1.y + t1.x);
-            if (k != 0 && k != M - k) {
-                const V s2 = cadd(xb[q], cconj(xa[q])), d2 = csub(xb[q], cconj(xa[q]));
-                const V t2 = cmul(cconj(tw[M - k]), d2);
-                buf[row * OP + perm_pos<M>(M - k)] = cmake<V, T>(s2.x - t2.y, s2.y + t2.x);
-            }
-        }
-    }
-    __syncthreads();
-    lds_fft<T, M, +1>(buf, ZROWS, OP, 1, twm);
-    __syncthreads();
-    V* outp = reinterpret_cast<V*>(fd.G + ((size_t)d * H * H + row0) * H);
-    stage<ROW_THREADS, ZROWS * M, V>([&](int u) { return buf[(u / M) * OP + u % M]; },
-                                     [&](int u, const V& v) { outp[u] = v; });
+    Z::template inverse<ROW_THREADS>(buf, tw, reinterpret_cast<V*>(fd.G + ((size_t)d * H * H + row0) * H));
 }
 
 // ---------------------------------------------------------------------------
@@ -743,15 +814,15 @@ static hipError_t fwd_planes_h(const FieldDesc<T>* fd, int count, int ncomp, boo
         constexpr int NKB = (H / 2 + 1 + KB - 1) / KB;
         launch_kernel((k_fwd_zrows<T, H>), dim3(ncomp * H * H / ZROWS, count), dim3(ROW_THREADS), 0, s, fd,
                       consume ? 1 : 0);
-        launch_kernel((k_ycols<T, H, -1>), dim3(ncomp * H * NKB, count), dim3(PENCIL_THREADS), 0, s, fd);
+        launch_kernel((k_ycols<T, H, -1>), dim3(ncomp * H * NKB, count), dim3(KB * Split<H>::N1), 0, s, fd);
     } else {
-        launch_kernel((k_fwd_planes<T, H>), dim3(H * ncomp, count), dim3(FWD_THREADS), 0, s, fd, consume ? 1 : 0);
+        launch_kernel((k_fwd_planes<T, H>), dim3(H * ncomp, count), dim3(plane_threads<H>()), 0, s, fd, consume ? 1 : 0);
     }
     return hipGetLastError();
 }
 template <typename T, int H>
 static hipError_t xpencils_h(const FieldDesc<T>* fd, int count, int mode, hipStream_t s) {
-    const dim3 g((H * (H / 2 + 1) + KB - 1) / KB, count), b(PENCIL_THREADS);
+    const dim3 g((H * (H / 2 + 1) + pencil_cols<H>() - 1) / pencil_cols<H>(), count), b(pencil_threads<H>());
     switch (mode) {
         case MODE_STEP: launch_kernel((k_xpencils<T, H, MODE_STEP>), g, b, 0, s, fd); break;
         case MODE_GRAD: launch_kernel((k_xpencils<T, H, MODE_GRAD>), g, b, 0, s, fd); break;
@@ -767,10 +838,10 @@ template <typename T, int H>
 static hipError_t inv_planes_h(const FieldDesc<T>* fd, int count, int ncomp, hipStream_t s) {
     if constexpr (H > MAX_PLANE_H) {
         constexpr int NKB = (H / 2 + 1 + KB - 1) / KB;
-        launch_kernel((k_ycols<T, H, +1>), dim3(ncomp * H * NKB, count), dim3(PENCIL_THREADS), 0, s, fd);
+        launch_kernel((k_ycols<T, H, +1>), dim3(ncomp * H * NKB, count), dim3(KB * Split<H>::N1), 0, s, fd);
         launch_kernel((k_inv_zrows<T, H>), dim3(ncomp * H * H / ZROWS, count), dim3(ROW_THREADS), 0, s, fd);
     } else {
-        launch_kernel((k_inv_planes<T, H>), dim3(ncomp * H, count), dim3(PLANE_THREADS), 0, s, fd, ncomp);
+        launch_kernel((k_inv_planes<T, H>), dim3(ncomp * H, count), dim3(plane_threads<H>()), 0, s, fd, ncomp);
     }
     return hipGetLastError();
 }

@@ -22,8 +22,8 @@ namespace sipf {
 
 template <int N> struct Split;
 template <> struct Split<4>   { static constexpr int N1 = 4,  N2 = 1; };
-template <> struct Split<8>   { static constexpr int N1 = 8,  N2 = 1; };
-template <> struct Split<16>  { static constexpr int N1 = 16, N2 = 1; };
+template <> struct Split<8>   { static constexpr int N1 = 4,  N2 = 2; };
+template <> struct Split<16>  { static constexpr int N1 = 4,  N2 = 4; };
 template <> struct Split<32>  { static constexpr int N1 = 8,  N2 = 4; };
 template <> struct Split<64>  { static constexpr int N1 = 8,  N2 = 8; };
 template <> struct Split<128> { static constexpr int N1 = 16, N2 = 8; };
@@ -31,9 +31,9 @@ template <> struct Split<256> { static constexpr int N1 = 16, N2 = 16; };
 // lengths with odd factors
 template <> struct Split<3>   { static constexpr int N1 = 3,  N2 = 1; };
 template <> struct Split<5>   { static constexpr int N1 = 5,  N2 = 1; };
-template <> struct Split<6>   { static constexpr int N1 = 6,  N2 = 1; };
+template <> struct Split<6>   { static constexpr int N1 = 3,  N2 = 2; };
 template <> struct Split<11>  { static constexpr int N1 = 11, N2 = 1; };
-template <> struct Split<12>  { static constexpr int N1 = 12, N2 = 1; };
+template <> struct Split<12>  { static constexpr int N1 = 4,  N2 = 3; };
 template <> struct Split<22>  { static constexpr int N1 = 11, N2 = 2; };
 template <> struct Split<23>  { static constexpr int N1 = 23, N2 = 1; };
 template <> struct Split<45>  { static constexpr int N1 = 9,  N2 = 5; };
@@ -187,71 +187,6 @@ template <typename T, int R, int DIR> struct Dft<T, R, DIR, true> {
         combine<0>(x, e, o);
     }
 };
-
-// count independent length-N transforms; element e of transform b at
-// buf[b * bs + e * es].  tw[m] = exp(-2 pi i m / N).  Caller synchronises
-// before and after.
-template <typename T, int N, int DIR>
-__device__ __forceinline__ void lds_fft(cplx_t<T>* buf, int count, int bs, int es, const cplx_t<T>* tw) {
-    using V = cplx_t<T>;
-    constexpr int N1 = Split<N>::N1, N2 = Split<N>::N2;
-    const int tid = threadIdx.x, nt = blockDim.x;
-    if constexpr (DIR < 0) {
-        for (int u = tid; u < count * N2; u += nt) {
-            const int b = u % count, n2 = u / count;
-            V* p = buf + b * bs + n2 * es;
-            V r[N1];
-#pragma unroll
-            for (int i = 0; i < N1; ++i) r[i] = p[i * N2 * es];
-            Dft<T, N1, -1>::run(r);
-            if constexpr (N2 > 1) {
-#pragma unroll
-                for (int k1 = 1; k1 < N1; ++k1) r[k1] = cmul(r[k1], tw[n2 * k1]);
-            }
-#pragma unroll
-            for (int i = 0; i < N1; ++i) p[i * N2 * es] = r[i];
-        }
-        if constexpr (N2 > 1) {
-            __syncthreads();
-            for (int u = tid; u < count * N1; u += nt) {
-                const int b = u % count, k1 = u / count;
-                V* p = buf + b * bs + k1 * N2 * es;
-                V r[N2];
-#pragma unroll
-                for (int i = 0; i < N2; ++i) r[i] = p[i * es];
-                Dft<T, N2, -1>::run(r);
-#pragma unroll
-                for (int i = 0; i < N2; ++i) p[i * es] = r[i];
-            }
-        }
-    } else {
-        if constexpr (N2 > 1) {
-            for (int u = tid; u < count * N1; u += nt) {
-                const int b = u % count, k1 = u / count;
-                V* p = buf + b * bs + k1 * N2 * es;
-                V r[N2];
-#pragma unroll
-                for (int i = 0; i < N2; ++i) r[i] = p[i * es];
-                Dft<T, N2, +1>::run(r);
-#pragma unroll
-                for (int n2 = 1; n2 < N2; ++n2) r[n2] = cmul(r[n2], cconj(tw[n2 * k1]));
-#pragma unroll
-                for (int i = 0; i < N2; ++i) p[i * es] = r[i];
-            }
-            __syncthreads();
-        }
-        for (int u = tid; u < count * N2; u += nt) {
-            const int b = u % count, n2 = u / count;
-            V* p = buf + b * bs + n2 * es;
-            V r[N1];
-#pragma unroll
-            for (int i = 0; i < N1; ++i) r[i] = p[i * N2 * es];
-            Dft<T, N1, +1>::run(r);
-#pragma unroll
-            for (int i = 0; i < N1; ++i) p[i * N2 * es] = r[i];
-        }
-    }
-}
 
 template <int N> __device__ __forceinline__ int perm_pos(int k) {
     return (k % Split<N>::N1) * Split<N>::N2 + k / Split<N>::N1;
