@@ -124,7 +124,16 @@ bool sorted_pass(const sipf_params* p, int n) {
 // that is not a power of two takes the same rule with ceil(H / 8) (the last
 // tile of an axis may be partial).  2-D: 16-cell tiles up to H = 1024 and H/64
 // above.
-int default_tile(const sipf_params* p, bool sorted) {
+//
+// P: the instance's particle count (0: at most 16 tiles per axis, as for a
+// tile that callers pass).  H = 256 takes 32 tiles per axis from MANY_TILES_P
+// particles on: 16-cell tiles fill a window when just sorted and leave it with
+// the first steps, while a sort into 32768 keys costs some 30 us more.  Us per
+// step with 16-cell / 8-cell tiles at their best periods: ring P = 1e5 413 /
+// 414, 3e5 443 / 415, 1e6 542 / 424, 3e6 792 / 461; mixed P = 1e6
+// 839 / 666.
+constexpr int64_t MANY_TILES_P = int64_t(1) << 18;
+int default_tile(const sipf_params* p, bool sorted, int64_t P) {
     const int least = std::min(p->H, sorted ? 8 : 4);
     if (dim_of(p) == 3 && !is_pow2(p->H)) {
         if (p->tile) return p->tile;
@@ -136,19 +145,24 @@ int default_tile(const sipf_params* p, bool sorted) {
         return t;
     }
     int t = p->tile ? p->tile : (p->H >= 128 ? 8 : (p->H >= 16 ? std::max(least, p->H / 8) : p->H));
-    if (p->H / t > 16) t = p->H / 16;
+    if (p->H / t > 16 && P < MANY_TILES_P) t = p->H / 16;
     return t;
 }
-// Re-sort period: every 6 steps in 3-D (4 in 2-D), or more often when the
-// Brownian spread over the period, sqrt(2 mu tau n), would exceed a quarter of
-// a tile (item boxes then outgrow their LDS windows and the pass falls back to
-// global atomics).  3-D, FP32 ms per step at periods 4 / 6 / 8: torus P = 1e7
-// 0.283 / 0.277 / 0.302 (the collapsing ring's drift outgrows the windows at
-// 8); blob P = 2e6 0.138 / 0.124 / 0.115; mixed P = 1e6 0.069 / 0.067 / 0.067.
-int default_resort(const sipf_params* p, bool sorted) {
+// Re-sort period: in 3-D every 8 steps (10 in the sorted pass) up to H = 64
+// and 6 above, in 2-D 4; or more often when the Brownian spread over the
+// period, sqrt(2 mu tau n), would exceed a quarter of a tile: items' boxes
+// then outgrow their LDS windows and strays go to global memory, which costs
+// most where the grid is finest.  Us per step at periods 4 / 6 / 8 / 12: mixed
+// H = 64, P = 1e6, 57.5 / 55.9 / 55.5 / 55.9 and P = 3e6 106.3 / 102.8 / 102.3
+// / 105.5; blob H = 32, P = 1e6, 57.6 / 54.5 / 52.5 / 50.4; mixed H = 128,
+// P = 3e6, 177 / 190 / 203; torus H = 128, P = 3e6, 125 / 122 / 124; ring
+// H = 256, P = 1e6, 434 / 428 / 425; mixed H = 256, P = 1e6, 720 / 761 / 807;
+// sorted pass, 64-instance ensemble (H = 32 and 64), 6 / 8 / 10 / 12: 575 /
+// 555 / 546 / 548.
+int default_resort(const sipf_params* p, int tile, bool sorted) {
     if (p->resort_every) return p->resort_every;
-    const double cap = dim_of(p) == 2 ? 4.0 : 6.0;
-    const double q = default_tile(p, sorted) * p->L / p->H / 4.0;
+    const double cap = dim_of(p) == 2 ? 4.0 : (p->H > 64 ? 6.0 : (sorted ? 10.0 : 8.0));
+    const double q = tile * p->L / p->H / 4.0;
     const double spread = 2.0 * p->mu * p->dt;
     if (spread <= 0) return (int)cap;
     const double n = std::floor(q * q / spread);
@@ -240,8 +254,9 @@ struct Group {
     std::vector<int> fslot;  // FieldDesc slot of instance i
     uint32_t* steps = nullptr;  // per-instance completed-step counters
     int* errs = nullptr;        // per-instance error flags
-    uint32_t* counts = nullptr;  // n x MAX_KEYS tile counts (zero between sorts)
-    uint32_t* cursor = nullptr;  // n x MAX_KEYS tile starts / scatter cursors
+    uint32_t* counts = nullptr;  // n x kstride tile counts (zero between sorts)
+    int kstride = 4096;          // sort keys per instance (sort_keys)
+    uint32_t* cursor = nullptr;  // n x kstride tile starts / scatter cursors
     void* pdesc = nullptr;       // 2n PartDesc<T>: set s of instance i at s*n + i
     void* fdesc = nullptr;       // n FieldDesc<T>, grouped by H class
     SortChunk* chunks = nullptr;
@@ -537,7 +552,7 @@ template <typename T> int do_sort(Group* g) {
     {
         Timed t(g, SIPF_PHASE_SORT);
         HIPCHK(launch_sort<T>(g->dim, pdesc_dev<T>(g, g->cur), pdesc_dev<T>(g, dst), g->chunks, g->nchunks, (int)g->in.size(),
-                              g->counts, g->cursor, g->seg, g->seg_off, g->seg_n, g->items, g->nitems, g->chunk,
+                              g->counts, g->cursor, g->kstride, g->seg, g->seg_off, g->seg_n, g->items, g->nitems, g->chunk,
                               g->stream, g->counts_ready));
         g->counts_ready = false;
     }
@@ -559,7 +574,7 @@ hipError_t particles_any(const Group* g, const PartDesc<T>* pd, bool deposit, bo
     return g->dim == 2 ? launch_particles2<T>(pd, g->items, g->nitems, g->pgrid, deposit, push, g->scheme,
                                               g->win_bytes, g->stream)
                        : launch_particles<T>(pd, g->items, g->nitems, g->pgrid, deposit, push, g->scheme,
-                                             g->win_bytes, g->pow2, g->sorted, g->stream, kcounts);
+                                             g->win_bytes, g->pow2, g->sorted, g->stream, kcounts, g->kstride);
 }
 template <typename T> hipError_t field_fwd(const Group* g, int H, const FieldDesc<T>* fd, int count, bool consume) {
     return g->dim == 2 ? launch_fwd_rows2<T>(H, fd, count, consume, g->stream)
@@ -916,7 +931,6 @@ template <typename T> int alloc_direct(Group* g) {
 template <typename T> int alloc_group(Group* g) {
     if (g->method == SIPF_METHOD_DIRECT) return alloc_direct<T>(g);
     const int n = (int)g->in.size();
-    const int mk = sort_max_keys();
     int rc;
     // H classes in ascending H; FieldDesc slots grouped by class
     std::vector<int> hs;
@@ -950,18 +964,25 @@ template <typename T> int alloc_group(Group* g) {
         return fail(SIPF_EINVAL, "too many particles in one group");
     g->items_cap = (int)cap;
     g->nchunks = (int)chunks.size();
+    int nkeys = 1;
+    for (int i = 0; i < n; ++i)
+        nkeys = std::max(nkeys, pdesc_params<T>(g->in[i].prm, g->in[i].P, g->in[i].H, g->in[i].dim, g->in[i].tile).nkeys);
+    g->kstride = sort_keys(nkeys);
+    const size_t mk = (size_t)g->kstride;
     // first the tables and counters, which one copy fills
     Arena ar;
     ar.want(&g->steps, n * sizeof(uint32_t));
     ar.want(&g->errs, n * sizeof(int));
     ar.want(&g->nitems, 16);
-    ar.want(&g->counts, (size_t)n * mk * sizeof(uint32_t));
+    const bool few = n * mk <= (size_t(1) << 18);  // counts: 1 MiB of the copied tables at most
+    if (few) ar.want(&g->counts, n * mk * sizeof(uint32_t));
     ar.want(&g->pdesc, 2 * n * sizeof(PartDesc<T>));
     ar.want(&g->fdesc, n * sizeof(FieldDesc<T>));
     ar.want(&g->seg_off, n * sizeof(int));
     ar.want(&g->chunks, chunks.size() * sizeof(SortChunk));
     const size_t table_bytes = ar.size;
-    ar.want(&g->cursor, (size_t)n * mk * sizeof(uint32_t));
+    if (!few) ar.want(&g->counts, n * mk * sizeof(uint32_t));
+    ar.want(&g->cursor, n * mk * sizeof(uint32_t));
     ar.want(&g->seg, cap * sizeof(WorkItem));
     ar.want(&g->seg_n, n * sizeof(int));
     ar.want(&g->items, cap * sizeof(WorkItem));
@@ -1000,6 +1021,7 @@ template <typename T> int alloc_group(Group* g) {
     std::memcpy(host(g->seg_off), seg_off.data(), n * sizeof(int));
     std::memcpy(host(g->chunks), chunks.data(), chunks.size() * sizeof(SortChunk));
     HIPCHK(hipMemcpy(g->arena, table.data(), table_bytes, hipMemcpyHostToDevice));
+    if (!few) HIPCHK(launch_fill<float>((float*)g->counts, (int64_t)(n * mk), 0.0f, g->stream));
     if (g->positivity)
         for (const Inst& I : g->in) HIPCHK(hipMemsetAsync(I.pos_sw, 0, I.P * sizeof(uint32_t), g->stream));
     g->pgrid = std::max(1, std::min(g->items_cap, g->dim == 2 ? particle_resident_blocks2<T>(g->scheme, g->win_bytes)
@@ -1159,8 +1181,6 @@ int setup_group(Group* g, int32_t n, const sipf_params* prm, const int64_t* P, c
     g->scheme = prm[0].scheme;
     g->stream = (hipStream_t)hip_stream;
     g->sorted = sorted_pass(&prm[0], n);
-    g->resort = default_resort(&prm[0], g->sorted);
-    for (int i = 1; i < n; ++i) g->resort = std::min(g->resort, default_resort(&prm[i], g->sorted));
     int64_t total_P = 0;
     for (int i = 0; i < n; ++i) total_P += P[i];
     g->chunk = item_chunk(&prm[0], total_P);
@@ -1173,7 +1193,9 @@ int setup_group(Group* g, int32_t n, const sipf_params* prm, const int64_t* P, c
         I.P = P[i];
         I.H = prm[i].H;
         I.dim = dim_of(&prm[i]);
-        I.tile = default_tile(&prm[i], g->sorted);
+        I.tile = default_tile(&prm[i], g->sorted, P[i]);
+        const int resort = default_resort(&prm[i], I.tile, g->sorted);
+        g->resort = i == 0 ? resort : std::min(g->resort, resort);
         if (!is_pow2(I.H)) g->pow2 = false;
     }
     return SIPF_OK;
@@ -1572,7 +1594,7 @@ int adjoint_typed(Group* c, int64_t N, int K, const T* phibar_in, double* loss_o
     if (c->counts_ready) {
         // the last forward step took the tile counts of a sort that the
         // segment sorts below do not consume: clear them
-        HIPCHK(launch_fill<float>((float*)c->counts, (int64_t)sort_max_keys(), 0.0f, c->stream));
+        HIPCHK(launch_fill<float>((float*)c->counts, (int64_t)c->kstride, 0.0f, c->stream));
         c->counts_ready = false;
     }
 
@@ -1627,7 +1649,7 @@ int adjoint_typed(Group* c, int64_t N, int K, const T* phibar_in, double* loss_o
     for (int64_t sgi = nseg - 1; sgi >= 0; --sgi) {
         const int64_t base = sgi * K;
         const int len = (int)std::min<int64_t>(K, N - base);
-        HIPCHK(launch_sort<T>(3, ps_dev + sgi, ps_dev + nseg, c->chunks, c->nchunks, 1, c->counts, c->cursor, c->seg,
+        HIPCHK(launch_sort<T>(3, ps_dev + sgi, ps_dev + nseg, c->chunks, c->nchunks, 1, c->counts, c->cursor, c->kstride, c->seg,
                               c->seg_off, c->seg_n, c->items, c->nitems, c->adj_chunk, c->stream));
         if ((rc = grad_of_tape(base, len))) return rc;
         for (int m = 1; m < len; ++m) {
@@ -1788,8 +1810,8 @@ template <typename T> int deposit_noalloc_typed(const sipf_params* p, int64_t P,
     void* base = nullptr;
     size_t bytes = 0;
     HIPCHK(noalloc_scratch(&base, &bytes));
-    const int H = p->H, tile = default_tile(p, false), chunk = item_chunk(p, P);
-    const int mk = sort_max_keys(), sc = sort_chunk();
+    const int H = p->H, tile = default_tile(p, false, 0), chunk = item_chunk(p, P);
+    const int sc = sort_chunk();
     const int nchunks = (int)((P + sc - 1) / sc);
     const int nt = (H + tile - 1) / tile;
     const int cap = (int)((P + chunk - 1) / chunk) + nt * nt * nt;
@@ -1808,6 +1830,7 @@ template <typename T> int deposit_noalloc_typed(const sipf_params* p, int64_t P,
         d[set].id = (uint32_t*)take(P * sizeof(uint32_t));
         d[set].phi = (T*)phi;
     }
+    const int mk = sort_keys(d[0].nkeys);  // at most 16 tiles per axis: the smaller of the two
     uint32_t* counts = (uint32_t*)take(mk * sizeof(uint32_t));
     uint32_t* cursor = (uint32_t*)take(mk * sizeof(uint32_t));
     PartDesc<T>* pd = (PartDesc<T>*)take(2 * sizeof(PartDesc<T>));
@@ -1827,7 +1850,7 @@ template <typename T> int deposit_noalloc_typed(const sipf_params* p, int64_t P,
     HIPCHK(launch_noalloc_setup<T>(d[0], d[1], pd, chunks, nchunks, sc, seg_off, counts, mk, nitems, err, step, s));
     HIPCHK(launch_fill<T>((T*)phi, (int64_t)H * H * H, (T)0, s));
     HIPCHK(launch_load_positions<T>((const T*)X, P, (T)p->L, d[0], err, s));
-    HIPCHK(launch_sort<T>(3, pd, pd + 1, chunks, nchunks, 1, counts, cursor, seg, seg_off, seg_n, items, nitems, chunk, s));
+    HIPCHK(launch_sort<T>(3, pd, pd + 1, chunks, nchunks, 1, counts, cursor, mk, seg, seg_off, seg_n, items, nitems, chunk, s));
     const int win = particle_window_bytes(sizeof(T) == 8);
     const int grid = std::max(1, std::min(cap, particle_resident_blocks<T>(p->scheme, win, false)));
     HIPCHK(launch_particles<T>(pd + 1, items, nitems, grid, true, false, p->scheme, win, is_pow2(H), false, s));
@@ -2031,9 +2054,11 @@ int sipf_autotune(const sipf_params* prm, int64_t P, const void* X0, int x0_on_d
     if (nsteps < 1) return fail(SIPF_EINVAL, "nsteps must be >= 1");
     if (prm->method == SIPF_METHOD_DIRECT) return fail(SIPF_EINVAL, "the direct SIPF method has nothing to tune");
     sipf_params cur = *prm;
-    cur.tile = default_tile(prm, sorted_pass(prm, 1));
+    // a default of more than 16 tiles per axis stays open (0): it is not a tile that callers can pass
+    const int tile = default_tile(prm, sorted_pass(prm, 1), P);
+    cur.tile = dim_of(prm) == 3 && prm->H / tile > 16 ? 0 : tile;
     cur.chunk = max_chunk(prm, P);
-    cur.resort_every = default_resort(prm, sorted_pass(prm, 1));
+    cur.resort_every = default_resort(prm, tile, sorted_pass(prm, 1));
     double t_best = 0;
     if ((rc = time_config(&cur, P, X0, x0_on_device, nsteps, hip_stream, &t_best))) return rc;
     auto try_axis = [&](int32_t sipf_params::*field, const std::vector<int>& cands) -> int {

@@ -185,11 +185,11 @@ template <typename T>
 // accumulates runs of equal cells (else the two-phase pass; FP64 and the
 // single-phase passes ignore it)
 // kcounts: when not null, the deposit + push pass also counts the pushed
-// particles' sort tiles into these counts (MAX_KEYS per instance, zero on
+// particles' sort tiles into these counts (kstride per instance, zero on
 // entry), so that the next sort can skip its histogram (launch_sort counted)
 hipError_t launch_particles(const PartDesc<T>* pd, const WorkItem* items, int* nitems, int grid, bool deposit,
                             bool push, int scheme, int win_bytes, bool pow2, bool sorted, hipStream_t s,
-                            uint32_t* kcounts = nullptr);
+                            uint32_t* kcounts = nullptr, int kstride = 0);
 // positivity-preserving deposit rounds (positivity.hip): flag nodes below
 // -thresh, switch the order-4 particles touching a flagged node to order 2
 // (count += switched; sw[i] = tag marks them), clamp negatives to zero; tmp
@@ -211,7 +211,7 @@ template <typename T>
 // and sets bit 2 of the instance's error flag (the scatter then writes
 // nothing past the array).
 hipError_t launch_sort(int dim, const PartDesc<T>* src, const PartDesc<T>* dst, const SortChunk* chunks, int nchunks, int ninst,
-                       uint32_t* counts, uint32_t* cursor, WorkItem* seg, const int* seg_off, int* seg_n,
+                       uint32_t* counts, uint32_t* cursor, int kstride, WorkItem* seg, const int* seg_off, int* seg_n,
                        WorkItem* items, int* nitems, int chunk, hipStream_t s, bool counted = false);
 int sort_chunk();
 template <typename T>
@@ -294,7 +294,8 @@ template <typename T> hipError_t launch_dot(const T* u, const T* v, int64_t n, d
 template <typename T> hipError_t launch_axpby(T* y, const T* x, T a, T b, int64_t n, hipStream_t s);
 hipError_t launch_set_u32(uint32_t* p, uint32_t v, hipStream_t s);
 hipError_t launch_zero_f64(double* p, int n, hipStream_t s);
-int sort_max_keys();
+// words of counts and cursors per instance (kstride) for instances of up to nkeys tiles
+int sort_keys(int nkeys);
 // allocation-free deposit (noalloc.hip): this device's static scratch array
 hipError_t noalloc_scratch(void** out, size_t* bytes);
 template <typename T>

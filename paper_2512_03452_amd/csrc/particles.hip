@@ -36,7 +36,10 @@ constexpr int CH = PT * PPT;       // particles per work item at most
 constexpr int SORT_THREADS = SIPF_SORT_THREADS;  // threads per sort workgroup
 constexpr int SORT_PER_THREAD = SIPF_SORT_PER_THREAD;
 constexpr int SORT_CHUNK = SORT_THREADS * SORT_PER_THREAD;
-constexpr int MAX_KEYS = 4096;     // (H / tile)^3 <= 16^3, (H / tile)^2 <= 64^2
+// Sort keys of an instance: up to 16^3 or 64^2 tiles, or up to 32^3 (the 8-cell
+// tiles of H = 256).  A group's counts and cursors hold kstride words per
+// instance, the smaller number when all its instances allow it.
+constexpr int FEW_KEYS = 4096, MANY_KEYS = 32768;
 // Smaller items deposit and gather straight from global memory: 32 atomics and
 // 24 loads per particle against a window's clearing, flush and staging.  At 64
 // instead of 16, us per step: mixed P = 5e4, H = 64, 59.8 against 40.2 (FP64
@@ -55,7 +58,7 @@ constexpr int MIN_WINDOW_ITEM = 16;
 
 int particle_threads() { return PT; }
 int particle_chunk() { return CH; }
-int sort_max_keys() { return MAX_KEYS; }
+int sort_keys(int nkeys) { return nkeys <= FEW_KEYS ? FEW_KEYS : MANY_KEYS; }
 
 // Bit b of v (< 32) moved to bit 3b: three shift-or-mask steps that move
 // groups of bits apart by 8, 4 and 2 places.
@@ -135,7 +138,7 @@ __device__ __forceinline__ uint32_t lane_runs(uint32_t key, int& head) {
 constexpr int TC_SLOTS = 125;
 #define LDS_AS __attribute__((address_space(3)))
 struct TileCount {
-    uint32_t* counts;  // the item's instance's counts (MAX_KEYS words), null when not counting
+    uint32_t* counts;  // the item's instance's counts, null when not counting
     uint32_t* slot;    // LDS, TC_SLOTS words, zero between items
     int* ref;          // LDS, the item's reference tile (3 words)
     __device__ __forceinline__ LDS_AS uint32_t* lslot() const { return (LDS_AS uint32_t*)slot; }
@@ -1124,7 +1127,7 @@ __device__ __forceinline__ bool item_sorted(const PartDesc<float>& a, int64_t be
     return true;
 }
 
-// kcounts: the sort's tile counts of every instance (MAX_KEYS each) when this
+// kcounts: the sort's tile counts of every instance (kstride each) when this
 // step takes them for the next sort (3-D deposit + push passes), else null.
 // COUNT: the instantiation that takes the counts (the other one carries no
 // counting code, so its registers are those of the plain pass).
@@ -1132,7 +1135,7 @@ template <typename T, bool DEP, bool PUSH, int SCHEME, bool P2, bool SORTED, boo
 __device__ __forceinline__ void particles_body(const PartDesc<T>* __restrict__ pds,
                                                const WorkItem* __restrict__ items, int* hdr, int win_bytes,
                                                unsigned char* smem_raw, int4* sh, int* slot_p, uint32_t* kcounts,
-                                               uint32_t* tslot, int* tref) {
+                                               int kstride, uint32_t* tslot, int* tref) {
     const int n = hdr[0];
     if (!COUNT) kcounts = nullptr;
     if (kcounts != nullptr)
@@ -1142,7 +1145,7 @@ __device__ __forceinline__ void particles_body(const PartDesc<T>* __restrict__ p
     for (int it = blockIdx.x; it < n; it = ticket.next()) {
         const WorkItem w = items[it];
         const PartDesc<T>& a = pds[w.inst];
-        const TileCount tc{kcounts != nullptr ? kcounts + (size_t)w.inst * MAX_KEYS : nullptr, tslot, tref};
+        const TileCount tc{kcounts != nullptr ? kcounts + (size_t)w.inst * kstride : nullptr, tslot, tref};
         bool done = false;
         if constexpr (SORTED) done = sorted_candidate(a, w, win_bytes) && item_sorted<SCHEME, P2>(a, w.beg, w.cnt, smem_raw, reinterpret_cast<int*>(sh), tc, ticket);
         if (!done) item_pass<T, DEP, PUSH, SCHEME, P2>(a, w.beg, w.cnt, smem_raw, sh, tc, ticket);
@@ -1155,13 +1158,13 @@ __device__ __forceinline__ void particles_body(const PartDesc<T>* __restrict__ p
 template <typename T, bool DEP, bool PUSH, int SCHEME, bool P2, bool COUNT = false>
 __global__ __launch_bounds__(PT) SIPF_PART_ATTR void k_particles(const PartDesc<T>* __restrict__ pds,
                                                   const WorkItem* __restrict__ items, int* hdr, int win_bytes,
-                                                  uint32_t* kcounts) {
+                                                  uint32_t* kcounts, int kstride) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     __shared__ int4 sh[PT / 64 + 1];
     __shared__ int slot;
     __shared__ uint32_t tslot[TC_SLOTS];
     __shared__ int tref[3];
-    particles_body<T, DEP, PUSH, SCHEME, P2, false, COUNT>(pds, items, hdr, win_bytes, smem_raw, sh, &slot, kcounts,
+    particles_body<T, DEP, PUSH, SCHEME, P2, false, COUNT>(pds, items, hdr, win_bytes, smem_raw, sh, &slot, kcounts, kstride,
                                                            tslot, tref);
 }
 
@@ -1174,14 +1177,14 @@ __global__ __launch_bounds__(PT) SIPF_PART_ATTR void k_particles(const PartDesc<
 template <int SCHEME, bool P2, bool COUNT = false>
 __global__ __launch_bounds__(PT) __attribute__((amdgpu_waves_per_eu(SIPF_TWO_WAVES))) void k_particles_two(
     const PartDesc<float>* __restrict__ pds, const WorkItem* __restrict__ items, int* hdr, int win_bytes,
-    uint32_t* kcounts) {
+    uint32_t* kcounts, int kstride) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     __shared__ int4 sh[PT / 64 + 1];
     __shared__ int slot;
     __shared__ uint32_t tslot[TC_SLOTS];
     __shared__ int tref[3];
     particles_body<float, true, true, SCHEME, P2, false, COUNT>(pds, items, hdr, win_bytes, smem_raw, sh, &slot,
-                                                                kcounts, tslot, tref);
+                                                                kcounts, kstride, tslot, tref);
 }
 
 // The fused deposit + push pass: its two windows (and, in FP32, the sort
@@ -1193,13 +1196,13 @@ __global__ __launch_bounds__(PT) __attribute__((amdgpu_waves_per_eu(SIPF_TWO_WAV
 template <typename T, int SCHEME, bool P2, bool COUNT = false>
 __global__ __launch_bounds__(PT) __attribute__((amdgpu_waves_per_eu(SIPF_FUSED_WAVES))) void k_particles_fused(
     const PartDesc<T>* __restrict__ pds, const WorkItem* __restrict__ items, int* hdr, int win_bytes,
-    uint32_t* kcounts) {
+    uint32_t* kcounts, int kstride) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     __shared__ int4 sh[PT / 64 + 1];
     __shared__ int slot;
     __shared__ uint32_t tslot[TC_SLOTS];
     __shared__ int tref[3];
-    particles_body<T, true, true, SCHEME, P2, true, COUNT>(pds, items, hdr, win_bytes, smem_raw, sh, &slot, kcounts,
+    particles_body<T, true, true, SCHEME, P2, true, COUNT>(pds, items, hdr, win_bytes, smem_raw, sh, &slot, kcounts, kstride,
                                                            tslot, tref);
 }
 
@@ -1241,7 +1244,7 @@ template <typename T> int particle_resident_blocks(int scheme, int win_bytes, bo
 
 template <typename T, bool P2>
 static void particles_p2(const PartDesc<T>* pd, const WorkItem* items, int* nitems, dim3 g, bool deposit,
-                         bool push, int scheme, int win_bytes, bool sorted, uint32_t* kcounts, hipStream_t s) {
+                         bool push, int scheme, int win_bytes, bool sorted, uint32_t* kcounts, int kstride, hipStream_t s) {
     const dim3 b(PT);
     // tile counts are taken only by the deposit + push pass, in its COUNT instantiation
     const bool count = deposit && push && kcounts != nullptr;
@@ -1252,10 +1255,10 @@ static void particles_p2(const PartDesc<T>* pd, const WorkItem* items, int* nite
                 const size_t shm = (size_t)win_bytes;
                 if (count)
                     launch_kernel(strang ? k_particles_two<SIPF_STRANG, P2, true> : k_particles_two<SIPF_EM, P2, true>, g,
-                                  b, shm, s, pd, items, nitems, win_bytes, kcounts);
+                                  b, shm, s, pd, items, nitems, win_bytes, kcounts, kstride);
                 else
                     launch_kernel(strang ? k_particles_two<SIPF_STRANG, P2> : k_particles_two<SIPF_EM, P2>, g, b, shm, s,
-                                  pd, items, nitems, win_bytes, (uint32_t*)nullptr);
+                                  pd, items, nitems, win_bytes, (uint32_t*)nullptr, 0);
                 return;
             }
             // the sorted pass holds both windows and the sort counters at once
@@ -1263,10 +1266,10 @@ static void particles_p2(const PartDesc<T>* pd, const WorkItem* items, int* nite
             const size_t shm = (size_t)win_bytes;
             if (count)
                 launch_kernel(strang ? k_particles_fused<T, SIPF_STRANG, P2, true> : k_particles_fused<T, SIPF_EM, P2, true>,
-                              g, b, shm, s, pd, items, nitems, win_bytes, kcounts);
+                              g, b, shm, s, pd, items, nitems, win_bytes, kcounts, kstride);
             else
                 launch_kernel(strang ? k_particles_fused<T, SIPF_STRANG, P2> : k_particles_fused<T, SIPF_EM, P2>, g, b, shm,
-                              s, pd, items, nitems, win_bytes, (uint32_t*)nullptr);
+                              s, pd, items, nitems, win_bytes, (uint32_t*)nullptr, 0);
             return;
         }
     }
@@ -1276,27 +1279,27 @@ static void particles_p2(const PartDesc<T>* pd, const WorkItem* items, int* nite
             if (count)
                 launch_kernel(strang ? k_particles<T, true, true, SIPF_STRANG, P2, true>
                                      : k_particles<T, true, true, SIPF_EM, P2, true>,
-                              g, b, shm, s, pd, items, nitems, win_bytes, kcounts);
+                              g, b, shm, s, pd, items, nitems, win_bytes, kcounts, kstride);
             else
                 launch_kernel(strang ? k_particles<T, true, true, SIPF_STRANG, P2> : k_particles<T, true, true, SIPF_EM, P2>,
-                              g, b, shm, s, pd, items, nitems, win_bytes, (uint32_t*)nullptr);
+                              g, b, shm, s, pd, items, nitems, win_bytes, (uint32_t*)nullptr, 0);
         }
     } else if (deposit) {
         launch_kernel((k_particles<T, true, false, SIPF_STRANG, P2>), g, b, shm, s, pd, items, nitems, win_bytes,
-                      (uint32_t*)nullptr);
+                      (uint32_t*)nullptr, 0);
     } else if (push) {
         launch_kernel(strang ? k_particles<T, false, true, SIPF_STRANG, P2> : k_particles<T, false, true, SIPF_EM, P2>, g,
-                      b, shm, s, pd, items, nitems, win_bytes, (uint32_t*)nullptr);
+                      b, shm, s, pd, items, nitems, win_bytes, (uint32_t*)nullptr, 0);
     }
 }
 
 template <typename T>
 hipError_t launch_particles(const PartDesc<T>* pd, const WorkItem* items, int* nitems, int grid, bool deposit,
                             bool push, int scheme, int win_bytes, bool pow2, bool sorted, hipStream_t s,
-                            uint32_t* kcounts) {
+                            uint32_t* kcounts, int kstride) {
     if (grid <= 0) return hipSuccess;
-    if (pow2) particles_p2<T, true>(pd, items, nitems, dim3(grid), deposit, push, scheme, win_bytes, sorted, kcounts, s);
-    else particles_p2<T, false>(pd, items, nitems, dim3(grid), deposit, push, scheme, win_bytes, sorted, kcounts, s);
+    if (pow2) particles_p2<T, true>(pd, items, nitems, dim3(grid), deposit, push, scheme, win_bytes, sorted, kcounts, kstride, s);
+    else particles_p2<T, false>(pd, items, nitems, dim3(grid), deposit, push, scheme, win_bytes, sorted, kcounts, kstride, s);
     return hipGetLastError();
 }
 
@@ -1304,16 +1307,16 @@ hipError_t launch_particles(const PartDesc<T>* pd, const WorkItem* items, int* n
 // tile sort: histogram, scan, combine, scatter -- for a group of instances
 //
 // The sort chunk table lists (instance, first particle) for every run of
-// SORT_CHUNK particles of every instance.  Counts and cursors hold MAX_KEYS
+// SORT_CHUNK particles of every instance.  Counts and cursors hold KEYS
 // entries per instance.  The scan writes each instance's work items into its
 // own segment; the combine pass concatenates the segments into one list that
 // the (persistent) particle pass walks.
 // ---------------------------------------------------------------------------
-template <typename T, int DIM>
+template <typename T, int DIM, int KEYS>
 __global__ __launch_bounds__(SORT_THREADS) void k_tile_hist(const PartDesc<T>* __restrict__ pds,
                                                             const SortChunk* __restrict__ chunks,
                                                             uint32_t* counts) {
-    __shared__ uint32_t h[MAX_KEYS];
+    __shared__ uint32_t h[KEYS];
     const SortChunk ch = chunks[blockIdx.x];
     const PartDesc<T> a = pds[ch.inst];
     const int nk = a.nkeys;
@@ -1342,16 +1345,16 @@ __global__ __launch_bounds__(SORT_THREADS) void k_tile_hist(const PartDesc<T>* _
         if (ok && len) atomicAdd(&h[key], len);
     }
     __syncthreads();
-    uint32_t* cnt = counts + (size_t)ch.inst * MAX_KEYS;
+    uint32_t* cnt = counts + (size_t)ch.inst * KEYS;
     for (int i = tid; i < nk; i += SORT_THREADS)
         if (h[i]) atomicAdd(&cnt[i], h[i]);
 }
 
-// Block-wide exclusive scans of NV values per thread (1024 threads = 16
-// waves): inclusive scans inside each wave with lane shuffles, the wave
-// totals through LDS (part: at least 16 NV words), one barrier between.
+// Block-wide exclusive scans of NV values per thread (WAVES waves, 16 by
+// default): inclusive scans inside each wave with lane shuffles, the wave
+// totals through LDS (part: at least WAVES NV words), one barrier between.
 // totals[v] receives the block sum of value v.
-template <int NV>
+template <int NV, int WAVES = 16>
 __device__ __forceinline__ void block_exclusive_scan_n(uint32_t* v, uint32_t* part, uint32_t* totals) {
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     uint32_t inc[NV];
@@ -1368,13 +1371,13 @@ __device__ __forceinline__ void block_exclusive_scan_n(uint32_t* v, uint32_t* pa
     __syncthreads();  // part may still be read by a previous scan
     if (lane == 63)
 #pragma unroll
-        for (int q = 0; q < NV; ++q) part[q * 16 + w] = inc[q];
+        for (int q = 0; q < NV; ++q) part[q * WAVES + w] = inc[q];
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < NV; ++q) {
         uint32_t before = 0, all = 0;
-        for (int k = 0; k < 16; ++k) {
-            const uint32_t t = part[q * 16 + k];
+        for (int k = 0; k < WAVES; ++k) {
+            const uint32_t t = part[q * WAVES + k];
             before += k < w ? t : 0u;
             all += t;
         }
@@ -1399,36 +1402,83 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* p
 // draw items in list order, end on the small ones.  Clears the counts for the
 // next sort.  DIRECT (a single instance): the segment is the item list itself
 // and the scan writes its count, so no combine pass follows.
-template <typename T, bool DIRECT>
-__global__ __launch_bounds__(1024) void k_tile_scan(const PartDesc<T>* __restrict__ pds, uint32_t* counts,
-                                                    uint32_t* cursor, WorkItem* seg, const int* __restrict__ seg_off,
-                                                    int* seg_n, int chunk, int* nitems) {
-    __shared__ uint32_t part[1024];
+//
+// Sparse tiles share an item: eight tiles that form a cube of twice the side
+// (consecutive keys, all with one thread) and hold at most MERGE_ITEM
+// particles together are one item, if such a cube is no wider than a window
+// (tiles of at most MERGE_TILE cells) and more than MERGE_TILES tiles are in
+// use, about what the chip holds at once.  An item of a few particles costs its
+// window's clearing, staging and flush all the same; dense tiles keep items
+// and windows of their own, and a few sparse ones their parallelism (mixed
+// P = 5000, H = 64, 390 tiles in use: 39.8 us per step shared, 32.0 apart).  Us
+// per step without / with: mixed P = 1e6, H = 256 (30 per tile) 1048 / 666;
+// mixed P = 1e5, H = 128, 144 / 95; ring P = 3e5, H = 256, 437 / 415.  Limits
+// of 128 / 256 / 640 / 1536 particles: 790 / 720 / 718 / 743 and, ring P = 3e6,
+// 474 / 474 / 477 / 479.
+constexpr uint32_t MERGE_ITEM = 256;
+constexpr int MERGE_TILE = 8;
+constexpr int MERGE_TILES = 1024;
+// Threads of the scan: eight keys each, or 1024 threads.
+constexpr int scan_threads(int keys) { return keys / 8 < 1024 ? keys / 8 : 1024; }
+template <typename T, int DIM, bool DIRECT, int KEYS>
+__global__ __launch_bounds__(scan_threads(KEYS)) void k_tile_scan(const PartDesc<T>* __restrict__ pds,
+                                                                  uint32_t* counts, uint32_t* cursor, WorkItem* seg,
+                                                                  const int* __restrict__ seg_off, int* seg_n,
+                                                                  int chunk, int* nitems) {
+    constexpr int THREADS = scan_threads(KEYS);
+    __shared__ uint32_t part[3 * THREADS / 64];
     const int inst = blockIdx.x;
     const int nk = pds[inst].nkeys;
-    uint32_t* cnt = counts + (size_t)inst * MAX_KEYS;
-    uint32_t* cur = cursor + (size_t)inst * MAX_KEYS;
+    uint32_t* cnt = counts + (size_t)inst * KEYS;
+    uint32_t* cur = cursor + (size_t)inst * KEYS;
     WorkItem* items = DIRECT ? seg : seg + seg_off[inst];
     const int tid = threadIdx.x;
-    constexpr int PER = MAX_KEYS / 1024;  // keys per thread, consecutive in key order
+    constexpr int PER = KEYS / THREADS;  // keys per thread, consecutive in key order
     const uint32_t half = ((uint32_t)chunk + 1u) / 2u;
-    static_assert(PER == 4, "one 16-byte load of counts per thread");
-    uint32_t loc[PER], nit[PER];
+    uint32_t loc[PER], own[PER];  // particles of each key, and of the items that start at it
     uint32_t sum = 0, ibig = 0, ismall = 0;
-    // the instance's MAX_KEYS counts are 16-byte aligned: one load per thread
-    const uint4 c4 = reinterpret_cast<const uint4*>(cnt)[tid];
-    const uint32_t cv[4] = {c4.x, c4.y, c4.z, c4.w};
+    // the instance's counts are 16-byte aligned: loads of four
+#pragma unroll
+    for (int q = 0; q < PER / 4; ++q) {
+        const uint4 c4 = reinterpret_cast<const uint4*>(cnt)[tid * (PER / 4) + q];
+        loc[4 * q] = c4.x;
+        loc[4 * q + 1] = c4.y;
+        loc[4 * q + 2] = c4.z;
+        loc[4 * q + 3] = c4.w;
+    }
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
         const int i = tid * PER + j;
-        loc[j] = i < nk ? cv[j] : 0u;
-        nit[j] = (loc[j] + chunk - 1) / chunk;
+        loc[j] = i < nk ? loc[j] : 0u;
+        own[j] = loc[j];
         sum += loc[j];
-        if (loc[j] >= half) ibig += nit[j];
-        else if (loc[j] > 0) ismall += 1u;
+    }
+    if (DIM == 3 && nk > MERGE_TILES && pds[inst].tile <= MERGE_TILE) {
+        uint32_t used = 0, tiles;
+#pragma unroll
+        for (int j = 0; j < PER; ++j) used += loc[j] > 0 ? 1u : 0u;
+        block_exclusive_scan_n<1, THREADS / 64>(&used, part, &tiles);
+        if (tiles > (uint32_t)MERGE_TILES) {
+#pragma unroll
+            for (int q = 0; q < PER; q += 8) {
+                uint32_t all = 0;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) all += loc[q + j];
+                if (all > min(MERGE_ITEM, (uint32_t)chunk)) continue;
+                own[q] = all;
+#pragma unroll
+                for (int j = 1; j < 8; ++j) own[q + j] = 0;
+            }
+        }
+    }
+    auto items_of = [&](uint32_t c) { return c <= (uint32_t)chunk ? 1u : (c + chunk - 1) / chunk; };
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        if (own[j] >= half) ibig += items_of(own[j]);
+        else if (own[j] > 0) ismall += 1u;
     }
     uint32_t sc[3] = {sum, ibig, ismall}, tot[3];
-    block_exclusive_scan_n<3>(sc, part, tot);
+    block_exclusive_scan_n<3, THREADS / 64>(sc, part, tot);
     if (tot[0] != (uint32_t)pds[inst].P) {
         // the counts do not add up to the particle count: list no work items
         // (the scatter drops what would land outside the array) and flag it
@@ -1452,30 +1502,35 @@ __global__ __launch_bounds__(1024) void k_tile_scan(const PartDesc<T>* __restric
     uint32_t rsmall = tbig + sc[2];
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
-        const int i = tid * PER + j;
-        if (i < nk) {
-            cur[i] = run;
-            cnt[i] = 0u;
-            if (nit[j] > 0) {
-                // nit items: the first rem of base + 1 particles, the rest of base
-                const uint32_t base = loc[j] / nit[j], rem = loc[j] - base * nit[j];
-                const bool big = loc[j] >= half;
-                const uint32_t at = big ? rbig : rsmall;
-                uint32_t b = run;
-                for (uint32_t k = 0; k < nit[j]; ++k) {
-                    const uint32_t c = base + (k < rem ? 1u : 0u);
-                    WorkItem w;
-                    w.beg = (int64_t)b;
-                    w.cnt = (int32_t)c;
-                    w.inst = inst;
-                    items[at + k] = w;
-                    b += c;
-                }
-                if (big) rbig += nit[j];
-                else rsmall += 1u;
+        if (own[j] > 0) {
+            // nit items: the first rem of base + 1 particles, the rest of base
+            const uint32_t nit = items_of(own[j]);
+            const uint32_t base = nit == 1u ? own[j] : own[j] / nit, rem = own[j] - base * nit;
+            const bool big = own[j] >= half;
+            const uint32_t at = big ? rbig : rsmall;
+            uint32_t b = run;
+            for (uint32_t k = 0; k < nit; ++k) {
+                const uint32_t c = base + (k < rem ? 1u : 0u);
+                WorkItem w;
+                w.beg = (int64_t)b;
+                w.cnt = (int32_t)c;
+                w.inst = inst;
+                items[at + k] = w;
+                b += c;
             }
+            if (big) rbig += nit;
+            else rsmall += 1u;
         }
-        run += loc[j];
+        const uint32_t n = loc[j];
+        loc[j] = run;
+        run += n;
+    }
+    // starts and zero counts, four a store (keys from nk on have no readers)
+#pragma unroll
+    for (int q = 0; q < PER / 4; ++q) {
+        const int i = tid * (PER / 4) + q;
+        reinterpret_cast<uint4*>(cur)[i] = make_uint4(loc[4 * q], loc[4 * q + 1], loc[4 * q + 2], loc[4 * q + 3]);
+        reinterpret_cast<uint4*>(cnt)[i] = make_uint4(0u, 0u, 0u, 0u);
     }
     if (tid == 0) {
         seg_n[inst] = (int)(tbig + tsmall);
@@ -1514,17 +1569,17 @@ __global__ __launch_bounds__(1024) void k_items_combine(const WorkItem* __restri
     if (tid == 0) *nitems = (int)total;
 }
 
-template <typename T, int DIM>
+template <typename T, int DIM, int KEYS>
 __global__ __launch_bounds__(SORT_THREADS) void k_tile_scatter(const PartDesc<T>* __restrict__ src,
                                                                const PartDesc<T>* __restrict__ dst,
                                                                const SortChunk* __restrict__ chunks,
                                                                uint32_t* cursor) {
-    __shared__ uint32_t lc[MAX_KEYS];  // counts of the chunk's keys, then their first slots
+    __shared__ uint32_t lc[KEYS];  // counts of the chunk's keys, then their first slots
     const SortChunk ch = chunks[blockIdx.x];
     const PartDesc<T> a = src[ch.inst];
     const PartDesc<T> b = dst[ch.inst];
     const int nk = a.nkeys;
-    uint32_t* cur = cursor + (size_t)ch.inst * MAX_KEYS;
+    uint32_t* cur = cursor + (size_t)ch.inst * KEYS;
     const int tid = threadIdx.x;
     T px[SORT_PER_THREAD], py[SORT_PER_THREAD], pz[SORT_PER_THREAD];
     uint32_t pid[SORT_PER_THREAD], key[SORT_PER_THREAD], rank[SORT_PER_THREAD];
@@ -1575,28 +1630,34 @@ __global__ __launch_bounds__(SORT_THREADS) void k_tile_scatter(const PartDesc<T>
 
 int sort_chunk() { return SORT_CHUNK; }
 
-template <typename T>
-hipError_t launch_sort(int dim, const PartDesc<T>* src, const PartDesc<T>* dst, const SortChunk* chunks, int nchunks,
-                       int ninst, uint32_t* counts, uint32_t* cursor, WorkItem* seg, const int* seg_off, int* seg_n,
-                       WorkItem* items, int* nitems, int chunk, hipStream_t s, bool counted) {
-    if (chunk <= 0 || chunk > CH) chunk = CH;
-    if (ninst < 1 || ninst > 1024 || (dim != 2 && dim != 3)) return hipErrorInvalidValue;
-    if (!counted) {
-        if (dim == 3) launch_kernel((k_tile_hist<T, 3>), dim3(nchunks), dim3(SORT_THREADS), 0, s, src, chunks, counts);
-        else launch_kernel((k_tile_hist<T, 2>), dim3(nchunks), dim3(SORT_THREADS), 0, s, src, chunks, counts);
-    }
+template <typename T, int DIM, int KEYS>
+static void sort_keys_launch(const PartDesc<T>* src, const PartDesc<T>* dst, const SortChunk* chunks, int nchunks,
+                             int ninst, uint32_t* counts, uint32_t* cursor, WorkItem* seg, const int* seg_off,
+                             int* seg_n, WorkItem* items, int* nitems, int chunk, hipStream_t s, bool counted) {
+    const dim3 b(SORT_THREADS);
+    if (!counted) launch_kernel((k_tile_hist<T, DIM, KEYS>), dim3(nchunks), b, 0, s, src, chunks, counts);
     if (ninst == 1) {
-        launch_kernel((k_tile_scan<T, true>), dim3(1), dim3(1024), 0, s, src, counts, cursor, items, seg_off, seg_n,
-                      chunk, nitems);
+        launch_kernel((k_tile_scan<T, DIM, true, KEYS>), dim3(1), dim3(scan_threads(KEYS)), 0, s, src, counts, cursor, items, seg_off,
+                      seg_n, chunk, nitems);
     } else {
-        launch_kernel((k_tile_scan<T, false>), dim3(ninst), dim3(1024), 0, s, src, counts, cursor, seg, seg_off,
+        launch_kernel((k_tile_scan<T, DIM, false, KEYS>), dim3(ninst), dim3(scan_threads(KEYS)), 0, s, src, counts, cursor, seg, seg_off,
                       seg_n, chunk, nitems);
         launch_kernel(k_items_combine, dim3(1), dim3(1024), 0, s, seg, seg_off, seg_n, ninst, items, nitems);
     }
-    if (dim == 3)
-        launch_kernel((k_tile_scatter<T, 3>), dim3(nchunks), dim3(SORT_THREADS), 0, s, src, dst, chunks, cursor);
-    else
-        launch_kernel((k_tile_scatter<T, 2>), dim3(nchunks), dim3(SORT_THREADS), 0, s, src, dst, chunks, cursor);
+    launch_kernel((k_tile_scatter<T, DIM, KEYS>), dim3(nchunks), b, 0, s, src, dst, chunks, cursor);
+}
+
+template <typename T>
+hipError_t launch_sort(int dim, const PartDesc<T>* src, const PartDesc<T>* dst, const SortChunk* chunks, int nchunks,
+                       int ninst, uint32_t* counts, uint32_t* cursor, int kstride, WorkItem* seg, const int* seg_off,
+                       int* seg_n, WorkItem* items, int* nitems, int chunk, hipStream_t s, bool counted) {
+    if (chunk <= 0 || chunk > CH) chunk = CH;
+    if (ninst < 1 || ninst > 1024 || (dim != 2 && dim != 3)) return hipErrorInvalidValue;
+    auto run = dim == 2 ? sort_keys_launch<T, 2, FEW_KEYS> : sort_keys_launch<T, 3, FEW_KEYS>;
+    if constexpr (sizeof(T) == 4)  // H = 256 is FP32 only
+        if (dim == 3 && kstride == MANY_KEYS) run = sort_keys_launch<T, 3, MANY_KEYS>;
+    if (kstride != FEW_KEYS && !(sizeof(T) == 4 && dim == 3 && kstride == MANY_KEYS)) return hipErrorInvalidValue;
+    run(src, dst, chunks, nchunks, ninst, counts, cursor, seg, seg_off, seg_n, items, nitems, chunk, s, counted);
     return hipGetLastError();
 }
 
@@ -1705,10 +1766,10 @@ hipError_t launch_philox_dbg(uint64_t seed, int64_t n, const uint32_t* ctr, uint
 #define SIPF_INST(T)                                                                                              \
     template int particle_resident_blocks<T>(int, int, bool);                                                     \
     template hipError_t launch_particles<T>(const PartDesc<T>*, const WorkItem*, int*, int, bool, bool, int, \
-                                            int, bool, bool, hipStream_t, uint32_t*);                             \
+                                            int, bool, bool, hipStream_t, uint32_t*, int);                        \
     template hipError_t launch_sort<T>(int, const PartDesc<T>*, const PartDesc<T>*, const SortChunk*, int, int,   \
-                                       uint32_t*, uint32_t*, WorkItem*, const int*, int*, WorkItem*, int*, int,    \
-                                       hipStream_t, bool);                                                         \
+                                       uint32_t*, uint32_t*, int, WorkItem*, const int*, int*, WorkItem*, int*,    \
+                                       int, hipStream_t, bool);                                                         \
     template hipError_t launch_load_positions<T>(const T*, int64_t, T, PartDesc<T>, int*, hipStream_t);          \
     template hipError_t launch_unsort<T>(const PartDesc<T>*, T*, hipStream_t);                                    \
     template hipError_t launch_fill<T>(T*, int64_t, T, hipStream_t);                                              \
