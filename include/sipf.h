@@ -182,7 +182,7 @@ typedef struct sipf_params {
     int32_t  chunk;        /* max particles per work item of the particle pass (256..4096); 0 = default:
                               4096 in 2-D and from 2^23 particles per 3-D group, else 3072.  3-D groups
                               of P particles take items of about P/192 (at least 256) where that is
-                              smaller; the adjoint's reverse pass by default at most 2048 */
+                              smaller; the adjoint's reverse pass takes at most 4096 by default */
     uint64_t seed;         /* Philox key                                          */
     uint32_t instance;     /* fourth Philox counter word                          */
     uint32_t dim;          /* space dimension: 3 (0 means 3) or 2                 */

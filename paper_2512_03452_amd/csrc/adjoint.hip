@@ -18,88 +18,94 @@
 
 namespace sipf {
 
-// sum over the 32 nodes of Gamma_4 of phibar[node] * dF/dlambda (eq. 4ord)
-// Nodes are read from P at ((i - ox) mod H, (j - oy) mod H, (k - oz) mod H) with
-// row strides (Wy, Wz): the whole grid for o = 0, W = H, or a window of it.
-template <typename T>
-__device__ __forceinline__ void deposit_grad(const T* __restrict__ phibar, T x, T y, T z, T hl, int H, T& gx_, T& gy_,
-                                             T& gz_, int ox = 0, int oy = 0, int oz = 0, int Wy = 0, int Wz = 0) {
-    const int Hm = H - 1;
-    if (Wy == 0) {
-        Wy = H;
-        Wz = H;
+// Four nodes p[u][v] of a square with trilinear weights (1 - lu, lu) x (1 - lv, lv):
+// the interpolated value and its derivatives by lu and lv.
+template <typename T> struct Quad {
+    T q, u, v;
+    __device__ __forceinline__ Quad(T p00, T p01, T p10, T p11, T lu, T lv) {
+        const T d0 = p01 - p00, d1 = p11 - p10;
+        const T r0 = p00 + lv * d0, r1 = p10 + lv * d1;
+        u = r1 - r0;
+        q = r0 + lu * u;
+        v = d0 + lu * (d1 - d0);
     }
-    const T s[3] = {x * hl, y * hl, z * hl};
-    int g[3];
-    T F[3][4], D[3][4], dS[3], S = (T)1;
+};
+
+// sum over the 32 nodes of Gamma_4 of phibar[node] * dF/dlambda (eq. 4ord), as
+// a contraction along one axis after the other: node(i, j, k) is the value at
+// cell offsets (i - 1, j - 1, k - 1), l the position in the cell.
+template <typename T, typename Node>
+__device__ __forceinline__ void deposit_grad(Node node, const T* l, T& ax, T& ay, T& az) {
+    T F[3][2], D[3][2], dS[3], S = (T)1;  // weights of the outer nodes 0 and 3 and their derivatives
+#pragma unroll
     for (int a = 0; a < 3; ++a) {
-        const T f = floor(s[a]);
-        g[a] = (int)f;
-        const T l = s[a] - f;
-        const T om = (T)1 - l;
-        const T lo = l * om;
-        F[a][0] = -((T)2 - l) * lo * (T)(1.0 / 6.0);
-        F[a][1] = om;
-        F[a][2] = l;
-        F[a][3] = -((T)1 + l) * lo * (T)(1.0 / 6.0);
-        D[a][0] = -((T)2 - (T)6 * l + (T)3 * l * l) * (T)(1.0 / 6.0);
-        D[a][1] = (T)-1;
-        D[a][2] = (T)1;
-        D[a][3] = -((T)1 - (T)3 * l * l) * (T)(1.0 / 6.0);
+        const T om = (T)1 - l[a], lo = l[a] * om;
+        F[a][0] = -((T)2 - l[a]) * lo * (T)(1.0 / 6.0);
+        F[a][1] = -((T)1 + l[a]) * lo * (T)(1.0 / 6.0);
+        D[a][0] = -((T)2 - (T)6 * l[a] + (T)3 * l[a] * l[a]) * (T)(1.0 / 6.0);
+        D[a][1] = -((T)1 - (T)3 * l[a] * l[a]) * (T)(1.0 / 6.0);
         S += lo * (T)0.5;
-        dS[a] = ((T)1 - (T)2 * l) * (T)0.5;
+        dS[a] = ((T)1 - (T)2 * l[a]) * (T)0.5;
     }
-    auto node = [&](int i, int j, int k) -> T {
-        const int ix = (g[0] - 1 + i - ox) & Hm, iy = (g[1] - 1 + j - oy) & Hm, iz = (g[2] - 1 + k - oz) & Hm;
-        return phibar[((size_t)ix * Wy + iy) * Wz + iz];
-    };
-    T ax = 0, ay = 0, az = 0;
-    // inner nodes: F = X Y Z S
-    for (int i = 1; i <= 2; ++i)
-        for (int j = 1; j <= 2; ++j)
-            for (int k = 1; k <= 2; ++k) {
-                const T p = node(i, j, k);
-                const T xyz = F[0][i] * F[1][j] * F[2][k];
-                ax += p * (D[0][i] * F[1][j] * F[2][k] * S + xyz * dS[0]);
-                ay += p * (F[0][i] * D[1][j] * F[2][k] * S + xyz * dS[1]);
-                az += p * (F[0][i] * F[1][j] * D[2][k] * S + xyz * dS[2]);
-            }
+    {  // inner nodes: F = X Y Z S
+        const Quad<T> a(node(1, 1, 1), node(1, 1, 2), node(1, 2, 1), node(1, 2, 2), l[1], l[2]);
+        const Quad<T> b(node(2, 1, 1), node(2, 1, 2), node(2, 2, 1), node(2, 2, 2), l[1], l[2]);
+        const T dx = b.q - a.q, v = a.q + l[0] * dx;
+        ax = dx * S + v * dS[0];
+        ay = (a.u + l[0] * (b.u - a.u)) * S + v * dS[1];
+        az = (a.v + l[0] * (b.v - a.v)) * S + v * dS[2];
+    }
     // outer nodes: F = X Y Z with one index in {0, 3}
+#pragma unroll
     for (int o = 0; o < 2; ++o) {
         const int e = o ? 3 : 0;
-        for (int u = 1; u <= 2; ++u)
-            for (int v = 1; v <= 2; ++v) {
-                {  // outer on x: (e, u, v)
-                    const T p = node(e, u, v);
-                    ax += p * D[0][e] * F[1][u] * F[2][v];
-                    ay += p * F[0][e] * D[1][u] * F[2][v];
-                    az += p * F[0][e] * F[1][u] * D[2][v];
-                }
-                {  // outer on y: (u, e, v)
-                    const T p = node(u, e, v);
-                    ax += p * D[0][u] * F[1][e] * F[2][v];
-                    ay += p * F[0][u] * D[1][e] * F[2][v];
-                    az += p * F[0][u] * F[1][e] * D[2][v];
-                }
-                {  // outer on z: (u, v, e)
-                    const T p = node(u, v, e);
-                    ax += p * D[0][u] * F[1][v] * F[2][e];
-                    ay += p * F[0][u] * D[1][v] * F[2][e];
-                    az += p * F[0][u] * F[1][v] * D[2][e];
-                }
-            }
+        const Quad<T> x(node(e, 1, 1), node(e, 1, 2), node(e, 2, 1), node(e, 2, 2), l[1], l[2]);
+        ax += D[0][o] * x.q;
+        ay += F[0][o] * x.u;
+        az += F[0][o] * x.v;
+        const Quad<T> y(node(1, e, 1), node(1, e, 2), node(2, e, 1), node(2, e, 2), l[0], l[2]);
+        ax += F[1][o] * y.u;
+        ay += D[1][o] * y.q;
+        az += F[1][o] * y.v;
+        const Quad<T> z(node(1, 1, e), node(1, 2, e), node(2, 1, e), node(2, 2, e), l[0], l[1]);
+        ax += F[2][o] * z.u;
+        ay += F[2][o] * z.v;
+        az += D[2][o] * z.q;
     }
-    gx_ = ax;
-    gy_ = ay;
-    gz_ = az;
+}
+
+// The same from the whole grid of H^3 nodes (a power of two), around cell g.
+template <typename T>
+__device__ __forceinline__ void deposit_grad_grid(const T* __restrict__ phibar, int H, const int* g, const T* l, T& ax,
+                                                  T& ay, T& az) {
+    const int Hm = H - 1;
+    const auto p = gp(phibar);
+    deposit_grad(
+        [&](int i, int j, int k) -> T {
+            const int ix = (g[0] - 1 + i) & Hm, iy = (g[1] - 1 + j) & Hm, iz = (g[2] - 1 + k) & Hm;
+            return p[((size_t)ix * H + iy) * H + iz];
+        },
+        l, ax, ay, az);
+}
+
+template <typename T> __device__ __forceinline__ void cell_of(const T* X, T hl, int* g, T* l) {
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const T s = X[d] * hl, f = floor(s);
+        g[d] = (int)f;
+        l[d] = s - f;
+    }
 }
 
 template <typename T>
 __global__ __launch_bounds__(256) void k_adj_seed(AdjDesc<T> a) {
     const T c = a.wmass * a.hl;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.P; i += (int64_t)gridDim.x * blockDim.x) {
-        T gx, gy, gz;
-        deposit_grad(a.phibar, a.x[i], a.y[i], a.z[i], a.hl, a.H, gx, gy, gz);
+        const T X[3] = {a.x[i], a.y[i], a.z[i]};
+        T gx, gy, gz, l[3];
+        int g[3];
+        cell_of(X, a.hl, g, l);
+        deposit_grad_grid(a.phibar, a.H, g, l, gx, gy, gz);
         const size_t p = a.id[i];
         a.xbar[3 * p] = c * gx;
         a.xbar[3 * p + 1] = c * gy;
@@ -121,32 +127,36 @@ __device__ __forceinline__ double block_sum(double v, double* sh) {
 
 // ---------------------------------------------------------------------------
 // Reverse particle pass over the work items of a tile sort (one item = up to
-// AdjShape<T>::PT x PPT particles of one tile, consecutive in the segment's order).  Per item,
-// the cells of X bound a window of the grid that covers the trilinear stencil
-// at Y = X + W^- (margin gmargin):
-//   G window     the gradient grids, staged once from HBM (gather of v, J);
+// AdjShape<T>::PT x PPT particles of one tile, consecutive in the segment's
+// order).  Per item, windows of the grid around the cells of X:
+//   G window     the gradient grids, staged once from HBM (gather of v, J at
+//                Y = X + W^-);
 //   Gbar window  fixed-point accumulators of the transpose of the gather,
 //                added to the grid once per item instead of once per particle;
-//   phibar window the deposit cotangent.
-// A particle whose Y cell leaves the window, or an item whose window does not
-// fit, goes straight to HBM (gathers, float atomics).  The transpose of the
-// deposit at X gathers the deposit cotangent from a third window (order-4
-// stencil around the cells of X).
+//   phibar window the deposit cotangent, for the transpose of the deposit at X.
+// Windows have fixed strides and at most as many cells as these allow: where
+// the item's box is wider (particles drift out of their tile over a segment),
+// the window keeps to the item's middle and the few particles outside go
+// straight to HBM (gathers, float atomics).
 // ---------------------------------------------------------------------------
-// Launch shape per precision: threads per workgroup and particles per thread
-// (an item holds up to PT x PPT particles).  The pass needs ~166 VGPRs: one
-// 768-thread workgroup is three waves per SIMD (measured FP32 forward +
-// adjoint 37.6 against 38.7 ms with 512 threads); FP64 at 768 threads would
-// spill, so it keeps 512 (two waves per SIMD).
+// Launch shape per precision: threads per workgroup, particles per thread (an
+// item holds up to PT x PPT particles), waves per SIMD that the registers are
+// budgeted for, nodes per axis of the gradient windows (G) and of the phibar
+// window (D).
+//
+// What bounds the pass: the windows' staging and their float atomics into the
+// grid once per item, LDS atomics (24 per particle) and latency; its 124 bytes
+// per FP64 particle alone would take 52 us at P = 2e6.  Contracting along one
+// axis after the other and one gradient component at a time keeps the
+// registers at 108 (FP32) and 155 (FP64) without spills, where all 24 node
+// values at once took 168 and 256 with spills: two 512-thread workgroups per CU
+// in FP32, one of 768 in FP64 (1024 threads spill, 168 us; two of 512 with
+// windows of 11 nodes 216, since the particles drift about a cell over a
+// segment; 768 160).  Adjoint workload (P = 2e6, H = 64, segments of ten
+// steps), us per launch: FP64 277 -> 160, FP32 161 -> 83.
 template <typename T> struct AdjShape;
-template <> struct AdjShape<float> { static constexpr int PT = 768, PPT = 6; };
-template <> struct AdjShape<double> { static constexpr int PT = 512, PPT = 8; };
-#ifndef ADJ_UNROLL
-#define ADJ_UNROLL 1
-#endif
-#ifndef ADJ_BATCH
-#define ADJ_BATCH 4
-#endif
+template <> struct AdjShape<float> { static constexpr int PT = 512, PPT = 8, WAVES = 4, G = 13, D = 15; };
+template <> struct AdjShape<double> { static constexpr int PT = 768, PPT = 6, WAVES = 3, G = 14, D = 13; };
 
 // Gbar accumulator: a term t (already scaled by 2^S) is added as round(t); S is
 // chosen per item so that every node sum stays below 2^E in magnitude.
@@ -164,29 +174,39 @@ template <> struct AdjFixed<double> {
     __device__ static U q(double t) { return (U)Magic<double>::take(t + Magic<double>::M); }
 };
 
-int adj_window_bytes(bool fp64) { return fp64 ? 150 * 1024 : 76 * 1024; }
+template <typename T> constexpr int adj_lds_bytes() {
+    using A = AdjShape<T>;
+    return 3 * A::G * A::G * A::G * (int)(sizeof(typename AdjFixed<T>::I) + sizeof(T)) + A::D * A::D * A::D * (int)sizeof(T);
+}
+
+// Window along one axis, in cells relative to the item's reference cell: n
+// cells from o for cells that span [lo, hi], wanted with m cells of margin on
+// both sides, at most `most` of them, around `mean` if they find no room.
+__device__ __forceinline__ void adj_axis(int lo, int hi, int m, int mean, int most, int H, int& o, int& n) {
+    const int nb = hi - lo + 1;
+    n = min(min(nb + 2 * m, most), H);
+    o = lo - (n - nb) / 2;
+    if (nb > n) o = max(lo, min(hi - n + 1, mean - n / 2));
+}
 
 template <typename T, int SCHEME>
-__device__ __forceinline__ void adj_item(const AdjDesc<T>& a, int64_t beg, int cnt, unsigned char* lds, int lds_bytes,
-                                         int* sh, double& chib, double& sb) {
+__device__ __forceinline__ void adj_item(const AdjDesc<T>& a, int64_t beg, int cnt, unsigned char* lds, int4* sh,
+                                         const Ticket& ticket, double& chib, double& sb) {
     using I = typename AdjFixed<T>::I;
     using U = typename AdjFixed<T>::U;
-    constexpr int APT = AdjShape<T>::PT, APPT = AdjShape<T>::PPT;
+    constexpr int APT = AdjShape<T>::PT, APPT = AdjShape<T>::PPT, NW = APT / 64;
+    constexpr int G = AdjShape<T>::G, G2 = G * G, G3 = G2 * G, D = AdjShape<T>::D, D2 = D * D;
     const int tid = threadIdx.x;
     const int H = a.H, Hm = H - 1, Hh = H / 2;
     const T hl = a.hl;
     const size_t H3 = (size_t)H * H * H;
     // the load phase keeps the particles only long enough for the bounding box
     // and the cotangent bound; the main loop re-reads each one from L2
-    if (tid < 3) sh[tid] = INT_MAX;
-    else if (tid < 6) sh[tid] = INT_MIN;
-    else if (tid == 6) sh[6] = 0;
-    __syncthreads();
     const int rx = ifloor(a.x[beg] * hl) & Hm, ry = ifloor(a.y[beg] * hl) & Hm, rz = ifloor(a.z[beg] * hl) & Hm;
-    int mnx = INT_MAX, mny = INT_MAX, mnz = INT_MAX, mxx = INT_MIN, mxy = INT_MIN, mxz = INT_MIN;
+    int bx = BOUNDS_NONE, by = BOUNDS_NONE, bz = BOUNDS_NONE, sx = 0, sy = 0, sz = 0;
     float bmax = 0.f;
-    // in batches of ADJ_BATCH particles per thread, to bound the registers held
-    constexpr int NB = APPT < ADJ_BATCH ? APPT : ADJ_BATCH;
+    // in batches of four particles per thread, to bound the registers held
+    constexpr int NB = APPT < 4 ? APPT : 4;
 #pragma unroll
     for (int k0 = 0; k0 < APPT; k0 += NB) {
         T px[NB], py[NB], pz[NB], qx[NB], qy[NB], qz[NB];
@@ -208,9 +228,12 @@ __device__ __forceinline__ void adj_item(const AdjDesc<T>& a, int64_t beg, int c
                 const int cx = (((ifloor(px[kk] * hl) & Hm) - rx + Hh) & Hm) - Hh;
                 const int cy = (((ifloor(py[kk] * hl) & Hm) - ry + Hh) & Hm) - Hh;
                 const int cz = (((ifloor(pz[kk] * hl) & Hm) - rz + Hh) & Hm) - Hh;
-                mnx = min(mnx, cx); mxx = max(mxx, cx);
-                mny = min(mny, cy); mxy = max(mxy, cy);
-                mnz = min(mnz, cz); mxz = max(mxz, cz);
+                bx = pk_min(bx, pk_bounds(cx));
+                by = pk_min(by, pk_bounds(cy));
+                bz = pk_min(bz, pk_bounds(cz));
+                sx += cx;
+                sy += cy;
+                sz += cz;
                 // |x| rounded up to float (values beyond float range give +inf)
                 const float m3 =
                     (float)fmax(fmax(fabs((double)qx[kk]), fabs((double)qy[kk])), fabs((double)qz[kk]));
@@ -218,65 +241,69 @@ __device__ __forceinline__ void adj_item(const AdjDesc<T>& a, int64_t beg, int c
             }
         }
     }
-    mnx = wave_min(mnx); mny = wave_min(mny); mnz = wave_min(mnz);
-    mxx = wave_max(mxx); mxy = wave_max(mxy); mxz = wave_max(mxz);
-    int bm = __float_as_int(bmax);  // non-negative floats order like their bit patterns
-    bm = wave_max(bm);
-    if ((tid & 63) == 0) {
-        atomicMin(&sh[0], mnx); atomicMin(&sh[1], mny); atomicMin(&sh[2], mnz);
-        atomicMax(&sh[3], mxx); atomicMax(&sh[4], mxy); atomicMax(&sh[5], mxz);
-        atomicMax(&sh[6], bm);
+    // non-negative floats order like their bit patterns
+    const int bm = block_bounds3_max<NW>(bx, by, bz, __float_as_int(bmax), sh);
+    ticket.draw();
+    const double bound = (double)cnt * (double)a.chitau * (double)__int_as_float(bm);
+    const bool gwin = bound < 1e300;
+    int mx = 0, my = 0, mz = 0;
+    if (max(max(pk_hi(bx) - pk_lo(bx), pk_hi(by) - pk_lo(by)), pk_hi(bz) - pk_lo(bz)) >= min(G - 1, D - 3)) {
+        // a box wider than a window: the item's mean cell
+        __syncthreads();  // the bounds have been read
+        int* sum = reinterpret_cast<int*>(sh);
+        if (tid < 3) sum[tid] = 0;
+        __syncthreads();
+        atomicAdd(sum, sx);
+        atomicAdd(sum + 1, sy);
+        atomicAdd(sum + 2, sz);
+        __syncthreads();
+        mx = sum[0] / cnt;
+        my = sum[1] / cnt;
+        mz = sum[2] / cnt;
     }
-    __syncthreads();
-
-    // window geometry (uniform across the workgroup)
-    const double bound = (double)cnt * (double)a.chitau * (double)__int_as_float(sh[6]);
-    int gox = 0, goy = 0, goz = 0, gWx = H, gWy = H, gWz = H;
-    bool gwin = false;
-    if (bound < 1e300) {
-        for (int m = a.gmargin; m >= 0 && !gwin; --m) {
-            axis_window(rx, sh[0] - m, sh[3] + 1 + m, H, gox, gWx);
-            axis_window(ry, sh[1] - m, sh[4] + 1 + m, H, goy, gWy);
-            axis_window(rz, sh[2] - m, sh[5] + 1 + m, H, goz, gWz);
-            gwin = 3 * (int64_t)gWx * gWy * gWz * (int64_t)(sizeof(I) + sizeof(T)) <= lds_bytes;
-        }
-    }
-    const int gn = gwin ? gWx * gWy * gWz : 0;
+    // gradient windows (first cell, cells), Gbar then G in LDS; nodes = cells + 1
+    int gox, goy, goz, gnx, gny, gnz;
+    adj_axis(pk_lo(bx), pk_hi(bx), a.gmargin, mx, G - 1, H, gox, gnx);
+    adj_axis(pk_lo(by), pk_hi(by), a.gmargin, my, G - 1, H, goy, gny);
+    adj_axis(pk_lo(bz), pk_hi(bz), a.gmargin, mz, G - 1, H, goz, gnz);
+    gox = (gox + rx) & Hm;
+    goy = (goy + ry) & Hm;
+    goz = (goz + rz) & Hm;
     I* Gb = reinterpret_cast<I*>(lds);
-    T* Gw = reinterpret_cast<T*>(lds + (size_t)3 * gn * sizeof(I));
-    // deposit-cotangent window: the order-4 stencil (-1 .. +2) around the cells of X
-    const size_t used = (size_t)3 * gn * (sizeof(I) + sizeof(T));
-    int dox = 0, doy = 0, doz = 0, dWx = H, dWy = H, dWz = H;
-    bool dwin = false;
+    T* Gw = reinterpret_cast<T*>(lds + (size_t)3 * G3 * sizeof(I));
+    // deposit-cotangent window: cells of X, order-4 stencil (-1 .. +2) around them
+    int dox = 0, doy = 0, doz = 0, dnx = 0, dny = 0, dnz = 0;
+    T* Pw = Gw + 3 * G3;
     if (a.phibar != nullptr) {
-        axis_window(rx, sh[0] - 1, sh[3] + 2, H, dox, dWx);
-        axis_window(ry, sh[1] - 1, sh[4] + 2, H, doy, dWy);
-        axis_window(rz, sh[2] - 1, sh[5] + 2, H, doz, dWz);
-        dwin = used + (size_t)dWx * dWy * dWz * sizeof(T) <= (size_t)lds_bytes;
-    }
-    T* Pw = reinterpret_cast<T*>(lds + used);
-    if (dwin) {
-        const int dn = dWx * dWy * dWz;
-        const float inv_y = 1.0f / (float)dWy, inv_z = 1.0f / (float)dWz;
+        adj_axis(pk_lo(bx), pk_hi(bx), 0, mx, D - 3, H, dox, dnx);
+        adj_axis(pk_lo(by), pk_hi(by), 0, my, D - 3, H, doy, dny);
+        adj_axis(pk_lo(bz), pk_hi(bz), 0, mz, D - 3, H, doz, dnz);
+        dox = (dox + rx) & Hm;
+        doy = (doy + ry) & Hm;
+        doz = (doz + rz) & Hm;
+        const int wy = dny + 3, wz = dnz + 3, dn = (dnx + 3) * wy * wz;
+        const float inv_y = 1.0f / (float)wy, inv_z = 1.0f / (float)wz;
         for (int e = tid; e < dn; e += APT) {
             int i, j, k;
-            unflatten3(e, dWy, dWz, inv_z, inv_y, i, j, k);
-            Pw[e] = gp(a.phibar)[((size_t)((dox + i) & Hm) * H + ((doy + j) & Hm)) * H + ((doz + k) & Hm)];
+            unflatten3(e, wy, wz, inv_z, inv_y, i, j, k);
+            Pw[i * D2 + j * D + k] =
+                gp(a.phibar)[(uint32_t)((((dox - 1 + i) & Hm) * H + ((doy - 1 + j) & Hm)) * H + ((doz - 1 + k) & Hm))];
         }
     }
     const T cdep = a.wmass * hl;
+    const int wy = gny + 1, wz = gnz + 1, gn = (gnx + 1) * wy * wz;
+    const float inv_y = 1.0f / (float)wy, inv_z = 1.0f / (float)wz;
     if (gwin) {
-        const float inv_y = 1.0f / (float)gWy, inv_z = 1.0f / (float)gWz;
         for (int e = tid; e < gn; e += APT) {
             int i, j, k;
-            unflatten3(e, gWy, gWz, inv_z, inv_y, i, j, k);
-            const size_t node = ((size_t)((gox + i) & Hm) * H + ((goy + j) & Hm)) * H + ((goz + k) & Hm);
-            Gw[e] = gp(a.G)[node];
-            Gw[gn + e] = gp(a.G)[H3 + node];
-            Gw[2 * gn + e] = gp(a.G)[2 * H3 + node];
-            Gb[e] = 0;
-            Gb[gn + e] = 0;
-            Gb[2 * gn + e] = 0;
+            unflatten3(e, wy, wz, inv_z, inv_y, i, j, k);
+            const uint32_t node = (uint32_t)((((gox + i) & Hm) * H + ((goy + j) & Hm)) * H + ((goz + k) & Hm));
+            const int at = i * G2 + j * G + k;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                Gw[d * G3 + at] = gp(a.G + d * H3)[node];
+                Gb[d * G3 + at] = 0;
+            }
         }
     }
     int e2 = 0;
@@ -285,7 +312,7 @@ __device__ __forceinline__ void adj_item(const AdjDesc<T>& a, int64_t beg, int c
     const T back = (T)ldexp(1.0, e2 - AdjFixed<T>::E);
     __syncthreads();
 
-#pragma unroll ADJ_UNROLL
+#pragma unroll 1
     for (int k = 0; k < APPT; ++k) {
         const int j = tid + k * APT;
         if (j >= cnt) continue;
@@ -317,95 +344,77 @@ __device__ __forceinline__ void adj_item(const AdjDesc<T>& a, int64_t beg, int c
             }
         }
         int gc[3];
-        T w[3][2];
-        for (int d = 0; d < 3; ++d) {
-            const T sv = Y[d] * hl;
-            const T f = floor(sv);
-            gc[d] = (int)f;
-            w[d][1] = sv - f;
-            w[d][0] = (T)1 - w[d][1];
-        }
+        T l[3];
+        cell_of(Y, hl, gc, l);
         const int i0 = (gc[0] - gox) & Hm, j0 = (gc[1] - goy) & Hm, k0 = (gc[2] - goz) & Hm;
-        const bool inside = gwin && (gWx == H || i0 <= gWx - 2) && (gWy == H || j0 <= gWy - 2) &&
-                            (gWz == H || k0 <= gWz - 2);
-        // node offsets: in the window, or in the whole grid
-        int off[8];
-        {
-            int q = 0;
-            for (int ia = 0; ia < 2; ++ia)
-                for (int ib = 0; ib < 2; ++ib)
-                    for (int ic = 0; ic < 2; ++ic, ++q) {
-                        if (inside)
-                            off[q] = (((gc[0] + ia - gox) & Hm) * gWy + ((gc[1] + ib - goy) & Hm)) * gWz +
-                                     ((gc[2] + ic - goz) & Hm);
-                        else
-                            off[q] = (((gc[0] + ia) & Hm) * H + ((gc[1] + ib) & Hm)) * H + ((gc[2] + ic) & Hm);
-                    }
-        }
-        // gradient values at the 8 nodes: from the LDS window or from HBM (two
-        // explicit paths, so that LDS reads stay ds_read instructions)
-        T gv[3][8];
+        const bool inside = gwin && i0 < gnx && j0 < gny && k0 < gnz;
+        const T wyz[4] = {((T)1 - l[1]) * ((T)1 - l[2]), ((T)1 - l[1]) * l[2], l[1] * ((T)1 - l[2]), l[1] * l[2]};
+        const T wt[8] = {((T)1 - l[0]) * wyz[0], ((T)1 - l[0]) * wyz[1], ((T)1 - l[0]) * wyz[2], ((T)1 - l[0]) * wyz[3],
+                         l[0] * wyz[0],          l[0] * wyz[1],          l[0] * wyz[2],          l[0] * wyz[3]};
+        T yb[3] = {xb[0], xb[1], xb[2]}, xv = 0;
+        // gradient component d at the cell's nodes: its value and derivatives
+        auto component = [&](int d, T vb, auto node) {
+            const Quad<T> lo(node(0, 0, 0), node(0, 0, 1), node(0, 1, 0), node(0, 1, 1), l[1], l[2]);
+            const Quad<T> hi(node(1, 0, 0), node(1, 0, 1), node(1, 1, 0), node(1, 1, 1), l[1], l[2]);
+            const T dx = hi.q - lo.q, vh = vb * hl;
+            xv += xb[d] * (lo.q + l[0] * dx);
+            yb[0] += vh * dx;
+            yb[1] += vh * (lo.u + l[0] * (hi.u - lo.u));
+            yb[2] += vh * (lo.v + l[0] * (hi.v - lo.v));
+        };
+        // two explicit paths, so that LDS reads stay ds_read instructions; the
+        // transpose of the gather spreads vbar with the trilinear weights at Y
         if (inside) {
+            const int at = i0 * G2 + j0 * G + k0;
 #pragma unroll
-            for (int q = 0; q < 8; ++q)
+            for (int d = 0; d < 3; ++d) {
+                const T vb = a.chitau * xb[d], vs = vb * scale;
+                const T* g = Gw + d * G3 + at;
+                component(d, vb, [&](int ia, int ib, int ic) { return g[ia * G2 + ib * G + ic]; });
+                U* b = reinterpret_cast<U*>(Gb + d * G3 + at);
 #pragma unroll
-                for (int d = 0; d < 3; ++d) gv[d][q] = Gw[d * gn + off[q]];
+                for (int q = 0; q < 8; ++q)
+                    atomicAdd(b + (q >> 2) * G2 + ((q >> 1) & 1) * G + (q & 1), AdjFixed<T>::q(wt[q] * vs));
+            }
         } else {
-#pragma unroll
-            for (int q = 0; q < 8; ++q)
-#pragma unroll
-                for (int d = 0; d < 3; ++d) gv[d][q] = gp(a.G)[d * H3 + off[q]];
+            const uint32_t r0 = (gc[0] & Hm) * H * H, r1 = ((gc[0] + 1) & Hm) * H * H;
+            const uint32_t c0 = (gc[1] & Hm) * H, c1 = ((gc[1] + 1) & Hm) * H, e0 = gc[2] & Hm, e1 = (gc[2] + 1) & Hm;
+            auto at = [&](int ia, int ib, int ic) { return (ia ? r1 : r0) + (ib ? c1 : c0) + (ic ? e1 : e0); };
+#pragma unroll 1
+            for (int d = 0; d < 3; ++d) {
+                const T xd = d == 0 ? xb[0] : (d == 1 ? xb[1] : xb[2]);
+                const T vb = a.chitau * xd;
+                const auto g = gp(a.G + d * H3);
+                const Quad<T> lo(g[at(0, 0, 0)], g[at(0, 0, 1)], g[at(0, 1, 0)], g[at(0, 1, 1)], l[1], l[2]);
+                const Quad<T> hi(g[at(1, 0, 0)], g[at(1, 0, 1)], g[at(1, 1, 0)], g[at(1, 1, 1)], l[1], l[2]);
+                const T dx = hi.q - lo.q, vh = vb * hl;
+                xv += xd * (lo.q + l[0] * dx);
+                yb[0] += vh * dx;
+                yb[1] += vh * (lo.u + l[0] * (hi.u - lo.u));
+                yb[2] += vh * (lo.v + l[0] * (hi.v - lo.v));
+                for (int q = 0; q < 8; ++q)
+                    gatomic_add(a.Gbar + d * H3 + at(q >> 2, (q >> 1) & 1, q & 1), wt[q] * vb);
+            }
         }
-        T v[3] = {0, 0, 0}, J[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}}, wt[8];
-        {
-            int q = 0;
-#pragma unroll
-            for (int ia = 0; ia < 2; ++ia)
-#pragma unroll
-                for (int ib = 0; ib < 2; ++ib)
-#pragma unroll
-                    for (int ic = 0; ic < 2; ++ic, ++q) {
-                        const T wyz = w[1][ib] * w[2][ic], wxz = w[0][ia] * w[2][ic], wxy = w[0][ia] * w[1][ib];
-                        wt[q] = w[0][ia] * wyz;
-                        const T dx = (ia ? hl : -hl) * wyz;
-                        const T dy = (ib ? hl : -hl) * wxz;
-                        const T dz = (ic ? hl : -hl) * wxy;
-#pragma unroll
-                        for (int d = 0; d < 3; ++d) {
-                            v[d] += wt[q] * gv[d][q];
-                            J[d][0] += dx * gv[d][q];
-                            J[d][1] += dy * gv[d][q];
-                            J[d][2] += dz * gv[d][q];
-                        }
-                    }
-        }
-        chib += (double)(a.tau * (xb[0] * v[0] + xb[1] * v[1] + xb[2] * v[2]));
-        T vb[3], yb[3];
-        for (int d = 0; d < 3; ++d) vb[d] = a.chitau * xb[d];
-        for (int e = 0; e < 3; ++e) yb[e] = xb[e] + vb[0] * J[0][e] + vb[1] * J[1][e] + vb[2] * J[2][e];
+        chib += (double)(a.tau * xv);
         if (SCHEME == SIPF_STRANG)
             sb += (double)(xb[0] * zp[0] + xb[1] * zp[1] + xb[2] * zp[2] + yb[0] * zm[0] + yb[1] * zm[1] +
                            yb[2] * zm[2]);
         else
             sb += (double)(xb[0] * zp[0] + xb[1] * zp[1] + xb[2] * zp[2]);
-        // transpose of the gather: vbar spread with the trilinear weights at Y
-        if (inside) {
-            const T vs[3] = {vb[0] * scale, vb[1] * scale, vb[2] * scale};
-            for (int q = 0; q < 8; ++q)
-                for (int d = 0; d < 3; ++d)
-                    atomicAdd(reinterpret_cast<U*>(Gb + d * gn + off[q]), AdjFixed<T>::q(wt[q] * vs[d]));
-        } else {
-            for (int q = 0; q < 8; ++q)
-                for (int d = 0; d < 3; ++d) gatomic_add(a.Gbar + d * H3 + off[q], wt[q] * vb[d]);
-        }
         // transpose of the deposit at X
         if (a.phibar != nullptr) {
-            T gx, gy, gz;
-            if (dwin) deposit_grad(Pw, X[0], X[1], X[2], hl, H, gx, gy, gz, dox, doy, doz, dWy, dWz);
-            else deposit_grad(a.phibar, X[0], X[1], X[2], hl, H, gx, gy, gz);
-            yb[0] += cdep * gx;
-            yb[1] += cdep * gy;
-            yb[2] += cdep * gz;
+            T dg[3];
+            cell_of(X, hl, gc, l);
+            const int di = (gc[0] - dox) & Hm, dj = (gc[1] - doy) & Hm, dk = (gc[2] - doz) & Hm;
+            if (di < dnx && dj < dny && dk < dnz) {
+                const T* p = Pw + di * D2 + dj * D + dk;
+                deposit_grad([&](int i, int j, int k) { return p[i * D2 + j * D + k]; }, l, dg[0], dg[1], dg[2]);
+            } else {
+                deposit_grad_grid(a.phibar, H, gc, l, dg[0], dg[1], dg[2]);
+            }
+#pragma unroll
+            for (int d = 0; d < 3; ++d) yb[d] += cdep * dg[d];
         }
         gp(a.xbx + beg)[j] = yb[0];
         gp(a.xby + beg)[j] = yb[1];
@@ -413,15 +422,15 @@ __device__ __forceinline__ void adj_item(const AdjDesc<T>& a, int64_t beg, int c
     }
     __syncthreads();
     if (gwin) {
-        const float inv_y = 1.0f / (float)gWy, inv_z = 1.0f / (float)gWz;
-        for (int e = tid; e < 3 * gn; e += APT) {
-            const I val = Gb[e];
-            if (val != 0) {
-                const int d = e >= 2 * gn ? 2 : (e >= gn ? 1 : 0);
-                int i, j, k;
-                unflatten3(e - d * gn, gWy, gWz, inv_z, inv_y, i, j, k);
-                const size_t node = ((size_t)((gox + i) & Hm) * H + ((goy + j) & Hm)) * H + ((goz + k) & Hm);
-                gatomic_add(a.Gbar + d * H3 + node, (T)val * back);
+        for (int e = tid; e < gn; e += APT) {
+            int i, j, k;
+            unflatten3(e, wy, wz, inv_z, inv_y, i, j, k);
+            const uint32_t node = (uint32_t)((((gox + i) & Hm) * H + ((goy + j) & Hm)) * H + ((goz + k) & Hm));
+            const int at = i * G2 + j * G + k;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                const I val = Gb[d * G3 + at];
+                if (val != 0) gatomic_add(a.Gbar + d * H3 + node, (T)val * back);
             }
         }
     }
@@ -439,30 +448,20 @@ __device__ __forceinline__ double block_sum_n(double v, double* sh, int nthreads
     return t;
 }
 
-// Register budget of the reverse pass: waves per SIMD to leave room for (0: the
-// compiler's choice).
-#ifndef ADJ_WAVES
-#define ADJ_WAVES 0
-#endif
-#if ADJ_WAVES > 0
-#define ADJ_ATTR __attribute__((amdgpu_waves_per_eu(ADJ_WAVES)))
-#else
-#define ADJ_ATTR
-#endif
 template <typename T, int SCHEME>
-__global__ __launch_bounds__(AdjShape<T>::PT) ADJ_ATTR void k_adj_items(AdjDesc<T> a,
-                                                                      const WorkItem* __restrict__ items, int* hdr,
-                                                                      int lds_bytes) {
+__global__ __launch_bounds__(AdjShape<T>::PT) __attribute__((amdgpu_waves_per_eu(AdjShape<T>::WAVES))) void k_adj_items(
+    AdjDesc<T> a, const WorkItem* __restrict__ items, int* hdr) {
     constexpr int APT = AdjShape<T>::PT;
     extern __shared__ __align__(16) unsigned char lds[];
-    __shared__ int sh[8];
+    __shared__ int4 sh[APT / 64];
     __shared__ int slot;
     __shared__ double shd[APT / 64];
     const int n = hdr[0];
     double chib = 0, sb = 0;
-    for (int it = blockIdx.x; it < n; it = next_item(hdr, n, &slot)) {
+    const Ticket ticket{hdr, n, &slot};
+    for (int it = blockIdx.x; it < n; it = ticket.next()) {
         const WorkItem w = items[it];
-        adj_item<T, SCHEME>(a, w.beg, w.cnt, lds, lds_bytes, sh, chib, sb);
+        adj_item<T, SCHEME>(a, w.beg, w.cnt, lds, sh, ticket, chib, sb);
     }
     __syncthreads();
     const double tc = block_sum_n(chib, shd, APT);
@@ -534,21 +533,28 @@ template <typename T> hipError_t launch_adj_seed(const AdjDesc<T>& a, hipStream_
     hipLaunchKernelGGL((k_adj_seed<T>), dim3(grid_for(a.P)), dim3(256), 0, s, a);
     return hipGetLastError();
 }
+// Workgroups of the reverse pass that the device holds at once
+template <typename T> int adj_resident_blocks(int scheme) {
+    const void* k = scheme == SIPF_STRANG ? (const void*)k_adj_items<T, SIPF_STRANG> : (const void*)k_adj_items<T, SIPF_EM>;
+    int per_cu = 0, dev = 0, cus = 0;
+    hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, adj_lds_bytes<T>());
+    if (e == hipSuccess)
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, AdjShape<T>::PT, adj_lds_bytes<T>());
+    if (e == hipSuccess) e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess || per_cu < 1 || cus < 1) {
+        (void)hipGetLastError();
+        return 256;
+    }
+    return per_cu * cus;
+}
 template <typename T>
 hipError_t launch_adj_items(const AdjDesc<T>& a, const WorkItem* items, int* nitems, int grid, hipStream_t s) {
     if (grid <= 0) return hipSuccess;
     constexpr int APT = AdjShape<T>::PT;
     if (particle_chunk() > APT * AdjShape<T>::PPT) return hipErrorInvalidValue;  // an item must fit one workgroup
-    const int lds = adj_window_bytes(sizeof(T) == 8);
-    if (a.scheme == SIPF_STRANG) {
-        (void)hipFuncSetAttribute((const void*)k_adj_items<T, SIPF_STRANG>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        hipLaunchKernelGGL((k_adj_items<T, SIPF_STRANG>), dim3(grid), dim3(APT), lds, s, a, items, nitems, lds);
-    } else {
-        (void)hipFuncSetAttribute((const void*)k_adj_items<T, SIPF_EM>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  lds);
-        hipLaunchKernelGGL((k_adj_items<T, SIPF_EM>), dim3(grid), dim3(APT), lds, s, a, items, nitems, lds);
-    }
+    auto k = a.scheme == SIPF_STRANG ? k_adj_items<T, SIPF_STRANG> : k_adj_items<T, SIPF_EM>;
+    hipLaunchKernelGGL(k, dim3(grid), dim3(APT), adj_lds_bytes<T>(), s, a, items, nitems);
     return hipGetLastError();
 }
 template <typename T>
@@ -586,6 +592,7 @@ hipError_t launch_zero_f64(double* p, int n, hipStream_t s) {
 }
 
 #define SIPF_ADJ_INST(T)                                                                \
+    template int adj_resident_blocks<T>(int);                                                   \
     template hipError_t launch_adj_seed<T>(const AdjDesc<T>&, hipStream_t);            \
     template hipError_t launch_adj_items<T>(const AdjDesc<T>&, const WorkItem*, int*, int, hipStream_t); \
     template hipError_t launch_copy_positions<T>(T*, T*, T*, uint32_t*, const T*, const T*, const T*,          \

@@ -190,11 +190,18 @@ int item_chunk(const sipf_params* p, int64_t total_P) {
     if (dim_of(p) == 2) return most;
     return (int)std::min<int64_t>(most, std::max<int64_t>(256, (total_P / 192 + 128) / 256 * 256));
 }
-// Work-item size of the adjoint's per-segment sorts: its reverse item pass
-// holds one workgroup per CU and three windows per item, and prefers items of
-// 2048 (adjoint workload, P = 2e6: reverse sweep ~0.75 ms shorter than at 3072;
-// blob P = 2e5, H = 32: 25.0 us per launch against 33.4 with items of 1024).
-int default_adj_chunk(const sipf_params* p) { return p->chunk ? p->chunk : 2048; }
+// Work-item size of the adjoint's per-segment sorts: the rule of item_chunk
+// with at most 4096, which one workgroup of the reverse pass holds.  An item
+// adds a window of float atomics to the cotangent grids and stages three, so
+// larger items win as long as there is about one per CU.  Us per launch of the
+// reverse pass at items of 512 / 1024 / 2048 / 3072 / 4096: FP64 blob P = 1e5,
+// H = 32, 20.5 / 21.0 / 28.4 / 36.9 / 44.4; P = 5e5, H = 64, 131 / 87 / 82 / 60
+// / 65; P = 2e6 459 / 289 / 205 / 189 / 156; FP32 P = 2e6 232 / 150 / 105 / 97 /
+// 82.
+int default_adj_chunk(const sipf_params* p, int64_t P) {
+    const int most = p->chunk ? p->chunk : 4096;
+    return (int)std::min<int64_t>(most, std::max<int64_t>(256, (P / 192 + 128) / 256 * 256));
+}
 
 }  // namespace
 
@@ -1184,7 +1191,7 @@ int setup_group(Group* g, int32_t n, const sipf_params* prm, const int64_t* P, c
     int64_t total_P = 0;
     for (int i = 0; i < n; ++i) total_P += P[i];
     g->chunk = item_chunk(&prm[0], total_P);
-    g->adj_chunk = default_adj_chunk(&prm[0]);
+    g->adj_chunk = default_adj_chunk(&prm[0], total_P);
     g->win_bytes = particle_window_bytes(g->prec == SIPF_FP64);
     g->in.resize(n);
     for (int i = 0; i < n; ++i) {
@@ -1626,6 +1633,7 @@ int adjoint_typed(Group* c, int64_t N, int K, const T* phibar_in, double* loss_o
     ad.k1 = ref.k1;
     ad.inst = ref.inst;
     ad.gmargin = ref.gmargin;
+    const int adj_grid = std::max(1, std::min(c->items_cap, adj_resident_blocks<T>(c->scheme)));
     ad.xbar = (T*)xbar.p;
     ad.xbx = (T*)xbs.p;
     ad.xby = ad.xbx + P;
@@ -1686,7 +1694,7 @@ int adjoint_typed(Group* c, int64_t N, int K, const T* phibar_in, double* loss_o
             ad.n = (uint32_t)n;
             // steps base+1 .. base+len-1 were pushed by the recompute, which kept their normals
             ad.zin = keep_noise && n < base + len ? (const T*)zseg.p + (size_t)(n - base - 1) * 6 * P : nullptr;
-            HIPCHK(launch_adj_items<T>(ad, c->items, c->nitems, c->pgrid, c->stream));
+            HIPCHK(launch_adj_items<T>(ad, c->items, c->nitems, adj_grid, c->stream));
             // (c) abar^(n-1) = A abar^(n) + sum_d (-i xi_d Phi) R2C(Gbar_d); for n > 1 the
             // same pass also makes the source term of abar^(n-1), i.e. phibar^(n-2) of step n - 1
             HIPCHK(launch_fwd_planes<T>(H, (const FieldDesc<T>*)fdA.p, 1, 3, true, c->stream));

@@ -234,7 +234,7 @@ template <typename T>
 hipError_t launch_xbar_order(T* xbar, T* bx, T* by, T* bz, const uint32_t* id, int64_t P, bool to_order,
                              hipStream_t s);
 hipError_t launch_iota_u32(uint32_t* p, int64_t n, hipStream_t s);
-int adj_window_bytes(bool fp64);
+template <typename T> int adj_resident_blocks(int scheme);
 // --- direct SIPF (direct.hip) -------------------------------------------------
 // One instance of Algorithm 1: particles in original order (SoA), full
 // spectra H^3 in natural order.

@@ -138,6 +138,36 @@ __device__ __forceinline__ int wave_pk_min(int v) {
     v = pk_min(v, __builtin_amdgcn_update_dpp(v, v, 0x143, 0xc, 0xf, false));
     return v;
 }
+constexpr int BOUNDS_NONE = 0x7FFF7FFF;  // of no value: the pairwise minimum's identity
+// lane 63 receives the maximum of non-negative v over the wave
+__device__ __forceinline__ int wave_max_dpp(int v) {
+    v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x111, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x112, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x114, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x118, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x142, 0xa, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x143, 0xc, 0xf, false));
+    return v;
+}
+// The bounds of three values (as block_bounds3) and the maximum of m >= 0
+template <int NW> __device__ __forceinline__ int block_bounds3_max(int& x, int& y, int& z, int m, int4* sh) {
+    const int bx = wave_pk_min(x), by = wave_pk_min(y), bz = wave_pk_min(z), bm = wave_max_dpp(m);
+    if ((threadIdx.x & 63) == 63) sh[threadIdx.x >> 6] = make_int4(bx, by, bz, bm);
+    __syncthreads();
+    int4 r = sh[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) {
+        const int4 v = sh[w];
+        r.x = pk_min(r.x, v.x);
+        r.y = pk_min(r.y, v.y);
+        r.z = pk_min(r.z, v.z);
+        r.w = max(r.w, v.w);
+    }
+    x = __builtin_amdgcn_readfirstlane(r.x);
+    y = __builtin_amdgcn_readfirstlane(r.y);
+    z = __builtin_amdgcn_readfirstlane(r.z);
+    return __builtin_amdgcn_readfirstlane(r.w);
+}
 template <int NW> __device__ __forceinline__ void block_bounds3(int& x, int& y, int& z, int4* sh) {
     const int bx = wave_pk_min(x), by = wave_pk_min(y), bz = wave_pk_min(z);
     if ((threadIdx.x & 63) == 63) sh[threadIdx.x >> 6] = make_int4(bx, by, bz, 0);
