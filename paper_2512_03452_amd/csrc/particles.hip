@@ -683,7 +683,10 @@ __device__ __forceinline__ void item_pass(const PartDesc<T>& a, int64_t beg, int
     } else if (windows) {
         rows.load(a.G, H, wr, gcx, gcy, gcz, gnx + 1, gny + 1, gnz + 1);
     }
-    if (!DEP) ticket.draw();
+    if (!DEP) {
+        if (!windows) __syncthreads();  // every wave has read the last draw (with windows: the bounds' barrier)
+        ticket.draw();
+    }
 
     if (PUSH) {
         T* Gw = reinterpret_cast<T*>(lds);
@@ -759,7 +762,7 @@ __device__ __forceinline__ void item_pass(const PartDesc<T>& a, int64_t beg, int
     }
 }
 
-// Persistent over the work items listed by the last sort (header: next_item).
+// Persistent over the work items listed by the last sort (header: Ticket).
 // Lane layout of an FP32 item of cnt particles: ppe = ceil(cnt / PT)
 // particles per lane on lact = ceil(cnt / ppe) lanes; lane t holds the
 // particles of ranks t ppe .. t ppe + ppe - 1 of the item, and rank
