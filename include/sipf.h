@@ -177,8 +177,9 @@ typedef struct sipf_params {
     int32_t  tile;         /* binning tile side in cells; 0 = tuned default; at most
                               16 (3-D) or 64 (2-D) tiles per axis; a power of two,
                               or any side when H is not one                      */
-    int32_t  resort_every; /* re-sort period in steps; 0 = default: 8 in 3-D (10 in the
-                              sorted pass; 6 above H = 64), 4 in 2-D, or fewer when sqrt(2 mu tau n) exceeds a quarter of a tile */
+    int32_t  resort_every; /* re-sort period in steps; 0 = default: 8 (10 in the sorted
+                              3-D pass; 6 in 3-D above H = 64), or fewer when in 3-D sqrt(2 mu tau n)
+                              exceeds a quarter of a tile, in 2-D an item outgrows its LDS window */
     int32_t  chunk;        /* max particles per work item of the particle pass (256..4096); 0 = default:
                               4096 in 2-D and from 2^23 particles per 3-D group, else 3072.  3-D groups
                               of P particles take items of about P/192 (at least 256) where that is

@@ -148,25 +148,39 @@ int default_tile(const sipf_params* p, bool sorted, int64_t P) {
     if (p->H / t > 16 && P < MANY_TILES_P) t = p->H / 16;
     return t;
 }
-// Re-sort period: in 3-D every 8 steps (10 in the sorted pass) up to H = 64
-// and 6 above, in 2-D 4; or more often when the Brownian spread over the
-// period, sqrt(2 mu tau n), would exceed a quarter of a tile: items' boxes
-// then outgrow their LDS windows and strays go to global memory, which costs
-// most where the grid is finest.  Us per step at periods 4 / 6 / 8 / 12: mixed
-// H = 64, P = 1e6, 57.5 / 55.9 / 55.5 / 55.9 and P = 3e6 106.3 / 102.8 / 102.3
-// / 105.5; blob H = 32, P = 1e6, 57.6 / 54.5 / 52.5 / 50.4; mixed H = 128,
-// P = 3e6, 177 / 190 / 203; torus H = 128, P = 3e6, 125 / 122 / 124; ring
-// H = 256, P = 1e6, 434 / 428 / 425; mixed H = 256, P = 1e6, 720 / 761 / 807;
-// sorted pass, 64-instance ensemble (H = 32 and 64), 6 / 8 / 10 / 12: 575 /
-// 555 / 546 / 548.
+// Re-sort period.  3-D: every 8 steps (10 in the sorted pass) up to H = 64 and
+// 6 above, or more often when the Brownian spread over the period, sqrt(2 mu
+// tau n), would exceed a quarter of a tile: items' boxes then outgrow their LDS
+// windows and strays go to global memory, which costs most where the grid is
+// finest.  Us per step at periods 4 / 6 / 8 / 12: mixed H = 64, P = 1e6, 57.5 /
+// 55.9 / 55.5 / 55.9 and P = 3e6 106.3 / 102.8 / 102.3 / 105.5; blob H = 32,
+// P = 1e6, 57.6 / 54.5 / 52.5 / 50.4; mixed H = 128, P = 3e6, 177 / 190 / 203;
+// torus H = 128, P = 3e6, 125 / 122 / 124; ring H = 256, P = 1e6, 434 / 428 /
+// 425; mixed H = 256, P = 1e6, 720 / 761 / 807; sorted pass, 64-instance
+// ensemble (H = 32 and 64), 6 / 8 / 10 / 12: 575 / 555 / 546 / 548.
+//
+// 2-D: every 8 steps, or as long as an item's box, the tile and five times the
+// spread on both sides, stays in the square deposit window: an item whose box
+// does not deposits all its particles in global memory.  Us per step at 1 / 2 /
+// 3 / 4 / 6 / 8: disk H = 2048 (8 cells of noise a step), P = 4e6, 156 / 161 /
+// 695 / 1165 / 1663 / 1933; H = 1024, P = 4e6, 114 / 95 / 89 / 86 / 89 / 98;
+// H = 512, P = 4e6, 110 / 86 / 79 / 74 / 71 / 69; H = 128, P = 4e6, 160 / 107 /
+// 91 / 80 / 71 / 66.
 int default_resort(const sipf_params* p, int tile, bool sorted) {
     if (p->resort_every) return p->resort_every;
-    const double cap = dim_of(p) == 2 ? 4.0 : (p->H > 64 ? 6.0 : (sorted ? 10.0 : 8.0));
-    const double q = tile * p->L / p->H / 4.0;
+    const bool plane = dim_of(p) == 2;
+    const double cap = plane || !sorted ? 8.0 : 10.0;
+    const double most = !plane && p->H > 64 ? 6.0 : cap;
+    double q = tile * p->L / p->H / 4.0;
+    if (plane) {
+        const bool fp64 = p->precision == SIPF_FP64;
+        const double window = std::sqrt((double)particle_window_bytes(fp64) / (fp64 ? 8 : 4)) - 3.0;
+        q = std::max(0.0, window - tile) * p->L / p->H / 10.0;
+    }
     const double spread = 2.0 * p->mu * p->dt;
-    if (spread <= 0) return (int)cap;
+    if (spread <= 0) return (int)most;
     const double n = std::floor(q * q / spread);
-    return (int)std::max(1.0, std::min(cap, n));
+    return (int)std::max(1.0, std::min(most, n));
 }
 // Largest work-item size where the parameters leave it open: in 3-D, 3072, and
 // 4096 from 2^23 particles per group; 2-D keeps 4096.  With several items per
