@@ -17,7 +17,7 @@
 //   dir_beta    thread = (kx, ky, run of QZ consecutive q_z); the particles of
 //               one slice of the particle range pass through LDS; per-slice
 //               partial sums.  Also advances the step counter.
-//   dir_modes   thread = mode: sums the slice partials in a fixed order, forms
+//   dir_modes   one or eight threads per mode: sums the slice partials in a fixed order, forms
 //               the gradient coefficients i xi Phi alpha^(n-1), then updates
 //               alpha.
 //   dir_grad    thread = particle, workgroup row = slice of the (kx, ky)
@@ -34,6 +34,7 @@ namespace sipf {
 constexpr int DIR_THREADS = 256;
 constexpr int DIR_PCHUNK = 256;  // particles staged per LDS pass of dir_beta
 constexpr int DIR_PAIRS = 8;     // (kx, ky) pairs staged per LDS pass of dir_push
+constexpr int DIR_LANES_FROM = 32;  // slices from which eight threads sum a mode
 constexpr int DIR_ANCHOR = 8;    // FP32: phase terms between fresh sincos evaluations
 
 __device__ __forceinline__ int signed_q(int k, int H) { return k < H / 2 ? k : k - H; }
@@ -98,16 +99,33 @@ __global__ __launch_bounds__(DIR_THREADS) void k_dir_beta(DirDesc<T> d, cplx_t<T
     }
 }
 
-template <typename T, int H>
+// LANES threads per mode share its slices (thread l those with s mod LANES = l)
+// and their sums meet in LDS: on small grids one thread per mode leaves most of
+// the chip idle behind a chain of up to 1024 dependent loads.  H = 16, P = 4096:
+// 19.0 us with one thread and 64 slices, 4.0 with eight and 128.
+template <typename T, int H, int LANES>
 __global__ __launch_bounds__(DIR_THREADS) void k_dir_modes(DirDesc<T> d, const cplx_t<T>* __restrict__ part,
                                                            int nslices) {
     using V = cplx_t<T>;
-    const int m = blockIdx.x * DIR_THREADS + threadIdx.x;
+    constexpr int MODES = DIR_THREADS / LANES;
+    __shared__ V sums[LANES > 1 ? DIR_THREADS : 1];
+    const int l = threadIdx.x / MODES;
+    const int m = blockIdx.x * MODES + threadIdx.x % MODES;
+    V beta = cmake<V, T>(0, 0);
+    if (m < H * H * H) {
+#pragma unroll 8
+        for (int s = l; s < nslices; s += LANES) beta = cadd(beta, part[(size_t)s * H * H * H + m]);
+    }
+    if constexpr (LANES > 1) {
+        sums[threadIdx.x] = beta;
+        __syncthreads();
+        if (l > 0) return;
+#pragma unroll
+        for (int k = 1; k < LANES; ++k) beta = cadd(beta, sums[k * MODES + threadIdx.x]);
+    }
     if (m >= H * H * H) return;
     const int kz = m % H, ky = (m / H) % H, kx = m / (H * H);
     const T qx = (T)signed_q(kx, H), qy = (T)signed_q(ky, H), qz = (T)signed_q(kz, H);
-    V beta = cmake<V, T>(0, 0);
-    for (int s = 0; s < nslices; ++s) beta = cadd(beta, part[(size_t)s * H * H * H + m]);
     beta = cscale(beta, d.bscale);
     const V a = d.alpha[m];
     const T q2 = qx * qx + qy * qy + qz * qz;
@@ -208,6 +226,7 @@ __global__ __launch_bounds__(DIR_THREADS) void k_dir_push(DirDesc<T> d, const T*
     T x, y, z, w0, w1, w2;
     dir_noise<T, SCHEME>(d, p, x, y, z, w0, w1, w2);
     T g0 = 0, g1 = 0, g2 = 0;
+#pragma unroll 8
     for (int k = 0; k < ms; ++k) {
         const T* g = gpart + (size_t)k * 3 * d.P;
         g0 += g[p];
@@ -241,11 +260,16 @@ int dir_mode_slices(int H, int64_t P) {
     return ms;
 }
 
+// Slices of the particle range in the mode sums: about 2048 workgroups, of at
+// least 32 particles each.  H = 16 (two workgroups of columns per slice),
+// P = 4096, us per step at 64 / 32 / 16 particles: 35.1 / 30.1 / 30.3; P = 8000,
+// 44.7 / 41.7 / 45.2; H = 8, P = 8000, 29.1 / 24.3 / 23.3.
+constexpr int DIR_SLICE = 32;
 int dir_slices(int H, int64_t P) {
     const int64_t cols = (int64_t)H * H * (H / dir_qz(H));
     const int64_t bx = (cols + DIR_THREADS - 1) / DIR_THREADS;
     int64_t s = (2048 + bx - 1) / bx;
-    s = std::min<int64_t>(s, (P + 63) / 64);
+    s = std::min<int64_t>(s, (P + DIR_SLICE - 1) / DIR_SLICE);
     return (int)std::max<int64_t>(1, std::min<int64_t>(s, 1024));
 }
 
@@ -255,8 +279,12 @@ static hipError_t dir_step_h(const DirDesc<T>& d, cplx_t<T>* part, int nslices, 
     const int cols = H * H * (H / QZ);
     launch_kernel((k_dir_beta<T, H, QZ>), dim3((cols + DIR_THREADS - 1) / DIR_THREADS, nslices), dim3(DIR_THREADS), 0,
                   s, d, part);
-    launch_kernel((k_dir_modes<T, H>), dim3((H * H * H + DIR_THREADS - 1) / DIR_THREADS), dim3(DIR_THREADS), 0, s, d,
-                  (const cplx_t<T>*)part, nslices);
+    if (nslices >= DIR_LANES_FROM)
+        launch_kernel((k_dir_modes<T, H, 8>), dim3((8 * H * H * H + DIR_THREADS - 1) / DIR_THREADS), dim3(DIR_THREADS),
+                      0, s, d, (const cplx_t<T>*)part, nslices);
+    else
+        launch_kernel((k_dir_modes<T, H, 1>), dim3((H * H * H + DIR_THREADS - 1) / DIR_THREADS), dim3(DIR_THREADS), 0,
+                      s, d, (const cplx_t<T>*)part, nslices);
     const unsigned pb = (unsigned)((d.P + DIR_THREADS - 1) / DIR_THREADS);
     if (d.scheme == SIPF_STRANG) {
         launch_kernel((k_dir_grad<T, H, SIPF_STRANG>), dim3(pb, ms), dim3(DIR_THREADS), 0, s, d, gpart);
