@@ -18,11 +18,11 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
-#include <mutex>
 #include <new>
 #include <string>
 #include <vector>
 
+#include "block_cache.h"
 #include "internal.h"
 #include "sipf.h"
 
@@ -288,8 +288,7 @@ struct Group {
     WorkItem* items = nullptr;  // concatenated work items of the particle pass
     int* nitems = nullptr;  // [0] item count, [1] ticket counter of the persistent passes (zero between launches)
     int items_cap = 0;
-    void* arena = nullptr;  // the block that holds the group's buffers (Arena)
-    size_t arena_bytes = 0;
+    Block arena;                // the block that holds the group's buffers (Arena)
     std::vector<void*> allocs;  // buffers made later (diagnostics)
     void* diag = nullptr;  // diagnostics scratch, allocated on first use
     // captured graphs of run segments, by (buffer set, steps since the last
@@ -319,73 +318,13 @@ struct sipf_batch : Group {};
 
 namespace {
 
-// Device blocks kept for later use instead of freed: hipMalloc and hipFree
-// cost tens of microseconds to milliseconds each, and hipFree waits for the
-// device.  A block goes to any later request on the same device that it fits
-// (best fit, at most twice the request).  Its last use has ended when it is
-// put back (the owner waits for its stream), so the next owner may use it on
-// any stream.  sipf_release_cached_memory returns the blocks.
-struct BufCache {
-    struct Blk {
-        int dev;
-        size_t n;
-        void* p;
-    };
-    explicit BufCache(size_t most) : limit(most) {}
-    const size_t limit;  // bytes kept per device at most
-    std::mutex mu;
-    std::vector<Blk> free_blocks;
-    // *got: the size of the block, to be handed back with it
-    hipError_t get(size_t n, void** out, size_t* got) {
-        int dev = 0;
-        hipError_t e = hipGetDevice(&dev);
-        if (e != hipSuccess) return e;
-        {
-            std::lock_guard<std::mutex> lock(mu);
-            int best = -1;
-            for (int i = 0; i < (int)free_blocks.size(); ++i) {
-                const Blk& b = free_blocks[i];
-                if (b.dev == dev && b.n >= n && b.n <= 2 * n && (best < 0 || b.n < free_blocks[best].n)) best = i;
-            }
-            if (best >= 0) {
-                *out = free_blocks[best].p;
-                *got = free_blocks[best].n;
-                free_blocks.erase(free_blocks.begin() + best);
-                return hipSuccess;
-            }
-        }
-        *got = n;
-        return hipMalloc(out, n);
-    }
-    void put(void* p, size_t n) {
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess) {
-            (void)hipGetLastError();
-            (void)hipFree(p);
-            return;
-        }
-        {
-            std::lock_guard<std::mutex> lock(mu);
-            size_t held = 0;
-            for (const Blk& b : free_blocks) held += b.dev == dev ? b.n : 0;
-            if (held + n <= limit) {
-                free_blocks.push_back({dev, n, p});
-                return;
-            }
-        }
-        (void)hipFree(p);
-    }
-    void release() {
-        std::lock_guard<std::mutex> lock(mu);
-        for (const Blk& b : free_blocks) {
-            int cur = 0;
-            if (hipGetDevice(&cur) == hipSuccess && cur != b.dev) (void)hipSetDevice(b.dev);
-            (void)hipFree(b.p);
-            if (cur != b.dev) (void)hipSetDevice(cur);
-        }
-        free_blocks.clear();
-    }
+struct HipDevice {
+    using Error = hipError_t;
+    static Error device(int* dev) { return hipGetDevice(dev); }
+    static Error alloc(void** p, size_t bytes) { return hipMalloc(p, bytes); }
+    static void free(void* p) { (void)hipFree(p); }
 };
+using BufCache = BlockCache<HipDevice>;
 // The adjoint's work buffers (about 2 GB of tape, segment and noise buffers in
 // an FP64 adjoint of 2e6 particles), and the blocks of destroyed contexts and
 // batches, of which at most 1 GiB per device stays.
@@ -428,20 +367,19 @@ struct Arena {
     }
     int commit(Group* g) {
         const size_t n = (size + 65535) / 65536 * 65536;
-        hipError_t e = g_group_cache.get(n, &g->arena, &g->arena_bytes);
+        hipError_t e = g_group_cache.get(n, &g->arena);
         if (e != hipSuccess) {
             // give the kept blocks back and try once more
             (void)hipGetLastError();
             g_group_cache.release();
             g_buf_cache.release();
-            e = g_group_cache.get(n, &g->arena, &g->arena_bytes);
+            e = g_group_cache.get(n, &g->arena);
         }
         if (e != hipSuccess) {
-            g->arena = nullptr;
             (void)hipGetLastError();
             return fail(SIPF_ENOMEM, std::string("hipMalloc failed: ") + hipGetErrorString(e));
         }
-        for (const Part& q : parts) *q.p = (char*)g->arena + q.off;
+        for (const Part& q : parts) *q.p = (char*)g->arena.p + q.off;
         return SIPF_OK;
     }
 };
@@ -943,7 +881,7 @@ template <typename T> int alloc_direct(Group* g) {
     ar.want(&I.part, (size_t)I.nslices * H3 * V);
     ar.want(&I.gpart, (size_t)I.mslices * 3 * I.P * sizeof(T));
     if ((rc = ar.commit(g))) return rc;
-    HIPCHK(hipMemsetAsync(g->arena, 0, zeros, g->stream));
+    HIPCHK(hipMemsetAsync(g->arena.p, 0, zeros, g->stream));
     g->classes.push_back(HClass{I.H, 0, 1});
     g->fslot.assign(1, 0);
     return SIPF_OK;
@@ -1031,7 +969,7 @@ template <typename T> int alloc_group(Group* g) {
     if ((rc = ar.commit(g))) return rc;
     // the tables: zero counters, descriptors, segment offsets, sort chunks
     std::vector<char> table(table_bytes, 0);
-    auto host = [&](const void* dev) { return table.data() + ((const char*)dev - (const char*)g->arena); };
+    auto host = [&](const void* dev) { return table.data() + ((const char*)dev - (const char*)g->arena.p); };
     PartDesc<T>* pd = (PartDesc<T>*)host(g->pdesc);
     FieldDesc<T>* fd = (FieldDesc<T>*)host(g->fdesc);
     for (int i = 0; i < n; ++i) {
@@ -1041,7 +979,7 @@ template <typename T> int alloc_group(Group* g) {
     }
     std::memcpy(host(g->seg_off), seg_off.data(), n * sizeof(int));
     std::memcpy(host(g->chunks), chunks.data(), chunks.size() * sizeof(SortChunk));
-    HIPCHK(hipMemcpy(g->arena, table.data(), table_bytes, hipMemcpyHostToDevice));
+    HIPCHK(hipMemcpy(g->arena.p, table.data(), table_bytes, hipMemcpyHostToDevice));
     if (!few) HIPCHK(launch_fill<float>((float*)g->counts, (int64_t)(n * mk), 0.0f, g->stream));
     if (g->positivity)
         for (const Inst& I : g->in) HIPCHK(hipMemsetAsync(I.pos_sw, 0, I.P * sizeof(uint32_t), g->stream));
@@ -1145,23 +1083,34 @@ int init_group(Group* g, const void* const* X0, int x0_on_device, const void* al
     return check_err(g);
 }
 
+// The device a group's memory is on, current for the scope's time.
+struct OnDevice {
+    int before = -1;
+    explicit OnDevice(int dev) {
+        int cur = 0;
+        if (dev >= 0 && hipGetDevice(&cur) == hipSuccess && cur != dev && hipSetDevice(dev) == hipSuccess) before = cur;
+    }
+    ~OnDevice() {
+        if (before >= 0) (void)hipSetDevice(before);
+    }
+};
+
 void free_group(Group* g) {
     if (!g) return;
+    const OnDevice on(g->arena.dev);
+    // The block goes to another owner, so nothing of this one may be pending on it.  The wait is for the
+    // whole device, as hipFree's is: the group's stream may be gone by now, its handle another's.
+    const bool idle = g->arena.p == nullptr || hipDeviceSynchronize() == hipSuccess;
+    if (!idle) (void)hipGetLastError();
     release_marks(g);
     for (auto& gs : g->gcache)
         if (gs.exec) (void)hipGraphExecDestroy(gs.exec);
     g->gcache.clear();
     if (g->cap) (void)hipStreamDestroy(g->cap);
     for (void* p : g->allocs) (void)hipFree(p);
-    if (g->arena) {
-        // nothing of the group is pending when its block goes back
-        if (hipStreamSynchronize(g->stream) != hipSuccess) {
-            (void)hipGetLastError();
-            (void)hipDeviceSynchronize();
-        }
-        g_group_cache.put(g->arena, g->arena_bytes);
-        g->arena = nullptr;
-    }
+    if (idle) g_group_cache.put(g->arena);
+    else (void)hipFree(g->arena.p);
+    g->arena = Block{};
 }
 
 // Shared set-up of contexts and batches: validation, host checks, tuning.
@@ -1406,27 +1355,19 @@ int profile_read_any(Group* g, double* ms, int64_t* launches) {
     return SIPF_OK;
 }
 
-int destroy_any(Group* g) {
-    if (g->stream) (void)hipStreamSynchronize(g->stream);
-    else (void)hipDeviceSynchronize();
-    free_group(g);
-    return SIPF_OK;
-}
-
 // ---------------------------------------------------------------------------
 // pathwise adjoint of a single-instance context
 // ---------------------------------------------------------------------------
 
 // Device buffer that goes back to the cache when it goes out of scope (adjoint temporaries).
 struct DevBuf {
+    Block block;
     void* p = nullptr;
-    size_t n = 0;
-    ~DevBuf() {
-        if (p) g_buf_cache.put(p, n);
-    }
+    ~DevBuf() { g_buf_cache.put(block); }
     hipError_t alloc(size_t bytes) {
-        n = bytes ? bytes : 16;
-        return g_buf_cache.get(n, &p, &n);
+        const hipError_t e = g_buf_cache.get(bytes ? bytes : 16, &block);
+        p = block.p;
+        return e;
     }
 };
 
@@ -2062,7 +2003,7 @@ int sipf_load(const char* path, void* hip_stream, sipf_ctx** out) {
 
 int sipf_destroy(sipf_ctx* c) {
     if (!c) return SIPF_OK;
-    destroy_any(c);
+    free_group(c);
     delete c;
     return SIPF_OK;
 }
@@ -2206,7 +2147,7 @@ int sipf_batch_use_graphs(sipf_batch* b, int enable) {
 
 int sipf_batch_destroy(sipf_batch* b) {
     if (!b) return SIPF_OK;
-    destroy_any(b);
+    free_group(b);
     delete b;
     return SIPF_OK;
 }
