@@ -352,7 +352,8 @@ int sipf_load(const char* path, void* hip_stream, sipf_ctx** out);
 
 /* Release the context and its device memory (NULL is a no-op).  Up to 1 GiB per
  * device of the memory of destroyed contexts and batches is kept for the next
- * ones (sipf_release_cached_memory returns it). */
+ * ones (sipf_release_cached_memory returns it, and so does any allocation of
+ * the library for which the device is too full). */
 int sipf_destroy(sipf_ctx* ctx);
 
 /* Message of the last failure on this thread ("" if none). */

@@ -321,7 +321,7 @@ namespace {
 struct HipDevice {
     using Error = hipError_t;
     static Error device(int* dev) { return hipGetDevice(dev); }
-    static Error alloc(void** p, size_t bytes) { return hipMalloc(p, bytes); }
+    static Error alloc(void** p, size_t bytes);
     static void free(void* p) { (void)hipFree(p); }
 };
 using BufCache = BlockCache<HipDevice>;
@@ -331,15 +331,26 @@ using BufCache = BlockCache<HipDevice>;
 BufCache g_buf_cache(SIZE_MAX);
 BufCache g_group_cache(size_t(1) << 30);
 
+// Every allocation of the library: when the device is full, the kept blocks go back first.
+hipError_t HipDevice::alloc(void** p, size_t bytes) {
+    return allocate_or_empty(
+        hipErrorOutOfMemory,
+        [&] {
+            const hipError_t e = hipMalloc(p, bytes);
+            if (e != hipSuccess) {
+                (void)hipGetLastError();
+                *p = nullptr;
+            }
+            return e;
+        },
+        g_group_cache, g_buf_cache);
+}
+
 int dalloc(Group* g, void** p, size_t bytes) {
     *p = nullptr;
     if (bytes == 0) bytes = 16;
-    hipError_t e = hipMalloc(p, bytes);
-    if (e != hipSuccess) {
-        *p = nullptr;
-        (void)hipGetLastError();
-        return fail(SIPF_ENOMEM, std::string("hipMalloc failed: ") + hipGetErrorString(e));
-    }
+    hipError_t e = HipDevice::alloc(p, bytes);
+    if (e != hipSuccess) return fail(SIPF_ENOMEM, std::string("hipMalloc failed: ") + hipGetErrorString(e));
     g->allocs.push_back(*p);
     return SIPF_OK;
 }
@@ -367,18 +378,8 @@ struct Arena {
     }
     int commit(Group* g) {
         const size_t n = (size + 65535) / 65536 * 65536;
-        hipError_t e = g_group_cache.get(n, &g->arena);
-        if (e != hipSuccess) {
-            // give the kept blocks back and try once more
-            (void)hipGetLastError();
-            g_group_cache.release();
-            g_buf_cache.release();
-            e = g_group_cache.get(n, &g->arena);
-        }
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
-            return fail(SIPF_ENOMEM, std::string("hipMalloc failed: ") + hipGetErrorString(e));
-        }
+        const hipError_t e = g_group_cache.get(n, &g->arena);
+        if (e != hipSuccess) return fail(SIPF_ENOMEM, std::string("hipMalloc failed: ") + hipGetErrorString(e));
         for (const Part& q : parts) *q.p = (char*)g->arena.p + q.off;
         return SIPF_OK;
     }
@@ -1001,10 +1002,8 @@ template <typename T> int load_positions(Group* g, int i, const void* X0, int on
     // host positions go through a temporary device buffer freed before return
     void* tmp = nullptr;
     const int64_t nv = (int64_t)g->in[i].dim * P;
-    if (hipMalloc(&tmp, nv * sizeof(T)) != hipSuccess) {
-        (void)hipGetLastError();
+    if (HipDevice::alloc(&tmp, nv * sizeof(T)) != hipSuccess)
         return fail(SIPF_ENOMEM, "hipMalloc failed for the staging buffer");
-    }
     hipError_t e = hipMemcpyAsync(tmp, X0, nv * sizeof(T), hipMemcpyHostToDevice, g->stream);
     if (e == hipSuccess) e = launch_load_positions<T>((const T*)tmp, P, L, d0, g->errs + i, g->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(g->stream);
@@ -1226,7 +1225,7 @@ template <typename T> int get_positions_typed(Group* g, int i, void* out, int on
     } else {
         void* tmp = nullptr;
         const size_t bytes = (size_t)d.dim * d.P * sizeof(T);
-        HIPCHK(hipMalloc(&tmp, bytes));
+        HIPCHK(HipDevice::alloc(&tmp, bytes));
         hipError_t e = launch_unsort<T>(&d, (T*)tmp, g->stream);
         if (e == hipSuccess) e = hipMemcpyAsync(out, tmp, bytes, hipMemcpyDeviceToHost, g->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(g->stream);
@@ -1424,10 +1423,7 @@ int adjoint_typed(Group* c, int64_t N, int K, const T* phibar_in, double* loss_o
     const int64_t nseg = (N + K - 1) / K;
     const size_t pos_bytes = (size_t)P * (3 * sizeof(T) + sizeof(uint32_t));
     auto need = [&](DevBuf& b, size_t n) -> int {
-        if (b.alloc(n) != hipSuccess) {
-            (void)hipGetLastError();
-            return fail(SIPF_ENOMEM, "adjoint: device allocation failed");
-        }
+        if (b.alloc(n) != hipSuccess) return fail(SIPF_ENOMEM, "adjoint: device allocation failed");
         return SIPF_OK;
     };
     DevBuf tape, ckpt, seg, Gseg, xbar, xbs, Gbar, phibar, abar, aN, scr, gs1, fdS, fdA, fdR, pdR, pdS, consts, acc,

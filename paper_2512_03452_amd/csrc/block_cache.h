@@ -8,6 +8,9 @@
 // A block carries the device it was allocated on: its owner may be destroyed,
 // from a finaliser for instance, while another device is current.
 //
+// Kept blocks never stand in the way of an allocation: allocate_or_empty frees
+// them and tries again before it reports that the memory is out.
+//
 // Api: the device calls (static; an Error that is zero on success), so that the
 // cache can be tested without a device:
 //   Error device(int* dev)               the current device
@@ -89,5 +92,14 @@ template <class Api> class BlockCache {
     std::mutex mu_;
     std::vector<Block> kept_;
 };
+
+// allocate() -> Error; when that says `full`, once more with every cache emptied.
+template <class Error, class Alloc, class... Caches>
+Error allocate_or_empty(Error full, Alloc allocate, Caches&... caches) {
+    const Error e = allocate();
+    if (e != full) return e;
+    (caches.release(), ...);
+    return allocate();
+}
 
 }  // namespace sipf

@@ -13,6 +13,7 @@ struct FakeDevice {
     static int current;
     static std::map<void*, std::pair<int, size_t>> live;  // pointer -> device, bytes
     static int freed;
+    static size_t room;  // bytes per device
     static char mem[1 << 16];
     static size_t used;
     static Error device(int* dev) {
@@ -20,6 +21,9 @@ struct FakeDevice {
         return 0;
     }
     static Error alloc(void** p, size_t n) {
+        size_t held = 0;
+        for (const auto& l : live) held += l.second.first == current ? l.second.second : 0;
+        if (held + n > room) return 2;
         *p = mem + used;  // addresses only: nothing is stored
         used += 16;
         live[*p] = {current, n};
@@ -33,6 +37,7 @@ struct FakeDevice {
 int FakeDevice::current = 0;
 std::map<void*, std::pair<int, size_t>> FakeDevice::live;
 int FakeDevice::freed = 0;
+size_t FakeDevice::room = 1 << 20;
 char FakeDevice::mem[1 << 16];
 size_t FakeDevice::used = 0;
 
@@ -90,5 +95,21 @@ int main() {
     check(FakeDevice::live.size() == 3, "a block above the limit is freed");
     cache.release();
     check(FakeDevice::live.empty() && FakeDevice::freed < 1000, "every block is freed once");
+
+    // a full device: the kept blocks of every cache go back, the blocks in use stay
+    FakeDevice::current = 0;
+    FakeDevice::room = 1000;
+    sipf::BlockCache<FakeDevice> other(1000);
+    auto allocate = [&](size_t n, void** p) {
+        return sipf::allocate_or_empty(2, [&] { return FakeDevice::alloc(p, n); }, cache, other);
+    };
+    check(cache.get(300, &a) == 0 && other.get(300, &b) == 0 && cache.get(200, &c) == 0, "three blocks");
+    cache.put(a);
+    other.put(b);
+    void *p = nullptr, *q = nullptr;
+    check(allocate(150, &p) == 0 && FakeDevice::live.size() == 4, "room for 150 beside the kept blocks");
+    check(allocate(600, &q) == 0 && FakeDevice::live.size() == 3, "600 once both caches are empty");
+    void* none = nullptr;
+    check(allocate(100, &none) == 2 && FakeDevice::live.count(c.p) == 1, "out of memory with nothing kept");
     return failures ? 1 : 0;
 }
