@@ -180,10 +180,10 @@ typedef struct sipf_params {
     int32_t  resort_every; /* re-sort period in steps; 0 = default: 8 (10 in the sorted
                               3-D pass; 6 in 3-D above H = 64), or fewer when in 3-D sqrt(2 mu tau n)
                               exceeds a quarter of a tile, in 2-D an item outgrows its LDS window */
-    int32_t  chunk;        /* max particles per work item of the particle pass (256..4096); 0 = default:
-                              4096 in 2-D and from 2^23 particles per 3-D group, else 3072.  3-D groups
-                              of P particles take items of about P/192 (at least 256) where that is
-                              smaller; the adjoint's reverse pass takes at most 4096 by default */
+    int32_t  chunk;        /* max particles per work item of the particle pass and of the adjoint's reverse
+                              pass (256..4096); 0 = default: 4096 in 2-D and from 2^23 particles per 3-D
+                              group, else 3072 (reverse pass 4096), and in 3-D groups of P particles about
+                              P/192 (at least 256) where that is smaller                         */
     uint64_t seed;         /* Philox key                                          */
     uint32_t instance;     /* fourth Philox counter word                          */
     uint32_t dim;          /* space dimension: 3 (0 means 3) or 2                 */
@@ -367,7 +367,9 @@ const char* sipf_last_error(void);
  * power of two, within the limits of sipf_params.tile), the
  * work-item size (1024, 2048, 3072, 4096), the re-sort period (2, 4, 6, 8, 16)
  * and, for FP32 3-D steps, the particle pass (sorted, two-phase), starting
- * from the defaults.  *best receives prm with tile, chunk, resort_every and
+ * from the defaults (item size: 3072 or 4096, whichever the default's limit is;
+ * below about 2e5 particles the default takes smaller items than the search
+ * tries).  *best receives prm with tile, chunk, resort_every and
  * particle_pass set to the fastest combination found, *ms_per_step its time.
  * Every trial context is destroyed before return; each needs the memory of
  * one sipf_init.  Synchronises.  Errors: those of sipf_init.
@@ -420,6 +422,11 @@ int sipf_batch_destroy(sipf_batch* b);
  *   normals of the stream contract (count x 6 in the given precision).
  * sipf_dbg_cells: the integer cell g = floor(X H / L) (count x 3 int32) that
  *   the particle pass uses for positions X (count x 3, precision of prm).
+ * sipf_dbg_plan: what sipf_init (n = 1) or sipf_batch_init would choose for n
+ * instances with these parameters and particle counts, without a device: out
+ * (4 + n int32) receives the largest work item of the particle pass, that of
+ * the adjoint's reverse pass, the sort keys per instance, the re-sort period
+ * and each instance's tile.
  * sipf_dbg_deposit: phi = I(sum_p w delta_{X_p}) with w = M0/count on the
  *   H^3 grid (the deposit of Algorithm 2 through the binning + LDS path).
  */
@@ -427,6 +434,7 @@ int sipf_dbg_philox(uint64_t seed, int64_t count, const uint32_t* ctr, uint32_t*
                     void* normals, int precision, void* hip_stream);
 int sipf_dbg_cells(const sipf_params* prm, int64_t count, const void* X, int32_t* cells,
                    void* hip_stream);
+int sipf_dbg_plan(int32_t n, const sipf_params* prm, const int64_t* P, int32_t* out);
 int sipf_dbg_deposit(const sipf_params* prm, int64_t count, const void* X, void* phi,
                      void* hip_stream);
 

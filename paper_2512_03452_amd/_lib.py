@@ -115,6 +115,7 @@ SIGNATURES = {
     "sipf_batch_destroy": [_vp],
     "sipf_dbg_philox": [_u64, _i64, _vp, _vp, _vp, ctypes.c_int, _vp],
     "sipf_dbg_cells": [_pp, _i64, _vp, _vp, _vp],
+    "sipf_dbg_plan": [_i32, _pp, ctypes.POINTER(_i64), ctypes.POINTER(_i32)],
     "sipf_dbg_deposit": [_pp, _i64, _vp, _vp, _vp],
     "sipf_deposit_noalloc": [_pp, _i64, _vp, _vp, _vp],
     "sipf_release_cached_memory": [],

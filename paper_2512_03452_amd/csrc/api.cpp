@@ -182,40 +182,40 @@ int default_resort(const sipf_params* p, int tile, bool sorted) {
     const double n = std::floor(q * q / spread);
     return (int)std::max(1.0, std::min(most, n));
 }
-// Largest work-item size where the parameters leave it open: in 3-D, 3072, and
-// 4096 from 2^23 particles per group; 2-D keeps 4096.  With several items per
-// CU the size trades per-item set-up (windows, barriers) against balance.
-// Measured (FP32, us per step, items of 4096 / 3072 / 2048): torus P = 1e7 289 /
-// 292 / 315; torus P = 6.5e6 224 / 215 / 231; 64-instance ensemble (P = 1.4e7)
+// Largest work-item size: the caller's, or where the parameters leave it open
+// 3072 in 3-D, and 4096 from 2^23 particles per group; 2-D keeps 4096.  With
+// several items per CU the size trades per-item set-up (windows, barriers) against
+// balance.  Measured (FP32, us per step, items of 4096 / 3072 / 2048): torus P = 1e7
+// 289 / 292 / 315; torus P = 6.5e6 224 / 215 / 231; 64-instance ensemble (P = 1.4e7)
 // 629 at 4096 / 741 at 2048.  2-D: P = 2^22 disk 265 / 272 (4096 / 2048).
 int max_chunk(const sipf_params* p, int64_t total_P) {
     if (p->chunk) return p->chunk;
     return dim_of(p) == 2 || total_P >= (int64_t(1) << 23) ? 4096 : 3072;
 }
-// Work-item size of a group: in 3-D, P / 192 in steps of 256 and at least 256,
-// where that is smaller.  An item is one workgroup's work from start to end, so
-// up to about one item per CU smaller items shorten the step.  Measured, us per
-// step: FP64 blob P = 1e4, H = 32, items of 256 / 1024 / 3072 particles: 28.3 /
-// 34.1 / 42.1; ball P = 97336, H = 46, 512 / 1024 / 3072: 38.0 / 40.1 / 49.2;
-// blob P = 2e5, H = 32, 512 / 1024 / 3072: 35.7 / 31.4 / 38.4; mixed P = 1e6,
-// H = 64, 1024 / 2048 / 3072: 71.1 / 56.1 / 56.9.
-int item_chunk(const sipf_params* p, int64_t total_P) {
-    const int most = max_chunk(p, total_P);
-    if (dim_of(p) == 2) return most;
+// P / 192 particles in steps of 256, at least 256 and at most `most`
+int chunk_for(int64_t total_P, int most) {
     return (int)std::min<int64_t>(most, std::max<int64_t>(256, (total_P / 192 + 128) / 256 * 256));
 }
-// Work-item size of the adjoint's per-segment sorts: the rule of item_chunk
-// with at most 4096, which one workgroup of the reverse pass holds.  An item
-// adds a window of float atomics to the cotangent grids and stages three, so
+// Work-item size of a group.  A size that the caller gives is taken as it is;
+// else, in 3-D, P / 192 where that is smaller than the largest default.  An item is
+// one workgroup's work from start to end, so up to about one item per CU smaller
+// items shorten the step.  Measured, us per step: FP64 blob P = 1e4, H = 32, items of
+// 256 / 1024 / 3072 particles: 28.3 / 34.1 / 42.1; ball P = 97336, H = 46, 512 / 1024
+// / 3072: 38.0 / 40.1 / 49.2; blob P = 2e5, H = 32, 512 / 1024 / 3072: 35.7 / 31.4 /
+// 38.4; mixed P = 1e6, H = 64, 1024 / 2048 / 3072: 71.1 / 56.1 / 56.9.
+int item_chunk(const sipf_params* p, int64_t total_P) {
+    const int most = max_chunk(p, total_P);
+    return p->chunk || dim_of(p) == 2 ? most : chunk_for(total_P, most);
+}
+// Work-item size of the adjoint's per-segment sorts: the caller's, or the rule of
+// item_chunk with at most 4096, which one workgroup of the reverse pass holds.  An
+// item adds a window of float atomics to the cotangent grids and stages three, so
 // larger items win as long as there is about one per CU.  Us per launch of the
 // reverse pass at items of 512 / 1024 / 2048 / 3072 / 4096: FP64 blob P = 1e5,
 // H = 32, 20.5 / 21.0 / 28.4 / 36.9 / 44.4; P = 5e5, H = 64, 131 / 87 / 82 / 60
 // / 65; P = 2e6 459 / 289 / 205 / 189 / 156; FP32 P = 2e6 232 / 150 / 105 / 97 /
 // 82.
-int default_adj_chunk(const sipf_params* p, int64_t P) {
-    const int most = p->chunk ? p->chunk : 4096;
-    return (int)std::min<int64_t>(most, std::max<int64_t>(256, (P / 192 + 128) / 256 * 256));
-}
+int default_adj_chunk(const sipf_params* p, int64_t P) { return p->chunk ? p->chunk : chunk_for(P, 4096); }
 
 }  // namespace
 
@@ -888,6 +888,13 @@ template <typename T> int alloc_direct(Group* g) {
     return SIPF_OK;
 }
 
+// Sort keys per instance: those of the instance with the most tiles.
+template <typename T> int group_keys(const Group* g) {
+    int nkeys = 1;
+    for (const Inst& I : g->in) nkeys = std::max(nkeys, pdesc_params<T>(I.prm, I.P, I.H, I.dim, I.tile).nkeys);
+    return sort_keys(nkeys);
+}
+
 template <typename T> int alloc_group(Group* g) {
     if (g->method == SIPF_METHOD_DIRECT) return alloc_direct<T>(g);
     const int n = (int)g->in.size();
@@ -924,10 +931,7 @@ template <typename T> int alloc_group(Group* g) {
         return fail(SIPF_EINVAL, "too many particles in one group");
     g->items_cap = (int)cap;
     g->nchunks = (int)chunks.size();
-    int nkeys = 1;
-    for (int i = 0; i < n; ++i)
-        nkeys = std::max(nkeys, pdesc_params<T>(g->in[i].prm, g->in[i].P, g->in[i].H, g->in[i].dim, g->in[i].tile).nkeys);
-    g->kstride = sort_keys(nkeys);
+    g->kstride = group_keys<T>(g);
     const size_t mk = (size_t)g->kstride;
     // first the tables and counters, which one copy fills
     Arena ar;
@@ -2170,6 +2174,21 @@ int sipf_dbg_cells(const sipf_params* prm, int64_t count, const void* X, int32_t
     else
         HIPCHK(launch_cells<double>((const double*)X, count, prm->H, (double)(prm->H / prm->L), cells, s));
     HIPCHK(hipStreamSynchronize(s));
+    return SIPF_OK;
+}
+
+int sipf_dbg_plan(int32_t n, const sipf_params* prm, const int64_t* P, int32_t* out) {
+    if (!out || !prm || !P || n < 1) return fail(SIPF_EINVAL, "bad arguments");
+    Group g;
+    const std::vector<const void*> X0((size_t)n, prm);  // not read: the plan does not depend on positions
+    const int rc = setup_group(&g, n, prm, P, X0.data(), 1, nullptr);
+    if (rc) return rc;
+    if (g.method == SIPF_METHOD_DIRECT) return fail(SIPF_EINVAL, "the direct SIPF method has no work items");
+    out[0] = g.chunk;
+    out[1] = g.adj_chunk;
+    out[2] = g.prec == SIPF_FP32 ? group_keys<float>(&g) : group_keys<double>(&g);
+    out[3] = g.resort;
+    for (int i = 0; i < n; ++i) out[4 + i] = g.in[i].tile;
     return SIPF_OK;
 }
 

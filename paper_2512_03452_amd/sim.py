@@ -346,6 +346,18 @@ def dbg_cells(X, **params):
     return out
 
 
+def dbg_plan(specs):
+    """What the library chooses for instances [(params dict, particle count), ...] (no device needed):
+    the largest work item of the particle pass (``chunk``) and of the reverse pass (``adj_chunk``),
+    sort ``keys`` per instance, the ``resort`` period and each instance's ``tile``."""
+    n = len(specs)
+    prm = (_lib.SipfParams * n)(*[_lib.default_params(**p) for p, _ in specs])
+    P = (ctypes.c_int64 * n)(*[c for _, c in specs])
+    out = (ctypes.c_int32 * (4 + n))()
+    check(_lib.load().sipf_dbg_plan(n, prm, P, out))
+    return dict(chunk=out[0], adj_chunk=out[1], keys=out[2], resort=out[3], tile=list(out[4:]))
+
+
 def dbg_deposit(X, **params):
     p = _lib.default_params(**params)
     X = torch.as_tensor(X).to(device="cuda", dtype=_dtype(p)).contiguous()
