@@ -1217,13 +1217,11 @@ template <typename T> int get_field_typed(Group* g, int i, int which, void* out,
     } else if (which == SIPF_FIELD_GRAD) {
         HIPCHK(hipMemcpyAsync(out, I.G, I.dim * ng * sizeof(T), kind, g->stream));
     } else if (which == SIPF_FIELD_ALPHA) {
-        // natural order on the device: straight into out, or by way of B1 (overwritten by the
-        // next step's first field pass before it is read) to the host or to a device address
-        // that is not aligned for whole complex values
-        const bool straight = on_device && (uintptr_t)out % sizeof(cplx_t<T>) == 0;
-        cplx_t<T>* nat = straight ? (cplx_t<T>*)out : (cplx_t<T>*)I.B1;
-        HIPCHK(launch_natural<T>(I.dim, H, (const cplx_t<T>*)I.alpha, nat, g->stream));
-        if (!straight) HIPCHK(hipMemcpyAsync(out, nat, 2 * nspec * sizeof(T), kind, g->stream));
+        // natural order on the device, in B1 (overwritten by the next step's first field pass
+        // before it is read), and from there a copy, which takes any address that out may be:
+        // host memory, memory of another device, not aligned for whole complex values
+        HIPCHK(launch_natural<T>(I.dim, H, (const cplx_t<T>*)I.alpha, (cplx_t<T>*)I.B1, g->stream));
+        HIPCHK(hipMemcpyAsync(out, I.B1, 2 * nspec * sizeof(T), kind, g->stream));
     } else {
         return fail(SIPF_EINVAL, "unknown field");
     }
