@@ -45,6 +45,18 @@ constexpr int FEW_KEYS = 4096, MANY_KEYS = 32768;
 // instead of 16, us per step: mixed P = 5e4, H = 64, 59.8 against 40.2 (FP64
 // 78.5 against 59.0), P = 2e4 42.9 against 36.1, P = 5e3 31.5 against 31.1.
 constexpr int MIN_WINDOW_ITEM = 16;
+// Work items that sparse tiles share (k_tile_scan): at most MERGE_ITEM particles
+// of a cube of eight tiles, of at most MERGE_TILE cells each, where more than
+// MERGE_TILES tiles are in use.
+constexpr uint32_t MERGE_ITEM = 256;
+constexpr int MERGE_TILE = 8;
+constexpr int MERGE_TILES = 1024;
+// Items whose few particles spread over many nodes: weights rounded at a scale
+// that follows from the particle count alone are coarser than FP32 weights there.
+constexpr int SPARSE_ITEM = 64;
+template <typename T> __device__ __forceinline__ bool sparse_item(const PartDesc<T>& a, int cnt) {
+    return (cnt < SPARSE_ITEM && a.H >= 16) || (a.nkeys > MERGE_TILES && cnt <= (int)MERGE_ITEM) || a.nkeys > FEW_KEYS;
+}
 
 // Waves per SIMD the registers of the two-phase FP64 step and of the
 // deposit-only and push-only passes of both precisions leave room for: four,
@@ -434,6 +446,19 @@ __device__ __forceinline__ bool deposit_fast(typename Fixed<T>::I* win, T x, T y
     return true;
 }
 
+// Adds 1 to the eight nodes of the particle's cell in the same window.
+template <typename T, bool P2>
+__device__ __forceinline__ void count_fast(typename Fixed<T>::I* win, T x, T y, T z, T hl, const Wrap<P2>& wr, int cx,
+                                           int cy, int cz, int nx, int ny, int nz) {
+    constexpr int D = Win<T>::D;
+    using U = typename Fixed<T>::U;
+    const int ix = wr(ifloor(x * hl) - cx), iy = wr(ifloor(y * hl) - cy), iz = wr(ifloor(z * hl) - cz);
+    if (ix >= nx || iy >= ny || iz >= nz) return;
+    U* w = reinterpret_cast<U*>(win) + mad24(mad24(ix, D, iy), D, iz);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) atomicAdd(w + ((1 + (q >> 2)) * D + 1 + ((q >> 1) & 1)) * D + 1 + (q & 1), (U)1);
+}
+
 // Window cells along one axis: n cells from relative cell o for an item whose
 // cells span [lo, hi] (mean: about `mean`), wanted with m cells of margin on
 // both sides, on a grid of H cells with at most `most` cells in the window.
@@ -532,6 +557,16 @@ template <typename T> struct GradRows {
 // their sort took 950 us, now 76).  Items of a few particles skip the
 // windows.
 //
+// The window's integers keep the weights' precision: items of many particles on
+// a compact box scale them by their particle count, within the quick rounding's
+// range; where few particles meet at a node (sparse_item, boxes wider than the
+// window) the particles in every node's cells are counted first, 8 LDS adds
+// against the deposit's 32, and the scale follows from the largest count.  Error
+// of rho against 64 bits, scale from the item's count / from the counts per node /
+// float atomics: uniform P = 2e4, H = 64 1.8e-7 / 6.8e-8 / 6.6e-8; torus P = 1e6,
+// H = 256, five steps after a sort 2.6e-6 / 7e-8 / 2.0e-7.  It costs the ring at
+// H = 256 9 of 434 us per step, runs of a few thousand particles 0.2 to 0.5 us.
+//
 // What bounds it: the LDS atomics and vector work of many items per workgroup
 // at large P, one item's chain of memory and LDS round trips at small P.
 // Hence: one barrier for the box; the gradient rows are loaded while the
@@ -540,7 +575,7 @@ template <typename T> struct GradRows {
 // code, in loops that are not unrolled (eight unrolled pushes with three
 // gathers each made 100 KB of code, more than the instruction cache; now 26 KB,
 // at the same time per particle).  Before and after, us per launch: H = 256,
-// P = 1e6 617 -> 177; torus P = 1e7, H = 128 190 -> 187 (with tile counts 243
+// P = 1e6 617 -> 186; torus P = 1e7, H = 128 190 -> 187 (with tile counts 243
 // -> 213); FP64 blob P = 2e6, H = 64 166 -> 101 (324 -> 131), its push-only
 // pass 117 -> 83; mixed P = 1e6, H = 64, the whole step, 58.5 -> 54.9.
 template <typename T, bool DEP, bool PUSH, int SCHEME, bool P2>
@@ -586,7 +621,6 @@ __device__ __forceinline__ void item_pass(const PartDesc<T>& a, int64_t beg, int
     }
     block_bounds3<PT / 64>(bx, by, bz, sh);
     const bool windows = cnt >= MIN_WINDOW_ITEM;
-    const bool fine = cnt <= PT;  // one particle per thread: weights at the full scale of the item
     // the item's mean cell, where its box outgrows a window
     int mx = 0, my = 0, mz = 0;
     constexpr int LEAST = D - 3 < G - 1 ? D - 3 : G - 1;
@@ -639,19 +673,53 @@ __device__ __forceinline__ void item_pass(const PartDesc<T>& a, int64_t beg, int
             int i0, wj, wk, nrep;
             plane_map(ny + 3, nz + 3, i0, wj, wk, nrep);
             for (int i = i0; i < nx + 3; i += nrep) win[(i * D + wj) * D + wk] = 0;
-            // 2^S with S = BITS - bitlength(ceil(11 cnt / 8)): |sum of F| <= 1.375 cnt per node
-            const int need = (11 * cnt + 7) / 8;
-            int S = Fixed<T>::BITS - (32 - __clz(need));
+        }
+        __syncthreads();
+        ticket.draw();
+        // 2^S with S as large as the node sums allow: |F| <= 1, so at most cnt
+        int S = 0;
+        bool fine = true;  // any S, else the quick rounding of deposit_fast
+        if (windows) {
+            int most = cnt;
+            const bool wide = max(max(pk_hi(bx) - pk_lo(bx), pk_hi(by) - pk_lo(by)), pk_hi(bz) - pk_lo(bz)) >= D - 3;
+            if constexpr (sizeof(T) == 4) {
+                fine = cnt <= PT || wide || sparse_item(a, cnt);
+                if (wide || sparse_item(a, cnt)) {
+                    // a sum is at most m (1 + 6 x 0.0642), m the largest number of particles in the eight
+                    // cells of a node: |F| <= 0.0642 at the outer nodes, whose 24 cells are six groups of
+                    // four that are among the eight of a neighbouring node
+#pragma unroll 1
+                    for (int j = tid; j < cnt; j += PT)
+                        count_fast<T>(win, gp(ix)[j], gp(iy)[j], gp(iz)[j], hl, wr, cx, cy, cz, nx, ny, nz);
+                    __syncthreads();
+                    int i0, wj, wk, nrep, m = 0;
+                    plane_map(ny + 3, nz + 3, i0, wj, wk, nrep);
+                    for (int i = i0; i < nx + 3; i += nrep) {
+                        m = max(m, (int)win[(i * D + wj) * D + wk]);
+                        win[(i * D + wj) * D + wk] = 0;
+                    }
+                    int* top = reinterpret_cast<int*>(sh);  // the bounds have been read
+                    m = wave_max_dpp(m);
+                    if ((tid & 63) == 63) top[tid >> 6] = m;
+                    __syncthreads();
+                    m = top[0];
+#pragma unroll
+                    for (int w = 1; w < PT / 64; ++w) m = max(m, top[w]);
+                    m = __builtin_amdgcn_readfirstlane(m);
+                    most = min(cnt, m + (m * 396) / 1024 + 1);
+                }
+            }
+            S = Fixed<T>::SUM_BITS - (32 - __clz(most));
+            if constexpr (sizeof(T) == 8) fine = cnt <= PT || (S > Magic<T>::MAXS && (wide || H <= D));
             if (!fine) S = min(Magic<T>::MAXS, S);
             scale = (T)ldexp(1.0, S);
             back = a.wmass * (T)ldexp(1.0, -S);
         }
-        __syncthreads();
-        ticket.draw();
         bool out = !windows;  // some particle of the thread is outside the window
         if (windows && fine) {
-            if (tid < cnt)
-                out = !deposit_fast<true>(win, px[0], py[0], pz[0], hl, wr, cx, cy, cz, nx, ny, nz, scale);
+#pragma unroll 1
+            for (int j = tid; j < cnt; j += PT)
+                out |= !deposit_fast<true>(win, gp(ix)[j], gp(iy)[j], gp(iz)[j], hl, wr, cx, cy, cz, nx, ny, nz, scale);
         } else if (windows) {
 #pragma unroll
             for (int k = 0; k < PPT; ++k)
@@ -880,8 +948,8 @@ __device__ __forceinline__ void load_cols(const PartDesc<float>& a, int64_t beg,
 
 // Whether an FP32 item can take the sorted pass (its box is checked there).
 __device__ __forceinline__ bool sorted_candidate(const PartDesc<float>& a, const WorkItem& w, int win_bytes) {
-    return a.ox == nullptr && w.cnt >= MIN_WINDOW_ITEM && a.H > Win<float>::D && a.H > Win<float>::G &&
-           win_bytes >= fused_bytes<float>();
+    return a.ox == nullptr && w.cnt >= SPARSE_ITEM && !sparse_item(a, w.cnt) && a.H > Win<float>::D &&
+           a.H > Win<float>::G && win_bytes >= fused_bytes<float>();
 }
 
 // FP32 work item in one loop, with the item kept sorted by cell between
@@ -982,8 +1050,7 @@ __device__ __forceinline__ bool item_sorted(const PartDesc<float>& a, int64_t be
             Gw[2 * G3 + o] = gp(a.G)[2 * H3 + node];
         }
     }
-    const int need = (11 * cnt + 7) / 8;
-    const int S = min(Magic<float>::MAXS, Fixed<float>::BITS - (32 - __clz(need)));
+    const int S = min(Magic<float>::MAXS, Fixed<float>::SUM_BITS - (32 - __clz(cnt)));  // as in item_pass
     const float scale = ldexpf(1.0f, S);
     const uint32_t step_n = *a.step + 1u;
     const size_t H3 = (size_t)H * H * H;
@@ -1418,9 +1485,6 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* p
 // mixed P = 1e5, H = 128, 144 / 95; ring P = 3e5, H = 256, 437 / 415.  Limits
 // of 128 / 256 / 640 / 1536 particles: 790 / 720 / 718 / 743 and, ring P = 3e6,
 // 474 / 474 / 477 / 479.
-constexpr uint32_t MERGE_ITEM = 256;
-constexpr int MERGE_TILE = 8;
-constexpr int MERGE_TILES = 1024;
 // Threads of the scan: eight keys each, or 1024 threads.
 constexpr int scan_threads(int keys) { return keys / 8 < 1024 ? keys / 8 : 1024; }
 template <typename T, int DIM, bool DIRECT, int KEYS>

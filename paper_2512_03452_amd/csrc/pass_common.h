@@ -42,18 +42,20 @@ template <typename T> __device__ __forceinline__ int ifloor(T v) { return (int)f
 // LDS run ~25x slower than integer ones on gfx950, so weights are rounded to
 // integers at a power-of-two scale 2^S chosen per work item so that no node
 // sum can overflow, summed exactly with integer LDS atomics, and converted
-// back once when the window is added to the grid.
+// back once when the window is added to the grid.  A sum of magnitude at most m
+// takes S = SUM_BITS - bitlength(m): m 2^S <= 2^SUM_BITS - 2^S, and 2^S is more
+// than the weights' rounding, half a unit each, adds up to.
 template <typename T> struct Fixed;
 template <> struct Fixed<float> {
     using I = int32_t;
     using U = uint32_t;
-    static constexpr int BITS = 30;
+    static constexpr int BITS = 30, SUM_BITS = 31;
     __device__ static I quant(float v) { return (I)rintf(v); }
 };
 template <> struct Fixed<double> {
     using I = long long;
     using U = unsigned long long;
-    static constexpr int BITS = 62;
+    static constexpr int BITS = 62, SUM_BITS = 63;
     __device__ static I quant(double v) { return (I)rint(v); }
 };
 
