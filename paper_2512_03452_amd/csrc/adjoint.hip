@@ -158,19 +158,26 @@ template <typename T> struct AdjShape;
 template <> struct AdjShape<float> { static constexpr int PT = 512, PPT = 8, WAVES = 4, G = 13, D = 15; };
 template <> struct AdjShape<double> { static constexpr int PT = 768, PPT = 6, WAVES = 3, G = 14, D = 13; };
 
-// Gbar accumulator: a term t (already scaled by 2^S) is added as round(t); S is
-// chosen per item so that every node sum stays below 2^E in magnitude.
+// Gbar accumulator: a term t (already scaled by 2^S) is added as round(t).  FP32:
+// S per item such that a node sum stays below 2^E, a little under the integers'
+// range for the terms' rounding (2^-16 of the bound, at least 2^15; half a unit for
+// each of up to 4096 particles is 2^11).  FP64: each term below 2^E, the quick
+// rounding's range; a sum of 4096 stays below 2^62 (a scale for the sum costs items
+// of 4096 twelve bits: error of dL/dX0 against 64 bits, P = 5e5, H = 64, 1.2e-14
+// instead of 2.8e-15).
 template <typename T> struct AdjFixed;
 template <> struct AdjFixed<float> {
     using I = int32_t;
     using U = uint32_t;
-    static constexpr int E = 30;
+    static constexpr int E = 31;
+    __device__ static double bound(int cnt, double term) { return (double)cnt * term * (1.0 + 0x1p-16); }
     __device__ static U q(float t) { return (U)(int32_t)rintf(t); }
 };
 template <> struct AdjFixed<double> {
     using I = long long;
     using U = unsigned long long;
     static constexpr int E = 50;
+    __device__ static double bound(int, double term) { return term; }
     __device__ static U q(double t) { return (U)Magic<double>::take(t + Magic<double>::M); }
 };
 
@@ -244,7 +251,7 @@ __device__ __forceinline__ void adj_item(const AdjDesc<T>& a, int64_t beg, int c
     // non-negative floats order like their bit patterns
     const int bm = block_bounds3_max<NW>(bx, by, bz, __float_as_int(bmax), sh);
     ticket.draw();
-    const double bound = (double)cnt * (double)a.chitau * (double)__int_as_float(bm);
+    const double bound = AdjFixed<T>::bound(cnt, (double)a.chitau * (double)__int_as_float(bm));
     const bool gwin = bound < 1e300;
     int mx = 0, my = 0, mz = 0;
     if (max(max(pk_hi(bx) - pk_lo(bx), pk_hi(by) - pk_lo(by)), pk_hi(bz) - pk_lo(bz)) >= min(G - 1, D - 3)) {

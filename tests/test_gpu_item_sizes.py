@@ -69,3 +69,23 @@ def test_reverse_pass(precision, wide, P, chunk):
     assert abs(dmu - omu) < tol * max(abs(omu), 1e-12)
     assert rel(dX0.cpu().numpy(), odX) < tol
     sim.close()
+
+
+@pytest.mark.parametrize("P", [1500, 4096])
+def test_reverse_pass_keeps_fp64(P):
+    """One FP64 item whose gradient cotangents carry a quarter of the gradient (large chi).
+
+    Rounding its 8 P terms at 2^-51 of the largest one changes the gradient by 7e-16, at 2^-51 of P times the
+    largest by 2.7e-12 (P = 4096; planted in the oracle); the rest of the FP64 pass adds some 1e-14.
+    """
+    H = 16
+    kw = dict(L=2.0, chi=200.0, mu=0.05, eps=1.0, k=1.0, M0=40.0, dt=1e-3, H=H, seed=21)
+    assert _largest(P, "adj_chunk", H=H, tile=H, chunk=4096, precision="fp64") == P
+    X0 = np.random.default_rng(1).uniform(-1.0, 1.0, (P, 3))
+    sim = pkg.Sim(X0, precision="fp64", tile=H, chunk=4096, **kw)
+    _, _, _, dX0 = sim.adjoint(3, 3)
+    _, odX, _, _ = oadj.loss_and_grad(X0, osipf.Params(**kw), 3)
+    err = rel(dX0.cpu().numpy(), odX)
+    print(f"reverse pass FP64 P={P}: {err:.1e}", flush=True)
+    assert err < 2e-13
+    sim.close()
