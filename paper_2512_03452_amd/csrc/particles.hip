@@ -751,10 +751,7 @@ __device__ __forceinline__ void item_pass(const PartDesc<T>& a, int64_t beg, int
     } else if (windows) {
         rows.load(a.G, H, wr, gcx, gcy, gcz, gnx + 1, gny + 1, gnz + 1);
     }
-    if (!DEP) {
-        if (!windows) __syncthreads();  // every wave has read the last draw (with windows: the bounds' barrier)
-        ticket.draw();
-    }
+    if (!DEP) ticket.draw();  // every wave has read the last draw: the box's barrier stands between
 
     if (PUSH) {
         T* Gw = reinterpret_cast<T*>(lds);

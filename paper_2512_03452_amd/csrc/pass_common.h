@@ -261,8 +261,8 @@ __device__ __forceinline__ int next_item(int* hdr, int n, int* slot) {
 
 // The same queue with the draw ahead of time: draw() once per item, by the
 // whole workgroup and after a barrier of that item (other waves may still be
-// reading the last draw), wherever its round trip is covered by
-// work that waits for no other memory; next() after the item.
+// reading the last draw; the box's reduction has one), wherever its round trip
+// is covered by work that waits for no other memory; next() after the item.
 struct Ticket {
     int* hdr;
     int n;
