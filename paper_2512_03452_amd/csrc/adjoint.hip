@@ -186,16 +186,6 @@ template <typename T> constexpr int adj_lds_bytes() {
     return 3 * A::G * A::G * A::G * (int)(sizeof(typename AdjFixed<T>::I) + sizeof(T)) + A::D * A::D * A::D * (int)sizeof(T);
 }
 
-// Window along one axis, in cells relative to the item's reference cell: n
-// cells from o for cells that span [lo, hi], wanted with m cells of margin on
-// both sides, at most `most` of them, around `mean` if they find no room.
-__device__ __forceinline__ void adj_axis(int lo, int hi, int m, int mean, int most, int H, int& o, int& n) {
-    const int nb = hi - lo + 1;
-    n = min(min(nb + 2 * m, most), H);
-    o = lo - (n - nb) / 2;
-    if (nb > n) o = max(lo, min(hi - n + 1, mean - n / 2));
-}
-
 template <typename T, int SCHEME>
 __device__ __forceinline__ void adj_item(const AdjDesc<T>& a, int64_t beg, int cnt, unsigned char* lds, int4* sh,
                                          const Ticket& ticket, double& chib, double& sb) {
@@ -270,9 +260,9 @@ __device__ __forceinline__ void adj_item(const AdjDesc<T>& a, int64_t beg, int c
     }
     // gradient windows (first cell, cells), Gbar then G in LDS; nodes = cells + 1
     int gox, goy, goz, gnx, gny, gnz;
-    adj_axis(pk_lo(bx), pk_hi(bx), a.gmargin, mx, G - 1, H, gox, gnx);
-    adj_axis(pk_lo(by), pk_hi(by), a.gmargin, my, G - 1, H, goy, gny);
-    adj_axis(pk_lo(bz), pk_hi(bz), a.gmargin, mz, G - 1, H, goz, gnz);
+    window_axis(pk_lo(bx), pk_hi(bx), a.gmargin, mx, G - 1, H, gox, gnx);
+    window_axis(pk_lo(by), pk_hi(by), a.gmargin, my, G - 1, H, goy, gny);
+    window_axis(pk_lo(bz), pk_hi(bz), a.gmargin, mz, G - 1, H, goz, gnz);
     gox = (gox + rx) & Hm;
     goy = (goy + ry) & Hm;
     goz = (goz + rz) & Hm;
@@ -282,9 +272,9 @@ __device__ __forceinline__ void adj_item(const AdjDesc<T>& a, int64_t beg, int c
     int dox = 0, doy = 0, doz = 0, dnx = 0, dny = 0, dnz = 0;
     T* Pw = Gw + 3 * G3;
     if (a.phibar != nullptr) {
-        adj_axis(pk_lo(bx), pk_hi(bx), 0, mx, D - 3, H, dox, dnx);
-        adj_axis(pk_lo(by), pk_hi(by), 0, my, D - 3, H, doy, dny);
-        adj_axis(pk_lo(bz), pk_hi(bz), 0, mz, D - 3, H, doz, dnz);
+        window_axis(pk_lo(bx), pk_hi(bx), 0, mx, D - 3, H, dox, dnx);
+        window_axis(pk_lo(by), pk_hi(by), 0, my, D - 3, H, doy, dny);
+        window_axis(pk_lo(bz), pk_hi(bz), 0, mz, D - 3, H, doz, dnz);
         dox = (dox + rx) & Hm;
         doy = (doy + ry) & Hm;
         doz = (doz + rz) & Hm;

@@ -343,40 +343,27 @@ __global__ __launch_bounds__(plane_threads<H>()) void k_fwd_planes(const FieldDe
         for (int i = 0; i < N1; ++i)
             r[q][i] = WIDE ? buf[Z::freq_at(n2 + i * N2, kz)] : Z::split(buf, tw, n2 + i * N2, kz);
         Dft<T, N1, -1>::run(r[q]);
-        if constexpr (N2 > 1) {
 #pragma unroll
-            for (int k = 1; k < N1; ++k) r[q][k] = cmul(r[q][k], tw[n2 * k]);
+        for (int k = 1; k < N1; ++k) r[q][k] = cmul(r[q][k], tw[n2 * k]);
+    }
+    __syncthreads();  // the rows are read, the columns overwrite them
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int u = tid + q * NT;
+        if (u < NI) {
+#pragma unroll
+            for (int k = 0; k < N1; ++k) buf[Z::freq_at(k * N2 + u / HH, u % HH)] = r[q][k];
         }
     }
-    if constexpr (N2 > 1) {
-        __syncthreads();  // the rows are read, the columns overwrite them
+    __syncthreads();
+    for (int u = tid; u < HH * N1; u += NT) {
+        const int kz = u % HH, k1 = u / HH;
+        V v[N2];
 #pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            const int u = tid + q * NT;
-            if (u < NI) {
+        for (int i = 0; i < N2; ++i) v[i] = buf[Z::freq_at(k1 * N2 + i, kz)];
+        Dft<T, N2, -1>::run(v);
 #pragma unroll
-                for (int k = 0; k < N1; ++k) buf[Z::freq_at(k * N2 + u / HH, u % HH)] = r[q][k];
-            }
-        }
-        __syncthreads();
-        for (int u = tid; u < HH * N1; u += NT) {
-            const int kz = u % HH, k1 = u / HH;
-            V v[N2];
-#pragma unroll
-            for (int i = 0; i < N2; ++i) v[i] = buf[Z::freq_at(k1 * N2 + i, kz)];
-            Dft<T, N2, -1>::run(v);
-#pragma unroll
-            for (int i = 0; i < N2; ++i) stg(out + (k1 * N2 + i) * HH + kz, v[i]);
-        }
-    } else {
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            const int u = tid + q * NT;
-            if (u < NI) {
-#pragma unroll
-                for (int k = 0; k < N1; ++k) stg(out + k * HH + u, r[q][k]);
-            }
-        }
+        for (int i = 0; i < N2; ++i) stg(out + (k1 * N2 + i) * HH + kz, v[i]);
     }
 }
 
@@ -402,8 +389,7 @@ enum { MODE_STEP = 0, MODE_GRAD = 1, MODE_ADJ_SRC = 2, MODE_ADJ_ACC = 3, MODE_RH
 // (ky, kz) (column c = ky_position (H/2 + 1) + kz), all H x rows of each: a
 // row of the block is KB contiguous values starting at a multiple of KB, one
 // aligned 128-byte line in FP32 (blocks of KB kz values of one ky straddled
-// two lines, since H/2 + 1 is odd).  Grids whose x transform is one register
-// DFT take 64 columns, a pencil per thread, and no LDS.
+// two lines, since H/2 + 1 is odd).
 //
 // H = N1 N2.  First- and last-stage items (n2, column) hold rows n2 + i N2,
 // groups (k1, column) hold the storage positions k1 N2 + i, i.e. the
@@ -411,8 +397,7 @@ enum { MODE_STEP = 0, MODE_GRAD = 1, MODE_ADJ_SRC = 2, MODE_ADJ_ACC = 3, MODE_RH
 // from the forward transform through the update into the inverse.  LDS carries
 // value q of a column at (q + q / N2) KB + column: four rows of a wave lie on
 // different banks in both stages.
-template <int H> constexpr int pencil_cols() { return Split<H>::N2 > 1 ? KB : 64; }
-template <int H> constexpr int pencil_threads() { return (pencil_cols<H>() * Split<H>::N1 * (Split<H>::N2 > 1) + 63) / 64 * 64 + (Split<H>::N2 > 1 ? 0 : 64); }
+template <int H> constexpr int pencil_threads() { return (KB * Split<H>::N1 + 63) / 64 * 64; }
 
 template <typename T, int H, int MODE>
 __global__ __launch_bounds__(pencil_threads<H>()) void k_xpencils(const FieldDesc<T>* __restrict__ fds) {
@@ -420,7 +405,8 @@ __global__ __launch_bounds__(pencil_threads<H>()) void k_xpencils(const FieldDes
     constexpr int HH = H / 2 + 1;
     constexpr int NC = H * HH;  // columns (ky, kz): the pitch of an x row in HBM
     constexpr int N1 = Split<H>::N1, N2 = Split<H>::N2;
-    constexpr int CB = pencil_cols<H>(), NT = pencil_threads<H>();
+    constexpr int CB = KB, NT = pencil_threads<H>();
+    static_assert(N2 > 1, "two stages");
     constexpr int NIN = MODE == MODE_ADJ_ACC || MODE == MODE_ADJ_ACC_SRC ? 3 : (MODE == MODE_STEP || MODE == MODE_RHO ? 1 : 0);
     constexpr int NOUT = MODE == MODE_STEP || MODE == MODE_GRAD ? 3 : (MODE == MODE_ADJ_ACC ? 0 : 1);
     // LDS for three grids at once where a block is small, so that their stages
@@ -428,8 +414,8 @@ __global__ __launch_bounds__(pencil_threads<H>()) void k_xpencils(const FieldDes
     // workgroups per CU (H = 256: 35 KB against 104)
     constexpr int NBUF = NIN == 3 || (NOUT == 3 && H <= 64) ? 3 : 1;
     constexpr int LEN = (H + N1) * CB;  // values per grid
-    __shared__ V lds[N2 > 1 ? NBUF * LEN : 1];
-    __shared__ V tw[N2 > 1 ? H : 1];
+    __shared__ V lds[NBUF * LEN];
+    __shared__ V tw[H];
     const FieldDesc<T>& fd = fds[blockIdx.y];
     const int c0 = blockIdx.x * CB;
     const int tid = threadIdx.x;
@@ -439,10 +425,10 @@ __global__ __launch_bounds__(pencil_threads<H>()) void k_xpencils(const FieldDes
     const int cc = min(col, NC - 1);
     const int kyp = cc / HH, kz = cc - kyp * HH;
     const int ky = perm_freq<H>(kyp);
-    const int k1 = N2 > 1 ? min(tid / CB, N1 - 1) : 0;  // the thread's group
-    constexpr int GN = N2 > 1 ? N2 : N1;                // its modes: position pos(i), frequency kx(i)
+    const int k1 = min(tid / CB, N1 - 1);  // the thread's group
+    constexpr int GN = N2;                 // its modes: position pos(i), frequency kx(i)
     auto pos = [&](int i) { return k1 * N2 + i; };
-    auto kx_of = [&](int i) { return N2 > 1 ? k1 + N1 * i : i; };
+    auto kx_of = [&](int i) { return k1 + N1 * i; };
     auto lat = [&](int q) { return (q + q / N2) * CB + tid % CB; };
     V al[GN];
     if constexpr (MODE != MODE_RHO) {
@@ -470,16 +456,7 @@ __global__ __launch_bounds__(pencil_threads<H>()) void k_xpencils(const FieldDes
     };
     // forward: the modes of the NIN input grids, z[d][i]
     V z[NIN > 0 ? NIN : 1][GN];
-    if constexpr (NIN > 0 && N2 == 1) {
-#pragma unroll
-        for (int d = 0; d < NIN; ++d) {
-#pragma unroll
-            for (int i = 0; i < N1; ++i) z[d][i] = ldg(fd.B1 + (size_t)d * H * NC + (size_t)i * NC + cc);
-        }
-        factors_ahead();
-#pragma unroll
-        for (int d = 0; d < NIN; ++d) Dft<T, N1, -1>::run(z[d]);
-    } else if constexpr (NIN > 0) {
+    if constexpr (NIN > 0) {
         constexpr int NI = NIN * CB * N2, Q = (NI + NT - 1) / NT;  // items (d, n2, column)
         V r[Q][N1];
 #pragma unroll
@@ -512,9 +489,9 @@ __global__ __launch_bounds__(pencil_threads<H>()) void k_xpencils(const FieldDes
             Dft<T, N2, -1>::run(z[d]);
         }
     } else {
-        if constexpr (N2 > 1) make_twiddles<T, H>(tw);
+        make_twiddles<T, H>(tw);
         factors_ahead();
-        if constexpr (N2 > 1) __syncthreads();
+        __syncthreads();
     }
     // the modes: al[i] becomes the spectrum whose (derivatives') inverse transform goes out
 #pragma unroll
@@ -557,50 +534,36 @@ __global__ __launch_bounds__(pencil_threads<H>()) void k_xpencils(const FieldDes
                 return cmake<V, T>(-xi * al[i].y, xi * al[i].x);
             }
         };
-        if constexpr (N2 == 1) {
+        constexpr int ND = NBUF == 3 && NOUT == 3 ? 3 : 1;  // grids per exchange
+        constexpr int NI = ND * CB * N2;
+        if constexpr (NIN == 3) __syncthreads();  // groups of all three grids are read
+#pragma unroll 1
+        for (int d0 = 0; d0 < NOUT; d0 += ND) {
+            if (d0 > 0) __syncthreads();  // the previous grid has been read
+            if (tid < CB * N1) {
 #pragma unroll
-            for (int d = 0; d < NOUT; ++d) {
-                V r[N1];
+                for (int d = 0; d < ND; ++d) {
+                    V r[N2];
 #pragma unroll
-                for (int i = 0; i < N1; ++i) r[i] = out_of(d, i);
-                Dft<T, N1, +1>::run(r);
-                if (ok) {
+                    for (int i = 0; i < N2; ++i) r[i] = out_of(d0 + d, i);
+                    Dft<T, N2, +1>::run(r);
 #pragma unroll
-                    for (int i = 0; i < N1; ++i) stg(fd.gspec + (size_t)d * H * NC + (size_t)i * NC + cc, r[i]);
+                    for (int i = 1; i < N2; ++i) r[i] = cmul(r[i], cconj(tw[i * k1]));
+#pragma unroll
+                    for (int i = 0; i < N2; ++i) lds[d * LEN + lat(pos(i))] = r[i];
                 }
             }
-        } else {
-            constexpr int ND = NBUF == 3 && NOUT == 3 ? 3 : 1;  // grids per exchange
-            constexpr int NI = ND * CB * N2;
-            if constexpr (NIN == 3) __syncthreads();  // groups of all three grids are read
-#pragma unroll 1
-            for (int d0 = 0; d0 < NOUT; d0 += ND) {
-                if (d0 > 0) __syncthreads();  // the previous grid has been read
-                if (tid < CB * N1) {
+            __syncthreads();
+            for (int u = tid; u < NI; u += NT) {
+                const int c = c0 + u % CB, n2 = u / CB % N2, d = u / (CB * N2);
+                V r[N1];
 #pragma unroll
-                    for (int d = 0; d < ND; ++d) {
-                        V r[N2];
+                for (int k = 0; k < N1; ++k) r[k] = lds[d * LEN + (k * N2 + n2 + k) * CB + u % CB];
+                Dft<T, N1, +1>::run(r);
+                if (c < NC) {
+                    V* o = fd.gspec + (size_t)(d0 + d) * H * NC + c;
 #pragma unroll
-                        for (int i = 0; i < N2; ++i) r[i] = out_of(d0 + d, i);
-                        Dft<T, N2, +1>::run(r);
-#pragma unroll
-                        for (int i = 1; i < N2; ++i) r[i] = cmul(r[i], cconj(tw[i * k1]));
-#pragma unroll
-                        for (int i = 0; i < N2; ++i) lds[d * LEN + lat(pos(i))] = r[i];
-                    }
-                }
-                __syncthreads();
-                for (int u = tid; u < NI; u += NT) {
-                    const int c = c0 + u % CB, n2 = u / CB % N2, d = u / (CB * N2);
-                    V r[N1];
-#pragma unroll
-                    for (int k = 0; k < N1; ++k) r[k] = lds[d * LEN + (k * N2 + n2 + k) * CB + u % CB];
-                    Dft<T, N1, +1>::run(r);
-                    if (c < NC) {
-                        V* o = fd.gspec + (size_t)(d0 + d) * H * NC + c;
-#pragma unroll
-                        for (int i = 0; i < N1; ++i) stg(o + (size_t)(n2 + i * N2) * NC, r[i]);
-                    }
+                    for (int i = 0; i < N1; ++i) stg(o + (size_t)(n2 + i * N2) * NC, r[i]);
                 }
             }
         }
@@ -635,59 +598,38 @@ __global__ __launch_bounds__(plane_threads<H>()) void k_inv_planes(const FieldDe
     const V* in = fd.gspec + ((size_t)d * H + ix) * H * HH;
     // along y: groups (k1, kz) of the positions k1 N2 + i, then items (n2, kz)
     constexpr int NG = HH * N1, NI = HH * N2;
-    if constexpr (N2 > 1) {
-        constexpr int Q = (NG + NT - 1) / NT;
-        V r[Q][N2];
+    constexpr int Q = (NG + NT - 1) / NT;
+    V r[Q][N2];
 #pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            const int u = tid + q * NT;
-            if (u < NG) {
+    for (int q = 0; q < Q; ++q) {
+        const int u = tid + q * NT;
+        if (u < NG) {
 #pragma unroll
-                for (int i = 0; i < N2; ++i) r[q][i] = ldg(in + (u / HH * N2 + i) * HH + u % HH);
-            }
+            for (int i = 0; i < N2; ++i) r[q][i] = ldg(in + (u / HH * N2 + i) * HH + u % HH);
         }
-        make_twiddles<T, H>(tw);
-        __syncthreads();
+    }
+    make_twiddles<T, H>(tw);
+    __syncthreads();
 #pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            const int u = tid + q * NT;
-            if (u < NG) {
-                Dft<T, N2, +1>::run(r[q]);
+    for (int q = 0; q < Q; ++q) {
+        const int u = tid + q * NT;
+        if (u < NG) {
+            Dft<T, N2, +1>::run(r[q]);
 #pragma unroll
-                for (int i = 1; i < N2; ++i) r[q][i] = cmul(r[q][i], cconj(tw[i * (u / HH)]));
+            for (int i = 1; i < N2; ++i) r[q][i] = cmul(r[q][i], cconj(tw[i * (u / HH)]));
 #pragma unroll
-                for (int i = 0; i < N2; ++i) buf[Z::freq_at(u / HH * N2 + i, u % HH)] = r[q][i];
-            }
+            for (int i = 0; i < N2; ++i) buf[Z::freq_at(u / HH * N2 + i, u % HH)] = r[q][i];
         }
-        __syncthreads();
-        for (int u = tid; u < NI; u += NT) {
-            const int kz = u % HH, n2 = u / HH;
-            V v[N1];
+    }
+    __syncthreads();
+    for (int u = tid; u < NI; u += NT) {
+        const int kz = u % HH, n2 = u / HH;
+        V v[N1];
 #pragma unroll
-            for (int k = 0; k < N1; ++k) v[k] = buf[Z::freq_at(k * N2 + n2, kz)];
-            Dft<T, N1, +1>::run(v);
+        for (int k = 0; k < N1; ++k) v[k] = buf[Z::freq_at(k * N2 + n2, kz)];
+        Dft<T, N1, +1>::run(v);
 #pragma unroll
-            for (int i = 0; i < N1; ++i) buf[Z::freq_at(i * N2 + n2, kz)] = v[i];
-        }
-    } else {
-        constexpr int Q = (NI + NT - 1) / NT;
-        V v[Q][N1];
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            const int u = min(tid + q * NT, NI - 1);
-#pragma unroll
-            for (int k = 0; k < N1; ++k) v[q][k] = ldg(in + k * HH + u);
-        }
-        make_twiddles<T, H>(tw);
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            const int u = tid + q * NT;
-            if (u < NI) {
-                Dft<T, N1, +1>::run(v[q]);
-#pragma unroll
-                for (int i = 0; i < N1; ++i) buf[Z::freq_at(i, u)] = v[q][i];
-            }
-        }
+        for (int i = 0; i < N1; ++i) buf[Z::freq_at(i * N2 + n2, kz)] = v[i];
     }
     __syncthreads();
     Z::template inverse<NT>(buf, tw, reinterpret_cast<V*>(fd.G + ((size_t)d * H + ix) * H * H));
@@ -822,7 +764,7 @@ static hipError_t fwd_planes_h(const FieldDesc<T>* fd, int count, int ncomp, boo
 }
 template <typename T, int H>
 static hipError_t xpencils_h(const FieldDesc<T>* fd, int count, int mode, hipStream_t s) {
-    const dim3 g((H * (H / 2 + 1) + pencil_cols<H>() - 1) / pencil_cols<H>(), count), b(pencil_threads<H>());
+    const dim3 g((H * (H / 2 + 1) + KB - 1) / KB, count), b(pencil_threads<H>());
     switch (mode) {
         case MODE_STEP: launch_kernel((k_xpencils<T, H, MODE_STEP>), g, b, 0, s, fd); break;
         case MODE_GRAD: launch_kernel((k_xpencils<T, H, MODE_GRAD>), g, b, 0, s, fd); break;

@@ -459,17 +459,6 @@ __device__ __forceinline__ void count_fast(typename Fixed<T>::I* win, T x, T y, 
     for (int q = 0; q < 8; ++q) atomicAdd(w + ((1 + (q >> 2)) * D + 1 + ((q >> 1) & 1)) * D + 1 + (q & 1), (U)1);
 }
 
-// Window cells along one axis: n cells from relative cell o for an item whose
-// cells span [lo, hi] (mean: about `mean`), wanted with m cells of margin on
-// both sides, on a grid of H cells with at most `most` cells in the window.
-// Cells that find no room are the item's outermost ones.
-__device__ __forceinline__ void window_axis(int lo, int hi, int m, int mean, int most, int H, int& o, int& n) {
-    const int nb = hi - lo + 1;
-    n = min(min(nb + 2 * m, most), H);
-    o = lo - (n - nb) / 2;  // spare cells on both sides
-    if (nb > n) o = max(lo, min(hi - n + 1, mean - n / 2));
-}
-
 // Trilinear gather from a fixed-stride window (node (i, j, k) at (i G + j) G + k,
 // three planes of G^3) whose first cell is (cx, cy, cz); false if the cell is
 // not one of the window's (nx, ny, nz).

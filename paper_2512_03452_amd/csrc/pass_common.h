@@ -223,17 +223,15 @@ template <bool P2> struct Wrap {
     }
 };
 
-// axis_window for any grid size
-template <bool P2>
-__device__ __forceinline__ void axis_window(int r, int lo, int hi, const Wrap<P2>& wr, int& o, int& W) {
-    const int w = hi - lo + 1;
-    if (w >= wr.H) {
-        o = 0;
-        W = wr.H;
-    } else {
-        o = wr(r + lo);
-        W = w;
-    }
+// Window cells along one axis: n cells from relative cell o for an item whose
+// cells span [lo, hi] (mean: about `mean`), wanted with m cells of margin on
+// both sides, on a grid of H cells with at most `most` cells in the window.
+// Cells that find no room are the item's outermost ones.
+__device__ __forceinline__ void window_axis(int lo, int hi, int m, int mean, int most, int H, int& o, int& n) {
+    const int nb = hi - lo + 1;
+    n = min(min(nb + 2 * m, most), H);
+    o = lo - (n - nb) / 2;  // spare cells on both sides
+    if (nb > n) o = max(lo, min(hi - n + 1, mean - n / 2));
 }
 
 // Work queue of the persistent item passes.  The item list's header holds the
