@@ -29,6 +29,8 @@
 // and writes LDS.  H = 2048, FP32, us per launch, before and after: forward 29.3
 // -> 11.7, x rows 57.4 -> 29.3, inverse 61.1 -> 21.9 (H = 4096, the whole step
 // at P = 1e5, 637 -> 358).
+#include <algorithm>
+
 #include "internal.h"
 #include "lds_fft.h"
 #include "pass_common.h"
@@ -166,16 +168,13 @@ template <typename T, int H> __device__ __forceinline__ cplx_t<T> ixi(const Fiel
     return cmake<cplx_t<T>, T>(-xi * a.y, xi * a.x);
 }
 
-// threads of the x pass: one middle-stage item each, two threads per item at
-// H = 2048, whose LDS holds two workgroups (152 against 155 us per step of the
-// critical-mass run; FP64 162 against 172)
+// Threads of the x pass: one group of frequencies each, the group whose modes the
+// thread carries from the forward to the inverse transform, and at least two waves.
+// (Half as many at H = 2048, one per middle-stage item, two groups each: the
+// critical-mass run 155 instead of 152 us per step, FP64 172 instead of 162.)
 template <typename T, int H> constexpr int xrow_threads() {
-    if constexpr (H > 256) {
-        constexpr int n = Rows2<T, H>::K * 16 * Fft16<T, H>::N2 * (H == 2048 ? 2 : 1);
-        return n < 128 ? 128 : n;
-    } else {
-        return 256;
-    }
+    if constexpr (H > 256) return std::max(128, Rows2<T, H>::K * Fft16<T, H>::G3);
+    else return 256;
 }
 
 template <typename T, int H, int MODE>
