@@ -30,6 +30,14 @@
 // 37; H = 128 11.9 / 17.5 / 18.2 -> 11.4 / 16.0 / 19.7; H = 64 5.0 / 6.0 / 7.1 ->
 // 5.3 / 6.6 / 6.9; H = 8 4.4 / 3.7 / 3.3 -> 3.5 / 2.8 / 2.6.
 //
+// The slower ones, from registers and counters: the values that wait for the
+// other half of a stage are held in registers and the padded addresses cost VALU
+// work.  k_inv_planes at H = 128 takes 86 registers instead of 58, so a CU holds one of
+// its 1024-thread workgroups instead of two and the 384 planes take two rounds
+// (VALU instructions +13 %, LDS waits -80 %); k_inv_zrows +16 % VALU instructions;
+// the forward and x passes of a single H = 64 grid have half and a quarter of the
+// waves in flight.
+//
 // The LDS FFT (lds_fft.h) leaves the forward transform in a digit-permuted
 // order and takes that order back in the inverse; the x and y frequency axes
 // of the stored spectra use it.

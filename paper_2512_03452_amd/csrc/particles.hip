@@ -6,11 +6,11 @@
 // Particles are kept approximately sorted by tile (T^3 cells, tiles in Morton
 // order) by a periodic counting sort.  A workgroup takes a contiguous chunk of
 // the sorted array (a work item), measures the bounding box of the chunk's
-// cells, and, when the box plus the stencil reach (-1..+2) fits, accumulates
-// the deposit in an LDS window in fixed point with integer LDS atomics, then
-// adds the window into the global grid once.  A chunk whose box does not fit
-// (sparse regions, long drift since the last sort) deposits straight into the
-// global grid with atomics; the result is the same sum in a different order.
+// cells, accumulates the deposit in an LDS window around them in fixed point with
+// integer LDS atomics, and adds the window into the global grid once.  Where the
+// box is wider than the window (sparse regions, long drift since the last sort)
+// the window keeps to the chunk's middle and the particles outside it add to the
+// global grid with float atomics, as do all particles of a chunk of a few.
 // Two forms of the FP32 pass: the two-phase one (deposit all of an item's
 // particles, then stage the gradient window and push them) and the sorted one
 // (each item kept sorted by cell between steps, runs of equal cells summed in
@@ -1461,9 +1461,11 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* p
 //
 // Sparse tiles share an item: eight tiles that form a cube of twice the side
 // (consecutive keys, all with one thread) and hold at most MERGE_ITEM
-// particles together are one item, if such a cube is no wider than a window
-// (tiles of at most MERGE_TILE cells) and more than MERGE_TILES tiles are in
-// use, about what the chip holds at once.  An item of a few particles costs its
+// particles together are one item, where tiles are of at most MERGE_TILE cells and
+// more than MERGE_TILES of them in use, about what the chip holds at once.  A cube of
+// 8-cell tiles spans 16 cells: the deposit window (16) holds it just sorted, the
+// gradient windows (14 cells in FP32, 12 in FP64) its middle, and the particles
+// outside gather from the grid.  An item of a few particles costs its
 // window's clearing, staging and flush all the same; dense tiles keep items
 // and windows of their own, and a few sparse ones their parallelism (mixed
 // P = 5000, H = 64, 390 tiles in use: 39.8 us per step shared, 32.0 apart).  Us
