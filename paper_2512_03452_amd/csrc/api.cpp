@@ -131,18 +131,13 @@ bool sorted_pass(const sipf_params* p, int n) {
 // above.
 //
 // P: the instance's particle count (0: at most 16 tiles per axis, as for a
-// tile that callers pass, and in a group whose instances do not all take more:
-// its sort would count the 32768 keys of the largest for each of them).  H = 256
-// takes 32 tiles per axis from MANY_TILES_P
+// tile that callers pass).  H = 256 takes 32 tiles per axis from MANY_TILES_P
 // particles on: 16-cell tiles fill a window when just sorted and leave it with
 // the first steps, while a sort into 32768 keys costs some 30 us more.  Us per
 // step with 16-cell / 8-cell tiles at their best periods: ring P = 1e5 413 /
 // 414, 3e5 443 / 415, 1e6 542 / 424, 3e6 792 / 461; mixed P = 1e6
 // 839 / 666.
 constexpr int64_t MANY_TILES_P = int64_t(1) << 18;
-bool takes_many_tiles(const sipf_params* p, int64_t P) {
-    return dim_of(p) == 3 && p->H == 256 && p->tile == 0 && P >= MANY_TILES_P;
-}
 int default_tile(const sipf_params* p, bool sorted, int64_t P) {
     const int least = std::min(p->H, sorted ? 8 : 4);
     if (dim_of(p) == 3 && !is_pow2(p->H)) {
@@ -155,7 +150,7 @@ int default_tile(const sipf_params* p, bool sorted, int64_t P) {
         return t;
     }
     int t = p->tile ? p->tile : (p->H >= 128 ? 8 : (p->H >= 16 ? std::max(least, p->H / 8) : p->H));
-    if (p->H / t > 16 && !takes_many_tiles(p, P)) t = p->H / 16;
+    if (p->H / t > 16 && P < MANY_TILES_P) t = p->H / 16;
     return t;
 }
 // Re-sort period.  3-D: every 8 steps (10 in the sorted pass) up to H = 64 and
@@ -1165,11 +1160,7 @@ int setup_group(Group* g, int32_t n, const sipf_params* prm, const int64_t* P, c
     g->stream = (hipStream_t)hip_stream;
     g->sorted = sorted_pass(&prm[0], n);
     int64_t total_P = 0;
-    bool many = true;
-    for (int i = 0; i < n; ++i) {
-        total_P += P[i];
-        many = many && takes_many_tiles(&prm[i], P[i]);
-    }
+    for (int i = 0; i < n; ++i) total_P += P[i];
     g->chunk = item_chunk(&prm[0], total_P);
     g->adj_chunk = default_adj_chunk(&prm[0], total_P);
     g->win_bytes = particle_window_bytes(g->prec == SIPF_FP64);
@@ -1180,7 +1171,7 @@ int setup_group(Group* g, int32_t n, const sipf_params* prm, const int64_t* P, c
         I.P = P[i];
         I.H = prm[i].H;
         I.dim = dim_of(&prm[i]);
-        I.tile = default_tile(&prm[i], g->sorted, many ? P[i] : 0);
+        I.tile = default_tile(&prm[i], g->sorted, P[i]);
         const int resort = default_resort(&prm[i], I.tile, g->sorted);
         g->resort = i == 0 ? resort : std::min(g->resort, resort);
         if (!is_pow2(I.H)) g->pow2 = false;

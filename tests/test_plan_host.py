@@ -1,6 +1,6 @@
 """What the library chooses before it runs (sipf_dbg_plan): a work-item size that
 the caller gives is taken as it is, in both passes, and left open it follows the
-particle count; a batch's sort keys."""
+particle count."""
 
 import pytest
 
@@ -31,19 +31,6 @@ def test_item_size_left_open(P, chunk, adj):
 def test_sizes_of_the_tuner_are_four_different_plans():
     plans = [dbg_plan([(dict(H=32, chunk=c), 40000)])["chunk"] for c in (1024, 2048, 3072, 4096)]
     assert plans == [1024, 2048, 3072, 4096]
-
-
-def test_one_finest_grid_does_not_set_the_batchs_sort():
-    big, small = (dict(H=256), 1 << 18), (dict(H=32), 5000)
-    p = dbg_plan([big])
-    assert p["keys"] == 32768 and p["tile"] == [8]
-    p = dbg_plan([big, big])
-    assert p["keys"] == 32768 and p["tile"] == [8, 8]
-    p = dbg_plan([small, big, small])
-    assert p["keys"] == 4096 and p["tile"] == [8, 16, 8]
-    p = dbg_plan([big, (dict(H=256), (1 << 18) - 1)])
-    assert p["keys"] == 4096 and p["tile"] == [16, 16]
-    assert dbg_plan([(dict(H=256, tile=16), 1 << 20)])["keys"] == 4096
 
 
 def test_invalid_arguments():
