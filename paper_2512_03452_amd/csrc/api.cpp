@@ -137,6 +137,12 @@ bool sorted_pass(const sipf_params* p, int n) {
 // step with 16-cell / 8-cell tiles at their best periods: ring P = 1e5 413 /
 // 414, 3e5 443 / 415, 1e6 542 / 424, 3e6 792 / 461; mixed P = 1e6
 // 839 / 666.
+//
+// In a batch one such instance gives every instance's tables 32768 keys (256 KB
+// each).  Us per step, 16-cell / 8-cell tiles: five balls of 2^20 in each of H = 8 .. 256
+// 3565 / 3012; one ball of 2^18 at H = 256 beside 100 of 2000 particles at H = 16
+// 477 / 437, beside 500 545 / 541, beside 1000 661 / 668, beside 100 of 1e5 at H = 64
+// 1017 / 1012.
 constexpr int64_t MANY_TILES_P = int64_t(1) << 18;
 int default_tile(const sipf_params* p, bool sorted, int64_t P) {
     const int least = std::min(p->H, sorted ? 8 : 4);

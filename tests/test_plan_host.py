@@ -33,6 +33,15 @@ def test_sizes_of_the_tuner_are_four_different_plans():
     assert plans == [1024, 2048, 3072, 4096]
 
 
+def test_tiles_of_the_finest_grid():
+    big, small = (dict(H=256), 1 << 18), (dict(H=32), 5000)
+    assert dbg_plan([big]) == dict(dbg_plan([big]), keys=32768, tile=[8])
+    assert dbg_plan([small, big]) == dict(dbg_plan([small, big]), keys=32768, tile=[8, 8])
+    few = dbg_plan([(dict(H=256), (1 << 18) - 1)])
+    assert few["keys"] == 4096 and few["tile"] == [16]
+    assert dbg_plan([(dict(H=256, tile=16), 1 << 20)])["keys"] == 4096
+
+
 def test_invalid_arguments():
     lib = _lib.load()
     assert lib.sipf_dbg_plan(1, None, None, None) == _lib.SIPF_EINVAL
