@@ -350,7 +350,8 @@ int sipf_profile_read(sipf_ctx* ctx, double* ms, int64_t* launches);
 int sipf_save(sipf_ctx* ctx, const char* path);
 int sipf_load(const char* path, void* hip_stream, sipf_ctx** out);
 
-/* Release the context and its device memory (NULL is a no-op).  Up to 1 GiB per
+/* Release the context and its device memory (NULL is a no-op); waits for the
+ * context's device, whichever device is current.  Up to 1 GiB per
  * device of the memory of destroyed contexts and batches is kept for the next
  * ones (sipf_release_cached_memory returns it, and so does any allocation of
  * the library for which the device is too full). */

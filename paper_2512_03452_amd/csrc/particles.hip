@@ -564,7 +564,7 @@ template <typename T> struct GradRows {
 // code, in loops that are not unrolled (eight unrolled pushes with three
 // gathers each made 100 KB of code, more than the instruction cache; now 26 KB,
 // at the same time per particle).  Before and after, us per launch: H = 256,
-// P = 1e6 617 -> 186; torus P = 1e7, H = 128 190 -> 187 (with tile counts 243
+// P = 1e6 617 -> 177 (55 with 8-cell tiles); torus P = 1e7, H = 128 190 -> 187 (with tile counts 243
 // -> 213); FP64 blob P = 2e6, H = 64 166 -> 101 (324 -> 131), its push-only
 // pass 117 -> 83; mixed P = 1e6, H = 64, the whole step, 58.5 -> 54.9.
 template <typename T, bool DEP, bool PUSH, int SCHEME, bool P2>
